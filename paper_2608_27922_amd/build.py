@@ -13,7 +13,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdensitykv.so")
-SOURCES = ["dkv_api.cpp", "dkv_update.hip", "dkv_gram_mfma.hip", "dkv_attention.hip", "dkv_sequential.hip"]
+# (source, extra flags): the Gram stages are compiled once per descriptor geometry
+SOURCES = [("dkv_api.cpp", []), ("dkv_update.hip", []), ("dkv_attention.hip", []), ("dkv_sequential.hip", [])] + [
+    ("dkv_gram_mfma.hip", [f"-DDKV_GRAM_DESC={d}", f"-DDKV_GRAM_KV={kv}"]) for d, kv in ((64, 0), (128, 0), (128, 1), (256, 1))]
 ARCH = "gfx950"
 
 FLAGS = [
@@ -35,9 +37,10 @@ def build(verbose: bool = False) -> str:
     os.makedirs(obj_dir, exist_ok=True)
     hipcc = _hipcc()
 
-    def compile_one(src):
-        obj = os.path.join(obj_dir, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc, "-x", "hip", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    def compile_one(unit):
+        src, extra = unit
+        obj = os.path.join(obj_dir, "_".join([os.path.splitext(src)[0]] + [x.split("=")[1] for x in extra]) + ".o")
+        cmd = [hipcc, "-x", "hip", *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")

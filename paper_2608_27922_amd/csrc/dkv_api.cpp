@@ -32,6 +32,7 @@ size_t workspace_layout(int B, int G, int Mcap, int N, int d, Workspace *ws, cha
   w.r_star = (int32_t *)take((size_t)G * 4);
   w.n_ev = (int32_t *)take(Bz * 4);
   w.m_new = (int32_t *)take(Bz * 4);
+  w.whole = w.m_new;
   w.cnorm = (float *)take(Bz * Nz * 4);
   w.bs = (float *)take(Bz * Mz * 4);
   w.acol = (int64_t *)take(Bz * Nz * 8);

@@ -424,7 +424,7 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
   const int x = bx * 32 * W + wave * 32 + n;
   const int m = ws.m[b];
   const int c0 = by * kColsPerSplit;
-  if (c0 >= m) return;
+  if (c0 >= m || ws.whole[b] == 2) return;  // the order of a block that enters whole is not needed
   const int ncols = min(kColsPerSplit, m - c0);
   constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
   __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
@@ -688,6 +688,9 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   else if constexpr (MODE == RS_SURV_EV) nrows = n_surv;
   else nrows = rs;
   if ((int)bx * kRowsPerWG >= nrows) return;
+  if constexpr (MODE == RS_FIXUP) {
+    if (ws.whole[b]) return;  // no state survives
+  }
   // columns of this workgroup: [c0, c1) of the mode's column list
   int c0 = 0, c1 = 0;
   if constexpr (MODE == RS_CHUNK) {  // prefixes [cfirst, clim) of the order, 1,024 per split
@@ -1450,7 +1453,7 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
   const int b = blockIdx.y;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, n = l & 31, hw = l >> 5;
   const int m = ws.m[b], R = ws.R[b];
-  if ((int)blockIdx.x * 32 * kWaves >= m) return;  // whole workgroup (the stages have barriers)
+  if ((int)blockIdx.x * 32 * kWaves >= m || ws.whole[b]) return;  // whole workgroup (the stages have barriers)
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   const int v = blockIdx.x * 32 * kWaves + wave * 32 + n;
   const bool rv = v < m;
@@ -1564,7 +1567,7 @@ __global__ __launch_bounds__(256) void k_cross_plan(Geom g, Workspace ws, int fo
   const int grp = blockIdx.x * 256 + threadIdx.x;
   if (grp >= g.G) return;
   const int b0 = grp * g.gs, R = ws.R[b0];
-  bool decided = R <= kCrossFirst;  // the first part tested every prefix
+  bool decided = R <= kCrossFirst || ws.whole[b0];  // the first part tested every prefix, or no search is needed
   for (int j = 0; j < g.gs && !decided; ++j) {
     const int b = b0 + j;
     decided = ws.crossed[b] > max(0, ws.m[b] + R - ws.M[b]);
@@ -1607,7 +1610,7 @@ __global__ __launch_bounds__(256) void k_gather_sorted(const void *seg_k, const 
   const int j0 = r0 + blockIdx.x * RPP * kGatherRows + threadIdx.x / CH;
   const size_t nb = (size_t)b * g.N;
   if (r0 + (int)blockIdx.x * RPP * kGatherRows >= r1) return;  // whole workgroup
-  if (second && !ws.more[b / g.gs]) return;
+  if (second ? !ws.more[b / g.gs] : ws.whole[b] != 0) return;
   const Desc src{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
   // loads from clamped (in-range) rows, unconditional so that they overlap
   int xs[kGatherRows];
@@ -1746,33 +1749,26 @@ void mfma_score_d(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, c
   else f ? mfma_score_impl<D, 4, true, KV>(bank, seg, g, p, score_q, score_f, density, ws, s) : mfma_score_impl<D, 4, false, KV>(bank, seg, g, p, score_q, score_f, density, ws, s);
 }
 
-inline bool kv_geometry(const Prm &p) { return (p.flags & DKV_POLICY_KV_DESCRIPTOR) != 0; }
-
 }  // namespace
 
+// The library compiles this file once per descriptor geometry (DKV_GRAM_DESC =
+// descriptor dimension, DKV_GRAM_KV = concatenated [K; V] rows), in parallel;
+// dkv_internal.hpp declares the four pairs of launchers.
+#define DKV_CAT2(a, b, c) a##b##_kv##c
+#define DKV_CAT(a, b, c) DKV_CAT2(a, b, c)
+
 // Stage launchers used by the update sequence for bf16 banks:
-// 0 score, 4 ordered copy, 1 crossing, 2 r* fix-up, 3 maintenance.  The
-// descriptor dimension is the key dimension, or twice it for [K; V].
-void launch_gram_mfma(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
-                      const dkv_update_out &out, const Workspace &ws, hipStream_t s, int stage) {
-  if (kv_geometry(p)) {
-    if (g.d == 128) mfma_stage_d<256, true>(bank, seg, g, p, out, ws, s, stage);
-    else mfma_stage_d<128, true>(bank, seg, g, p, out, ws, s, stage);
-  } else {
-    if (g.d == 128) mfma_stage_d<128, false>(bank, seg, g, p, out, ws, s, stage);
-    else mfma_stage_d<64, false>(bank, seg, g, p, out, ws, s, stage);
-  }
+// 0 score, 4 ordered copy, 1 crossing, 2 r* fix-up, 3 maintenance.
+void DKV_CAT(launch_gram_d, DKV_GRAM_DESC, DKV_GRAM_KV)(const dkv_bank &bank, const dkv_segment &seg, const Geom &g,
+                                                        const Prm &p, const dkv_update_out &out, const Workspace &ws,
+                                                        hipStream_t s, int stage) {
+  mfma_stage_d<DKV_GRAM_DESC, DKV_GRAM_KV != 0>(bank, seg, g, p, out, ws, s, stage);
 }
 
-void launch_score_mfma(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
-                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws, hipStream_t s) {
-  if (kv_geometry(p)) {
-    if (g.d == 128) mfma_score_d<256, true>(bank, seg, g, p, score_q, score_f, density, ws, s);
-    else mfma_score_d<128, true>(bank, seg, g, p, score_q, score_f, density, ws, s);
-  } else {
-    if (g.d == 128) mfma_score_d<128, false>(bank, seg, g, p, score_q, score_f, density, ws, s);
-    else mfma_score_d<64, false>(bank, seg, g, p, score_q, score_f, density, ws, s);
-  }
+void DKV_CAT(launch_score_d, DKV_GRAM_DESC, DKV_GRAM_KV)(const dkv_bank &bank, const dkv_segment &seg, const Geom &g,
+                                                         const Prm &p, int64_t *score_q, float *score_f,
+                                                         int64_t *density, const Workspace &ws, hipStream_t s) {
+  mfma_score_d<DKV_GRAM_DESC, DKV_GRAM_KV != 0>(bank, seg, g, p, score_q, score_f, density, ws, s);
 }
 
 }  // namespace dkv

@@ -51,6 +51,7 @@ struct Workspace {
   int32_t *maint_off;  // [B + 1] first maintenance work item of each bank; [B] = total
   int32_t *crossed;    // [B] states whose first crossing lies in the first part of the crossing search
   int32_t *more;       // [G] 1 where the group's crossing search needs the prefixes past its first part
+  int32_t *whole;      // [B] the bank's group is replaced whole (k_begin); the storage of m_new, free until k_select
   uint32_t *feas;      // [B, nfw] bit r: prefix length r feasible for this bank
   int nfw;             // words per bank of feas
   uint64_t *skeys;     // [B, npad] sort keys, sorted within 512-key chunks
@@ -107,10 +108,30 @@ struct KvSeg {
 };
 hipError_t launch_attention(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvSeg sink,
                             void *out, float scale, const Geom &g, hipStream_t s);
-void launch_gram_mfma(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
-                      const dkv_update_out &out, const Workspace &ws, hipStream_t s, int stage);
-void launch_score_mfma(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
-                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws, hipStream_t s);
+// The Gram stages of bf16 banks per descriptor geometry (dkv_gram_mfma.hip, compiled once for each): the
+// descriptor dimension is the key dimension, or twice it for the concatenated [K; V] rows.
+#define DKV_DECLARE_GRAM(D, KV)                                                                                     \
+  void launch_gram_d##D##_kv##KV(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,         \
+                                 const dkv_update_out &out, const Workspace &ws, hipStream_t s, int stage);         \
+  void launch_score_d##D##_kv##KV(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,        \
+                                  int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws, hipStream_t s);
+DKV_DECLARE_GRAM(64, 0)
+DKV_DECLARE_GRAM(128, 0)
+DKV_DECLARE_GRAM(128, 1)
+DKV_DECLARE_GRAM(256, 1)
+#undef DKV_DECLARE_GRAM
+inline void launch_gram_mfma(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
+                             const dkv_update_out &out, const Workspace &ws, hipStream_t s, int stage) {
+  const bool kv = (p.flags & DKV_POLICY_KV_DESCRIPTOR) != 0;
+  (kv ? (g.d == 128 ? launch_gram_d256_kv1 : launch_gram_d128_kv1)
+      : (g.d == 128 ? launch_gram_d128_kv0 : launch_gram_d64_kv0))(bank, seg, g, p, out, ws, s, stage);
+}
+inline void launch_score_mfma(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
+                              int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws, hipStream_t s) {
+  const bool kv = (p.flags & DKV_POLICY_KV_DESCRIPTOR) != 0;
+  (kv ? (g.d == 128 ? launch_score_d256_kv1 : launch_score_d128_kv1)
+      : (g.d == 128 ? launch_score_d128_kv0 : launch_score_d64_kv0))(bank, seg, g, p, score_q, score_f, density, ws, s);
+}
 hipError_t launch_pair_weight(const float *d2, int64_t n, const Prm &p, int32_t *w,
                               hipStream_t s);
 // Within-block sequential competition after the order is known (bf16 banks).

@@ -107,10 +107,20 @@ __device__ __forceinline__ float dot_row(const float (&kr)[D], const float *col)
 // (Eq. 6); the other workgroups compute candidate norms, the column aug steps
 // of candidates and bank states, and clear the accumulators that the Gram
 // stages fill with atomic adds.
+//
+// whole: the group's banks are replaced whole whatever the weights are.  With
+// R = M_b for every bank of the group that holds states, e_R = m + R - M_b = m:
+// the longest prefix may release every state, so it is feasible (Eqs. 9-10),
+// r* = R (Eq. 11), and e_{r*} = m states leave under every fill rule.  Then no
+// crossing, projected density or survivor is needed (1), and with R = N not
+// even the candidates' order (2): all of them enter.  This holds for budgets up
+// to one block.  Such a one-layer update (12 banks, budget = block = 4,680)
+// took 432 us with the score, the sort keys and the whole crossing search.
+// allow: the largest value the requested outputs permit.
 // ---------------------------------------------------------------------------
 template <int D, int DT>
 __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g,
-                                                    Workspace ws, float inv_s2, int norms) {
+                                                    Workspace ws, float inv_s2, int norms, int allow) {
   const int b = blockIdx.y;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   if (blockIdx.x > 0) {
@@ -168,6 +178,12 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
   int R = g.N;
   const int g0 = (b / g.gs) * g.gs;
   for (int j = 0; j < g.gs; ++j) R = min(R, clampi(bank.budget[g0 + j], 0, g.Mcap));
+  int whole = allow;
+  for (int j = 0; j < g.gs; ++j) {
+    const int Mj = clampi(bank.budget[g0 + j], 0, g.Mcap);
+    if (R != Mj && clampi(bank.occupancy[g0 + j], 0, Mj) > 0) whole = 0;
+  }
+  if (whole > 1 && R < g.N) whole = 1;
   // Score scale exponent E: binary exponent of max_i fp32(2^23 / b_i), i.e. of
   // the value at the smallest baseline (the division and rounding are monotone).
   __shared__ long long redb[kThreads / 64];
@@ -216,17 +232,18 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
     ws.R[b] = R;
     ws.E[b] = E;
     ws.crossed[b] = 0;
+    ws.whole[b] = whole;
   }
 }
 
 template <int D, int DT>
 void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p, const Workspace &ws,
-                  bool norms, hipStream_t s) {
+                  bool norms, int allow_whole, hipStream_t s) {
   const int span = g.N > g.Mcap ? g.N : g.Mcap;
   // [K; V] geometry: candidate norms over the concatenated key-value rows
   const void *seg_v = (p.flags & DKV_POLICY_KV_DESCRIPTOR) ? seg.v : nullptr;
   k_begin<D, DT><<<dim3((unsigned)(1 + (span + kThreads - 1) / kThreads), (unsigned)g.B), kThreads, 0, s>>>(
-      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0);
+      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole);
 }
 
 // ---------------------------------------------------------------------------
@@ -237,7 +254,7 @@ __global__ __launch_bounds__(kThreads) void k_score_gram(dkv_bank bank, const vo
                                                          Prm p, Workspace ws, int64_t *out_q,
                                                          float *out_f) {
   const int b = blockIdx.y, x = blockIdx.x * kThreads + threadIdx.x;
-  const int m = ws.m[b];
+  const int m = ws.whole[b] == 2 ? 0 : ws.m[b];
   const bool act = x < g.N;
   __shared__ float tk[kTile][D];
   __shared__ float tn[kTile], tb[kTile];
@@ -386,7 +403,7 @@ __global__ __launch_bounds__(kThreads) void k_cross_gram(dkv_bank bank, const vo
                                                          Prm p, Workspace ws, int32_t *out_first) {
   const int b = blockIdx.y, i = blockIdx.x * kThreads + threadIdx.x;
   const int m = ws.m[b], R = ws.R[b];
-  if ((int)blockIdx.x * kThreads >= m) return;  // uniform: no live state in this block
+  if ((int)blockIdx.x * kThreads >= m || ws.whole[b]) return;  // uniform: no live state in this block
   const bool act = i < m;
   __shared__ float tk[kTile][D];
   __shared__ float tn[kTile];
@@ -467,10 +484,11 @@ __global__ __launch_bounds__(kBig) void k_feas_bank(Geom g, Workspace ws) {
   __shared__ int tmp[16];
   const int R = ws.R[b];
   const int m = ws.m[b], M = ws.M[b];
+  const int mc = ws.whole[b] ? 0 : m;  // a bank replaced whole: every prefix counts as feasible, so r* = R
   for (int r = threadIdx.x; r <= R; r += kBig) hist[r] = 0;
   __syncthreads();
   // four independent (clamped, unconditional) loads per round trip
-  for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kBig) {
+  for (int i0 = threadIdx.x; i0 < mc; i0 += 4 * kBig) {
     int t[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) t[u] = ws.first[(size_t)b * g.Mcap + min(i0 + u * kBig, m - 1)];
@@ -539,7 +557,7 @@ __global__ __launch_bounds__(kThreads) void k_fixup(dkv_bank bank, const void *s
                                                     Workspace ws, int64_t *out_rho_t) {
   const int b = blockIdx.y, i = blockIdx.x * kThreads + threadIdx.x;
   const int m = ws.m[b];
-  if ((int)blockIdx.x * kThreads >= m) return;
+  if ((int)blockIdx.x * kThreads >= m || ws.whole[b]) return;
   const bool act = i < m;
   const int rs = ws.r_star[b / g.gs];
   const int full = rs / kCkStride;
@@ -636,6 +654,7 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   }
   // violators and candidates for the fill (four independent loads per round trip)
   int nv_local = 0;
+  const bool whole = ws.whole[b] != 0;  // e = m: every state leaves, no first crossing was searched
   for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kBig) {
     int f[4];
 #pragma unroll
@@ -644,7 +663,7 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
     for (int u = 0; u < 4; ++u) {
       const int i = i0 + u * kBig;
       if (i < m) {
-        const bool v = !no_mandatory && f[u] <= rs;
+        const bool v = !no_mandatory && !whole && f[u] <= rs;
         st[i] = v ? ST_VIOL : ST_CAND;
         nv_local += v;
       }
@@ -775,7 +794,6 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   }
   if (threadIdx.x == 0) {
     ws.n_ev[b] = n_ev;
-    ws.m_new[b] = m_new;
     bank.occupancy[b] = m_new;
     if (out.n_evicted) out.n_evicted[b] = n_ev;
     if (out.n_admitted) out.n_admitted[b] = rs;
@@ -1019,7 +1037,11 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   dkv_update_out out = outp ? *outp : dkv_update_out{};
   // bf16 banks: Gram stages on MFMA; fp32 banks: the same stages on the VALU.
   constexpr bool kMfma = DT == DKV_BF16;
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, s);
+  // the crossings and projected densities are computed in full when they are asked for; so are the scores
+  // (and the order they give), which the sequential competition needs in any case
+  const bool seq = (p.flags & DKV_POLICY_SEQUENTIAL) != 0;
+  const int allow_whole = (seq || out.first_cross || out.rho_tilde) ? 0 : ((out.order || out.score_q) ? 1 : 2);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, s);
   if (g.N > 0) {
     if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 0);
     else k_score_gram<D, DT><<<grid2(g.N, kThreads, g.B), kThreads, 0, s>>>(bank, seg.k, g, p, ws, nullptr, nullptr);
@@ -1060,7 +1082,7 @@ template <int D, int DT>
 hipError_t score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws,
                       hipStream_t s) {
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, s);
   if constexpr (DT == DKV_BF16) {
     launch_score_mfma(bank, seg, g, p, (g.N > 0) ? score_q : nullptr, (g.N > 0) ? score_f : nullptr, density, ws, s);
   } else {
