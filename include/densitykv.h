@@ -320,6 +320,24 @@ int densitykv_bank_attention_sink(const dkv_bank *bank, const void *q, int32_t n
                                   void *out, float softmax_scale, void *stream);
 
 /*
+ * The same attention with an optional device workspace.  A call whose query
+ * blocks (256 queries of one bank; 128 in fp32) are too few to fill the GPU splits
+ * its keys over workgroups, which leave partial results in the workspace, and a
+ * second kernel combines them.  densitykv_attention_workspace_size gives the
+ * bytes this takes (0 when the call does not split; host-only); with a NULL
+ * or smaller workspace the call runs unsplit, as densitykv_bank_attention_sink.
+ * The contents need not be kept between calls; calls that overlap in time need
+ * workspaces of their own.
+ */
+int densitykv_attention_workspace_size(const dkv_bank *bank, int32_t n_query, int32_t n_window, int32_t n_sink,
+                                       size_t *bytes);
+int densitykv_bank_attention_ws(const dkv_bank *bank, const void *q, int32_t n_query,
+                                const void *sink_k, const void *sink_v, int32_t n_sink,
+                                const void *win_k, const void *win_v, int32_t n_window,
+                                void *out, float softmax_scale, void *workspace, size_t workspace_bytes,
+                                void *stream);
+
+/*
  * The per-pair contract on its own: w_q23[i] = RNE(w(d2[i]) * 2^23) with
  * w = (1 + d2/sigma^2)^-p in binary32 (Eq. 2, eps = 1).  d2 [n] float,
  * w_q23 [n] int32, both device memory.  Used to check the kernels' weight

@@ -45,8 +45,8 @@ SEQ_WEIGHT_BYTES = 32 << 30     # pairwise-weight bytes the sequential workspace
 
 ENTRY_POINTS = ("densitykv_workspace_size", "densitykv_workspace_size_policy", "densitykv_score",
                 "densitykv_update_bank", "densitykv_update_bank_noalloc",
-                "densitykv_bank_attention", "densitykv_bank_attention_sink", "densitykv_pair_weight_q23",
-                "densitykv_status_string")
+                "densitykv_bank_attention", "densitykv_bank_attention_sink", "densitykv_attention_workspace_size",
+                "densitykv_bank_attention_ws", "densitykv_pair_weight_q23", "densitykv_status_string")
 
 _vp = ctypes.c_void_p
 
@@ -97,6 +97,10 @@ def lib() -> ctypes.CDLL:
                                                ctypes.c_float, _vp]
         L.densitykv_bank_attention_sink.argtypes = [P(DkvBank), _vp, ctypes.c_int32, _vp, _vp, ctypes.c_int32,
                                                     _vp, _vp, ctypes.c_int32, _vp, ctypes.c_float, _vp]
+        L.densitykv_attention_workspace_size.argtypes = [P(DkvBank), ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
+                                                         P(ctypes.c_size_t)]
+        L.densitykv_bank_attention_ws.argtypes = L.densitykv_bank_attention_sink.argtypes[:-1] + [_vp, ctypes.c_size_t,
+                                                                                                  _vp]
         L.densitykv_pair_weight_q23.argtypes = [_vp, ctypes.c_int64, P(DkvParams), _vp, _vp]
         L.densitykv_status_string.argtypes = [ctypes.c_int]
         L.densitykv_status_string.restype = ctypes.c_char_p
@@ -358,18 +362,28 @@ def _check_q(bank: Bank, q: torch.Tensor):
         raise ValueError("q must be a contiguous [num_banks, n_query, head_dim] tensor in the bank dtype")
 
 
+def _attention(bank: Bank, q, sink_k, sink_v, ns, win_k, win_v, nw, softmax_scale, out, where):
+    """The attention call; the partial results of a split one (few queries) in a
+    buffer of the caching allocator, held for the call on the current stream."""
+    if out is None:
+        out = torch.empty_like(q)
+    scale = (1.0 / bank.d ** 0.5) if softmax_scale is None else float(softmax_scale)
+    cb, nq, size = bank.c(), int(q.shape[1]), ctypes.c_size_t(0)
+    ws = None
+    if lib().densitykv_attention_workspace_size(ctypes.byref(cb), nq, nw, ns, ctypes.byref(size)) == 0 and size.value:
+        ws = torch.empty(size.value, dtype=torch.uint8, device=q.device)
+    _check(lib().densitykv_bank_attention_ws(ctypes.byref(cb), _ptr(q), nq, _ptr(sink_k), _ptr(sink_v), ns,
+                                             _ptr(win_k), _ptr(win_v), nw, _ptr(out), ctypes.c_float(scale), _ptr(ws),
+                                             size.value, _stream()), where)
+    return out
+
+
 def bank_attention(bank: Bank, q: torch.Tensor, win_k: Optional[torch.Tensor], win_v: Optional[torch.Tensor],
                    softmax_scale: Optional[float] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """densitykv_bank_attention: softmax(q [bank; window]^T * scale) [bank; window]."""
     _check_q(bank, q)
     nw = _kv_segment(bank, win_k, win_v, "window")
-    if out is None:
-        out = torch.empty_like(q)
-    scale = (1.0 / bank.d ** 0.5) if softmax_scale is None else float(softmax_scale)
-    cb = bank.c()
-    _check(lib().densitykv_bank_attention(ctypes.byref(cb), _ptr(q), int(q.shape[1]), _ptr(win_k), _ptr(win_v),
-                                          nw, _ptr(out), ctypes.c_float(scale), _stream()), "bank_attention")
-    return out
+    return _attention(bank, q, None, None, 0, win_k, win_v, nw, softmax_scale, out, "bank_attention")
 
 
 def bank_attention_sink(bank: Bank, q: torch.Tensor, sink_k: Optional[torch.Tensor], sink_v: Optional[torch.Tensor],
@@ -379,14 +393,7 @@ def bank_attention_sink(bank: Bank, q: torch.Tensor, sink_k: Optional[torch.Tens
     _check_q(bank, q)
     ns = _kv_segment(bank, sink_k, sink_v, "sink")
     nw = _kv_segment(bank, win_k, win_v, "window")
-    if out is None:
-        out = torch.empty_like(q)
-    scale = (1.0 / bank.d ** 0.5) if softmax_scale is None else float(softmax_scale)
-    cb = bank.c()
-    _check(lib().densitykv_bank_attention_sink(ctypes.byref(cb), _ptr(q), int(q.shape[1]), _ptr(sink_k),
-                                               _ptr(sink_v), ns, _ptr(win_k), _ptr(win_v), nw, _ptr(out),
-                                               ctypes.c_float(scale), _stream()), "bank_attention_sink")
-    return out
+    return _attention(bank, q, sink_k, sink_v, ns, win_k, win_v, nw, softmax_scale, out, "bank_attention_sink")
 
 
 def pair_weight_q23(d2: torch.Tensor, params: Params = Params()) -> torch.Tensor:

@@ -181,6 +181,11 @@ Geom geom_of(const dkv_bank *bk, int n) {
   return g;
 }
 
+bool attention_sizes_ok(int32_t nq, int32_t nw, int32_t ns) {
+  constexpr int32_t kMax = 1 << 24;
+  return nq >= 0 && nw >= 0 && ns >= 0 && nq <= kMax && nw <= kMax && ns <= kMax;
+}
+
 // Groups per batch of the sequential competition: as many whole groups as
 // DKV_SEQ_WEIGHT_BYTES of pairwise weights hold, at least one, at most all.
 int seq_default_groups(const dkv_bank *bank, int n) {
@@ -283,22 +288,42 @@ int densitykv_update_bank_noalloc(dkv_bank *bank, const dkv_segment *seg, const 
   return densitykv_update_bank(bank, seg, prm, out, ws, DKV_NOALLOC_SCRATCH_BYTES, stream);
 }
 
-int densitykv_bank_attention_sink(const dkv_bank *bank, const void *q, int32_t n_query, const void *sink_k,
-                                  const void *sink_v, int32_t n_sink, const void *win_k, const void *win_v,
-                                  int32_t n_window, void *out, float softmax_scale, void *stream) {
+int densitykv_attention_workspace_size(const dkv_bank *bank, int32_t n_query, int32_t n_window, int32_t n_sink,
+                                       size_t *bytes) {
   int rc = check_bank(bank);
   if (rc) return rc;
-  if (n_query < 0 || n_window < 0 || n_sink < 0 || n_query > (1 << 24) || n_window > (1 << 24) ||
-      n_sink > (1 << 24))
-    return DKV_ERR_SHAPE;
+  if (!bytes) return DKV_ERR_INVALID;
+  if (!attention_sizes_ok(n_query, n_window, n_sink)) return DKV_ERR_SHAPE;
+  attention_splits(*bank, n_query, n_window, n_sink, bytes);
+  return DKV_OK;
+}
+
+int densitykv_bank_attention_ws(const dkv_bank *bank, const void *q, int32_t n_query, const void *sink_k,
+                                const void *sink_v, int32_t n_sink, const void *win_k, const void *win_v,
+                                int32_t n_window, void *out, float softmax_scale, void *workspace,
+                                size_t workspace_bytes, void *stream) {
+  int rc = check_bank(bank);
+  if (rc) return rc;
+  if (!attention_sizes_ok(n_query, n_window, n_sink)) return DKV_ERR_SHAPE;
   if (n_query > 0 && (!q || !out)) return DKV_ERR_INVALID;
   if (n_window > 0 && (!win_k || !win_v)) return DKV_ERR_INVALID;
   if (n_sink > 0 && (!sink_k || !sink_v)) return DKV_ERR_INVALID;
   if (!(softmax_scale > 0.0f) || softmax_scale > 1e6f) return DKV_ERR_RANGE;
   const Geom g = geom_of(bank, 0);
+  // without room for the partial results every query block walks all its keys
+  size_t need = 0;
+  int nsplit = attention_splits(*bank, n_query, n_window, n_sink, &need);
+  if (!workspace || workspace_bytes < need) nsplit = 1;
   hipError_t e = launch_attention(*bank, q, n_query, KvSeg{win_k, win_v, n_window}, KvSeg{sink_k, sink_v, n_sink},
-                                  out, softmax_scale, g, static_cast<hipStream_t>(stream));
+                                  out, softmax_scale, g, workspace, nsplit, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DKV_OK : DKV_ERR_HIP;
+}
+
+int densitykv_bank_attention_sink(const dkv_bank *bank, const void *q, int32_t n_query, const void *sink_k,
+                                  const void *sink_v, int32_t n_sink, const void *win_k, const void *win_v,
+                                  int32_t n_window, void *out, float softmax_scale, void *stream) {
+  return densitykv_bank_attention_ws(bank, q, n_query, sink_k, sink_v, n_sink, win_k, win_v, n_window, out,
+                                     softmax_scale, nullptr, 0, stream);
 }
 
 int densitykv_bank_attention(const dkv_bank *bank, const void *q, int32_t n_query, const void *win_k,

@@ -15,95 +15,187 @@
 namespace dkv {
 namespace {
 
-constexpr int kAThreads = 256;
-constexpr int kATile = 32;
-
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// One thread per query row; every thread of the block walks the same key tiles.
-template <int D, int DT>
-__global__ __launch_bounds__(kAThreads) void k_attn_rowwise(dkv_bank bank, const void *q, int nq,
-                                                            KvSeg win, KvSeg sink, void *out, float scale_log2,
-                                                            Geom g) {
-  const int b = blockIdx.y, qi = blockIdx.x * kAThreads + threadIdx.x;
-  const bool act = qi < nq;
+// Tiles [t0, t1) of one split: the splits of a (bank, query block) take equal runs.
+__device__ __forceinline__ void split_range(int total, int nsplit, int split, int &t0, int &t1) {
+  const int per = (total + nsplit - 1) / nsplit;
+  t0 = min(total, split * per);
+  t1 = min(total, t0 + per);
+}
+
+// Partial results of a split attention: for split s and row (bank, query), the
+// running maximum and weight sum of its keys and the unnormalised output.
+struct Part {
+  float *o;   // [S, rows, D]
+  float2 *ml; // [S, rows] (maximum, sum); null without splits
+};
+
+// Weight sums of a row's keys (or part of them) under their maximum mx: -1 for
+// keys whose scores are all -inf (the result is NaN unless other parts hold
+// finite scores, whose combination multiplies this by 0), 0 without keys.
+__device__ __forceinline__ float row_sum(float mx, float l, bool keys) {
+  return keys && mx == -INFINITY && l == 0.0f ? -1.0f : l;
+}
+__device__ __forceinline__ float inv_sum(float l) { return l > 0.0f ? 1.0f / l : (l < 0.0f ? NAN : 0.0f); }
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// fp32 path on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  A wave owns 32
+// queries and walks tiles of 32 keys: S^T = K Q^T with the key rows as A and the
+// query rows as B (both read 16 bytes at dims 8 c + 4 h, so K step 4 c + j takes
+// dims 8 c + j and 8 c + 4 + j of both), so lane (h, n) holds query n's scores
+// for keys 8 (i / 4) + 4 h + i % 4; then O^T += V^T P^T with register i's two
+// keys as the K step.  Keys and values come straight from global memory: the
+// four waves of a workgroup read the same tiles.  Few queries leave the chip
+// idle, so the tiles are split over workgroups.  Before, one thread walked all
+// keys of its query: 148 us for 64 queries over 320 keys in 2 banks (D = 64),
+// 16 us now, most of it two launches.
+constexpr int kRWaves = 4;
+constexpr int kRQ = 32 * kRWaves;  // queries per workgroup
+constexpr int kRK = 32;            // keys per tile
+
+template <int D>
+__global__ __launch_bounds__(64 * kRWaves, 1) void k_attn_f32(dkv_bank bank, const float *__restrict__ q, int nq,
+                                                              KvSeg win, KvSeg sink, float *__restrict__ out,
+                                                              float scale_log2, Geom g, int nsplit, Part part) {
+  constexpr int DT = D / 32, KC = D / 8;
+  const int nqb = (nq + kRQ - 1) / kRQ;
+  const int bs = blockIdx.x / nqb, b = bs / nsplit, split = bs % nsplit;
+  const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = l >> 5, n = l & 31;
+  const int q0 = (blockIdx.x % nqb) * kRQ + wave * 32, qi = q0 + n;
+  if (q0 >= nq) return;  // whole wave; no barrier follows
+  const bool qv = qi < nq;
   const int M = clampi(bank.budget[b], 0, g.Mcap);
   const int m = clampi(bank.occupancy[b], 0, M);
   const int nw = win.n, ns = sink.n;
-  const int total = m + nw + ns;
-  __shared__ float tk[kATile][D];
-  __shared__ float tv[kATile][D];
-  float qr[D], o[D];
-  const size_t qrow = (size_t)b * nq + qi;
-  if (act) {
+  const int nt0 = (m + kRK - 1) / kRK, nt1 = nt0 + (nw + kRK - 1) / kRK;
+  int tb, nt;
+  split_range(nt1 + (ns + kRK - 1) / kRK, nsplit, split, tb, nt);
+  const size_t qrow = (size_t)b * nq + (qv ? qi : nq - 1);
+  float4 qf[KC];
 #pragma unroll
-    for (int j = 0; j < D; ++j) qr[j] = load_elem<DT>(q, qrow * D + j);
-  }
+  for (int c = 0; c < KC; ++c) qf[c] = *reinterpret_cast<const float4 *>(q + qrow * D + 8 * c + 4 * h);
+  f32x16 o[DT];
 #pragma unroll
-  for (int j = 0; j < D; ++j) o[j] = 0.0f;
-  float mx = -INFINITY, l = 0.0f;
-  for (int t0 = 0; t0 < total; t0 += kATile) {
-    const int nc = min(kATile, total - t0);
-    __syncthreads();
-    for (int t = threadIdx.x; t < kATile * D; t += kAThreads) {
-      const int c = t / D, j = t % D;
-      const int key = t0 + c;
-      float kv = 0.0f, vv = 0.0f;
-      if (c < nc) {
-        if (key < m) {
-          const size_t r = ((size_t)b * g.Mcap + key) * D + j;
-          kv = load_elem<DT>(bank.k, r);
-          vv = load_elem<DT>(bank.v, r);
-        } else if (key < m + nw) {
-          const size_t r = ((size_t)b * nw + (key - m)) * D + j;
-          kv = load_elem<DT>(win.k, r);
-          vv = load_elem<DT>(win.v, r);
-        } else {
-          const size_t r = ((size_t)b * ns + (key - m - nw)) * D + j;
-          kv = load_elem<DT>(sink.k, r);
-          vv = load_elem<DT>(sink.v, r);
-        }
-      }
-      tk[c][j] = kv;
-      tv[c][j] = vv;
+  for (int t2 = 0; t2 < DT; ++t2) o[t2] = f32x16{};
+  float mx = -INFINITY, lsum = 0.0f;
+  for (int t = tb; t < nt; ++t) {
+    // tiles never straddle a segment boundary
+    const float *kp, *vp;
+    int nv;
+    if (t < nt0) {
+      const size_t r = (size_t)b * g.Mcap + (size_t)t * kRK;
+      kp = static_cast<const float *>(bank.k) + r * D;
+      vp = static_cast<const float *>(bank.v) + r * D;
+      nv = min(kRK, m - t * kRK);
+    } else if (t < nt1) {
+      const size_t r = (size_t)b * nw + (size_t)(t - nt0) * kRK;
+      kp = static_cast<const float *>(win.k) + r * D;
+      vp = static_cast<const float *>(win.v) + r * D;
+      nv = min(kRK, nw - (t - nt0) * kRK);
+    } else {
+      const size_t r = (size_t)b * ns + (size_t)(t - nt1) * kRK;
+      kp = static_cast<const float *>(sink.k) + r * D;
+      vp = static_cast<const float *>(sink.v) + r * D;
+      nv = min(kRK, ns - (t - nt1) * kRK);
     }
-    __syncthreads();
-    if (!act) continue;
-    float s[kATile];
+    // rows past the tile's last key repeat it (their weights are 0)
+    float4 kx[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) kx[c] = *reinterpret_cast<const float4 *>(kp + min(n, nv - 1) * D + 8 * c + 4 * h);
+    float vx[DT][16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float *vr = vp + min(8 * (i >> 2) + 4 * h + (i & 3), nv - 1) * D + n;
+#pragma unroll
+      for (int t2 = 0; t2 < DT; ++t2) vx[t2][i] = vr[32 * t2];
+    }
+    f32x16 sc = {};
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kx[c].x, qf[c].x, sc, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kx[c].y, qf[c].y, sc, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kx[c].z, qf[c].z, sc, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kx[c].w, qf[c].w, sc, 0, 0, 0);
+    }
     float tmax = -INFINITY;
-    for (int c = 0; c < nc; ++c) {
-      float acc = 0.0f;
 #pragma unroll
-      for (int j = 0; j < D; ++j) acc = __builtin_fmaf(qr[j], tk[c][j], acc);
-      s[c] = acc * scale_log2;
-      tmax = fmaxf(tmax, s[c]);
+    for (int i = 0; i < 16; ++i) {
+      sc[i] = 8 * (i >> 2) + 4 * h + (i & 3) < nv ? sc[i] * scale_log2 : -INFINITY;
+      tmax = fmaxf(tmax, sc[i]);
     }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     const float mnew = fmaxf(mx, tmax);
-    const float corr = exp2f(mx - mnew);
-    l *= corr;
-#pragma unroll
-    for (int j = 0; j < D; ++j) o[j] *= corr;
-    for (int c = 0; c < nc; ++c) {
-      const float pr = exp2f(s[c] - mnew);
-      l += pr;
-#pragma unroll
-      for (int j = 0; j < D; ++j) o[j] = __builtin_fmaf(pr, tv[c][j], o[j]);
-    }
+    const float mref = mnew == -INFINITY ? 0.0f : mnew;  // scores of -inf alone: weights 0, not inf - inf
+    const float corr = exp2f(mx - mref);
     mx = mnew;
-  }
-  if (!act) return;
-  const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-  if constexpr (DT == DKV_BF16) {
-    uint16_t *op = static_cast<uint16_t *>(out);
+    float p[16], ps = 0.0f;
 #pragma unroll
-    for (int j = 0; j < D; ++j) op[qrow * D + j] = f32_to_bf16_bits(o[j] * inv);
+    for (int i = 0; i < 16; ++i) {
+      p[i] = exp2f(sc[i] - mref);
+      ps += p[i];
+    }
+    lsum = __builtin_fmaf(lsum, corr, ps);
+#pragma unroll
+    for (int t2 = 0; t2 < DT; ++t2) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[t2][i] *= corr;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int t2 = 0; t2 < DT; ++t2) o[t2] = __builtin_amdgcn_mfma_f32_32x32x2f32(vx[t2][i], p[i], o[t2], 0, 0, 0);
+  }
+  const float lt = row_sum(mx, lsum + __shfl_xor(lsum, 32, 64), tb < nt);
+  if (!qv) return;
+  float inv = 1.0f;
+  float *dst = out + qrow * D;
+  if (part.ml) {
+    const size_t row = (size_t)split * g.B * nq + qrow;
+    if (h == 0) part.ml[row] = float2{mx, lt};
+    dst = part.o + row * D;
   } else {
-    float *op = static_cast<float *>(out);
-#pragma unroll
-    for (int j = 0; j < D; ++j) op[qrow * D + j] = o[j] * inv;
+    inv = inv_sum(lt);
   }
+#pragma unroll
+  for (int t2 = 0; t2 < DT; ++t2)
+#pragma unroll
+    for (int gg = 0; gg < 4; ++gg)
+      *reinterpret_cast<float4 *>(dst + 32 * t2 + 8 * gg + 4 * h) =
+          float4{o[t2][4 * gg] * inv, o[t2][4 * gg + 1] * inv, o[t2][4 * gg + 2] * inv, o[t2][4 * gg + 3] * inv};
 }
 
+// Rows of a split attention: the partial outputs under their common maximum
+// (c: the factor of the maxima's unit to log2), divided by the common sum.
+// One wave per row group: D / 4 lanes per row, 16-byte loads.
+template <int D, int DT>
+__global__ __launch_bounds__(256) void k_attn_combine(Part part, int nsplit, size_t rows, void *out, float c) {
+  constexpr int LR = D / 4;
+  const size_t row = (size_t)blockIdx.x * (256 / LR) + threadIdx.x / LR;
+  const int j = 4 * (threadIdx.x % LR);
+  if (row >= rows) return;
+  float M = -INFINITY;
+  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part.ml[s * rows + row].x);
+  float l = 0.0f, a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int s = 0; s < nsplit; ++s) {
+    const float2 ml = part.ml[s * rows + row];
+    const float4 x = *reinterpret_cast<const float4 *>(part.o + (s * rows + row) * D + j);
+    const float w = ml.x == M ? 1.0f : __builtin_amdgcn_exp2f((ml.x - M) * c);
+    l = __builtin_fmaf(ml.y, w, l);
+    a[0] = __builtin_fmaf(x.x, w, a[0]);
+    a[1] = __builtin_fmaf(x.y, w, a[1]);
+    a[2] = __builtin_fmaf(x.z, w, a[2]);
+    a[3] = __builtin_fmaf(x.w, w, a[3]);
+  }
+  const float inv = inv_sum(l);
+  if constexpr (DT == DKV_BF16)
+    *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + row * D + j) =
+        uint2{pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv)};
+  else
+    *reinterpret_cast<float4 *>(static_cast<float *>(out) + row * D + j) =
+        float4{a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv};
+}
 
 // ---------------------------------------------------------------------------
 // bf16 path on MFMA (v_mfma_f32_32x32x16_bf16).
@@ -125,7 +217,6 @@ __global__ __launch_bounds__(kAThreads) void k_attn_rowwise(dkv_bank bank, const
 // ahead of the MFMAs that use them (6 MFMAs ahead for S, 4 for P V).
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -223,7 +314,7 @@ __device__ __forceinline__ void stage_barrier() { asm volatile("s_barrier" ::: "
 template <int D>
 __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, const uint16_t *q, int nq,
                                                                KvSeg win, KvSeg sink,
-                                                               uint16_t *out, float c, Geom g) {
+                                                               uint16_t *out, float c, Geom g, int nsplit, Part part) {
   constexpr int KS = D / 16;   // K steps of S
   constexpr int DT = D / 32;   // dv tiles of O
   constexpr int RB = FCfg<D>::kRowBytes;
@@ -232,13 +323,13 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
   constexpr int kTileLoads = 2 * (FCfg<D>::kLoadsPerTile / kFWaves);
   static_assert(FCfg<D>::kLoadsPerTile % kFWaves == 0, "tile loads must split evenly over the waves");
   // Workgroup L is dispatched to XCD L % 8.  Rank the workgroups XCD by XCD
-  // (p = workgroups on lower XCDs + L / 8) and give rank p bank p / nqb, query
-  // block p % nqb: the query blocks of a bank then run on one XCD and share
-  // its L2 for the bank's keys and values.
+  // (p = workgroups on lower XCDs + L / 8) and give rank p query block p % nqb
+  // of (bank, key split) p / nqb: the query blocks that read the same keys and
+  // values then run on one XCD and share its L2 for them.
   const int nqb = (nq + kFQ - 1) / kFQ;
   const int T = (int)gridDim.x, L = (int)blockIdx.x, xcd = L % 8;
   const int p = xcd * (T / 8) + min(xcd, T % 8) + L / 8;
-  const int b = p / nqb, qblk = p % nqb;
+  const int b = p / (nqb * nsplit), split = (p / nqb) % nsplit, qblk = p % nqb;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, h = l >> 5, n = l & 31;
   const int M = clampi(bank.budget[b], 0, g.Mcap);
   const int m = clampi(bank.occupancy[b], 0, M);
@@ -274,7 +365,9 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
   // ceil(nw/64) window tiles, so every tile has one (scalar) base pointer.
   const int nt0 = (m + kFK - 1) / kFK;
   const int nt1 = nt0 + (nw + kFK - 1) / kFK;
-  const int nt = nt1 + (ns + kFK - 1) / kFK;
+  // this split's tiles [tb, nt)
+  int tb, nt;
+  split_range(nt1 + (ns + kFK - 1) / kFK, nsplit, split, tb, nt);
   auto nvalid_of = [&](int t) {
     return t < nt0 ? min(kFK, m - t * kFK) : (t < nt1 ? min(kFK, nw - (t - nt0) * kFK) : min(kFK, ns - (t - nt1) * kFK));
   };
@@ -302,11 +395,14 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
   // may stay in flight), then at the barrier every wave has finished tile
   // t - 1, so its stage receives tile t + 2.  Then S^T = K Q^T, softmax
   // update, O^T += V^T P^T.
-  auto step = [&](int t, const char *kt, const char *vtile, char *kn, char *vn) {
+  auto sync = [&](int t, char *kn, char *vn) __attribute__((always_inline)) {
     if (t + 1 < nt) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kTileLoads));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
     stage_barrier();
     issue(t + 2, kn, vn);
+  };
+  auto step = [&](int t, const char *kt, const char *vtile, char *kn, char *vn) {
+    sync(t, kn, vn);
     f32x16 sc[2];
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
@@ -360,14 +456,15 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
       for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, sc[1][i]);
       tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
       const float mnew = fmaxf(mrun, tmax);
-      const float corr = __builtin_amdgcn_exp2f((mrun - mnew) * c);
+      const float mref = mnew == -INFINITY ? 0.0f : mnew;  // scores of -inf alone: weights 0, not inf - inf
+      const float corr = __builtin_amdgcn_exp2f((mrun - mref) * c);
       mrun = mnew;
       lrun *= corr;
 #pragma unroll
       for (int t2 = 0; t2 < DT; ++t2)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[t2][i] *= corr;
-      exps(-mrun * c);
+      exps(-mref * c);
     }
     lrun += psum;
 #pragma unroll
@@ -401,16 +498,36 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
   };
 
   static_assert(kFStages == 3, "the loop below cycles through three stage buffers");
-  issue(0, k0, v0);
-  issue(1, k1, v1);
-  for (int t = 0; t < nt; t += kFStages) {
+  issue(tb, k0, v0);
+  issue(tb + 1, k1, v1);
+  if (__builtin_amdgcn_readfirstlane(qblk * kFQ + wave * 32) >= nq) {  // a wave past the last query only loads
+    for (int t = tb; t < nt; t += kFStages) {
+      sync(t, k2, v2);
+      if (t + 1 < nt) sync(t + 1, k0, v0);
+      if (t + 2 < nt) sync(t + 2, k1, v1);
+    }
+    return;
+  }
+  for (int t = tb; t < nt; t += kFStages) {
     step(t, k0, v0, k2, v2);
     if (t + 1 < nt) step(t + 1, k1, v1, k0, v0);
     if (t + 2 < nt) step(t + 2, k2, v2, k1, v1);
   }
-  const float ltot = lrun + __shfl_xor(lrun, 32, 64);
+  // both half-waves hold the row's maximum (raised together) and a part of its sum
+  const float ltot = row_sum(mrun, lrun + __shfl_xor(lrun, 32, 64), tb < nt);
   if (!qv) return;
-  const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
+  if (part.ml) {
+    const size_t row = (size_t)split * g.B * nq + qrow;
+    if (h == 0) part.ml[row] = float2{mrun, ltot};
+#pragma unroll
+    for (int t2 = 0; t2 < DT; ++t2)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg)
+        *reinterpret_cast<float4 *>(part.o + row * D + 32 * t2 + 8 * gg + 4 * h) =
+            float4{o[t2][4 * gg], o[t2][4 * gg + 1], o[t2][4 * gg + 2], o[t2][4 * gg + 3]};
+    return;
+  }
+  const float inv = inv_sum(ltot);
 #pragma unroll
   for (int t2 = 0; t2 < DT; ++t2) {
 #pragma unroll
@@ -423,20 +540,82 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
   }
 }
 
+constexpr int kCUs = 256;
+constexpr int kMaxSplit = 64;
+
+// Key splits of a call whose query blocks alone do not fill the chip.  A
+// workgroup of the bf16 kernel takes a whole CU (256 queries, 96 KB of tile
+// stages), so the time is about rounds x (tiles per split + 6 tiles of
+// prologue and epilogue), plus a second kernel that combines the partial
+// results (about 4 tiles of launch and, in tiles of 1.6 us, its traffic).  With
+// 84 workgroups (12 banks x 7 query blocks, 18,720 keys) this gives 3 splits (417
+// -> 176 us); with 228 (12 x 19) a split cannot help, and one workgroup per query
+// block stays (237 us either way).
+int attn_splits_bf16(long long nwg, long long rows, int tiles, int d) {
+  int best = 1;
+  double best_cost = 0.0;
+  for (int S = 1; S <= kMaxSplit && (S == 1 || (tiles + S - 1) / S >= 4); ++S) {
+    const double rounds = (double)((nwg * S + kCUs - 1) / kCUs);
+    double cost = rounds * ((tiles + S - 1) / S + 6);
+    if (S > 1) cost += 4.0 + (double)rows * S * (8.0 * d + 16.0) / (4e12 * 1.6e-6);
+    if (S == 1 || cost < 0.95 * best_cost) best = S, best_cost = cost;
+  }
+  return best;
+}
+
+// fp32: a split walks at least one 32-key tile; up to two workgroups a CU.
+int attn_splits_f32(long long nwg, int tiles) {
+  const long long fill = 2 * kCUs / nwg;
+  return (int)(fill < 1 ? 1 : (fill > tiles ? (tiles < 1 ? 1 : tiles) : fill));
+}
+
+}  // namespace
+
+// Splits the launch takes (1: none) and the bytes of its partial results.
+int attention_splits(const dkv_bank &bank, int nq, int nw, int ns, size_t *bytes) {
+  *bytes = 0;
+  if (nq <= 0) return 1;
+  const long long rows = (long long)bank.num_banks * nq;
+  int S;
+  if (bank.dtype == DKV_BF16) {
+    const int tiles = (bank.capacity + kFK - 1) / kFK + (nw + kFK - 1) / kFK + (ns + kFK - 1) / kFK;
+    S = attn_splits_bf16((long long)((nq + kFQ - 1) / kFQ) * bank.num_banks, rows, tiles, bank.head_dim);
+  } else {
+    const int tiles = (bank.capacity + kRK - 1) / kRK + (nw + kRK - 1) / kRK + (ns + kRK - 1) / kRK;
+    S = attn_splits_f32((long long)((nq + kRQ - 1) / kRQ) * bank.num_banks, tiles);
+    if (S > kMaxSplit) S = kMaxSplit;
+  }
+  if (S > 1) *bytes = (size_t)rows * S * (bank.head_dim * 4 + 8);
+  return S;
+}
+
+namespace {
+
 template <int D, int DT>
 hipError_t attn_impl(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvSeg sink,
-                     void *out, float scale, const Geom &g, hipStream_t s) {
+                     void *out, float scale, const Geom &g, void *ws, int nsplit, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
   const float scale_log2 = scale * 1.4426950408889634f;
-  if constexpr (DT == DKV_BF16) {
-    const long long nwg = (long long)((nq + kFQ - 1) / kFQ) * g.B;   // one-dimensional grid
-    if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)nwg);
-    k_attn_mfma<D><<<grid, 64 * kFWaves, 0, s>>>(bank, static_cast<const uint16_t *>(q), nq,
-                                                 win, sink, static_cast<uint16_t *>(out), scale_log2, g);
-  } else {
-    dim3 grid((unsigned)((nq + kAThreads - 1) / kAThreads), (unsigned)g.B);
-    k_attn_rowwise<D, DT><<<grid, kAThreads, 0, s>>>(bank, q, nq, win, sink, out, scale_log2, g);
+  const size_t rows = (size_t)g.B * nq;
+  Part part{nullptr, nullptr};
+  if (nsplit > 1) {  // the outputs first (rows of D floats), then the maxima and sums
+    part.o = static_cast<float *>(ws);
+    part.ml = reinterpret_cast<float2 *>(part.o + rows * nsplit * D);
+  }
+  const int per = DT == DKV_BF16 ? kFQ : kRQ;
+  const long long nwg = (long long)((nq + per - 1) / per) * g.B * nsplit;   // one-dimensional grid
+  if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  if constexpr (DT == DKV_BF16)
+    k_attn_mfma<D><<<(unsigned)nwg, 64 * kFWaves, 0, s>>>(bank, static_cast<const uint16_t *>(q), nq, win, sink,
+                                                          static_cast<uint16_t *>(out), scale_log2, g, nsplit, part);
+  else
+    k_attn_f32<D><<<(unsigned)nwg, 64 * kRWaves, 0, s>>>(bank, static_cast<const float *>(q), nq, win, sink,
+                                                             static_cast<float *>(out), scale_log2, g, nsplit, part);
+  if (nsplit > 1) {
+    constexpr int kRows = 256 / (D / 4);
+    // the bf16 maxima are raw scores, the fp32 ones already in log2 units
+    k_attn_combine<D, DT><<<(unsigned)((rows + kRows - 1) / kRows), 256, 0, s>>>(part, nsplit, rows, out,
+                                                                                 DT == DKV_BF16 ? scale_log2 : 1.0f);
   }
   return hipGetLastError();
 }
@@ -444,11 +623,10 @@ hipError_t attn_impl(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvS
 }  // namespace
 
 hipError_t launch_attention(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvSeg sink, void *out,
-                            float scale, const Geom &g, hipStream_t s) {
-  if (g.d == 128 && g.dtype == DKV_BF16) return attn_impl<128, DKV_BF16>(bank, q, nq, win, sink, out, scale, g, s);
-  if (g.d == 128 && g.dtype == DKV_F32) return attn_impl<128, DKV_F32>(bank, q, nq, win, sink, out, scale, g, s);
-  if (g.d == 64 && g.dtype == DKV_BF16) return attn_impl<64, DKV_BF16>(bank, q, nq, win, sink, out, scale, g, s);
-  return attn_impl<64, DKV_F32>(bank, q, nq, win, sink, out, scale, g, s);
+                            float scale, const Geom &g, void *ws, int nsplit, hipStream_t s) {
+  auto impl = g.d == 128 ? (g.dtype == DKV_BF16 ? attn_impl<128, DKV_BF16> : attn_impl<128, DKV_F32>)
+                         : (g.dtype == DKV_BF16 ? attn_impl<64, DKV_BF16> : attn_impl<64, DKV_F32>);
+  return impl(bank, q, nq, win, sink, out, scale, g, ws, nsplit, s);
 }
 
 }  // namespace dkv

@@ -106,8 +106,10 @@ struct KvSeg {
   const void *v;
   int n;
 };
+// nsplit > 1: the keys in that many splits, their partial results in ws (attention_splits gives both).
 hipError_t launch_attention(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvSeg sink,
-                            void *out, float scale, const Geom &g, hipStream_t s);
+                            void *out, float scale, const Geom &g, void *ws, int nsplit, hipStream_t s);
+int attention_splits(const dkv_bank &bank, int nq, int nw, int ns, size_t *bytes);
 // The Gram stages of bf16 banks per descriptor geometry (dkv_gram_mfma.hip, compiled once for each): the
 // descriptor dimension is the key dimension, or twice it for the concatenated [K; V] rows.
 #define DKV_DECLARE_GRAM(D, KV)                                                                                     \

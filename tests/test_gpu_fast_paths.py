@@ -13,6 +13,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2608_27922_amd import api, synth  # noqa: E402
+from gpu_util import TORCH_DT, attention_error, dev, host  # noqa: E402
+from oracle import attention  # noqa: E402
 from test_gpu_parity import POLICY_FLAGS, SMALL, _log, _run_rollout  # noqa: E402
 
 
@@ -39,3 +41,61 @@ def test_banks_of_at_most_one_block(policy, dt, d, n, budgets, gs):
     flags = POLICY_FLAGS[policy] if policy else 0
     _run_rollout(cfg, 3, api.Params(sigma2_log2=4 if d == 64 else 5, flags=flags),
                  budgets=np.array(budgets, np.int32), dup_every=2, trace=False)
+
+
+@pytest.mark.parametrize("dt,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("nq,cap,m,nw,ns", [
+    (1, 1200, 1200, 70, 33),      # one query, every segment with a partial last tile
+    (33, 4000, 0, 65, 0),         # empty bank: all but one of the splits sized by the capacity hold no key
+    (257, 900, 130, 0, 1),        # a second query block of one query; a sink of one key
+    (70, 640, 640, 0, 0),
+    (40, 640, 0, 0, 0),           # no key at all: zeros
+])
+def test_attention_key_splits(dt, d, nq, cap, m, nw, ns):
+    """Few queries: the keys are split over workgroups and the partial results combined."""
+    _log(f"attention splits dt={dt} d={d} nq={nq} cap={cap} m={m} nw={nw} ns={ns}")
+    rng = np.random.default_rng(nq + d)
+    B = 2
+    bank = api.Bank(B, cap, d, dtype=TORCH_DT[dt])
+    draw = lambda n: synth.to_storage(rng.standard_normal((B, n, d)).astype(np.float32), dt)
+    K, V, wk, wv, sk, sv, q = (draw(n) for n in (m, m, nw, nw, ns, ns, nq))
+    bank.k[:, :m] = dev(K, dt)
+    bank.v[:, :m] = dev(V, dt)
+    bank.k[:, m:] = float("nan")  # slots beyond the occupancy are not read
+    bank.v[:, m:] = float("nan")
+    bank.occupancy.fill_(m)
+    opt = lambda a: dev(a, dt) if a.shape[1] else None
+    out = host(api.bank_attention_sink(bank, dev(q, dt), opt(sk), opt(sv), opt(wk), opt(wv)))
+    tol = 2e-2 if dt == "bf16" else 1e-5
+    for b in range(B):
+        if m + nw + ns == 0:
+            assert not out[b].any()
+            continue
+        ref = attention(q[b], np.concatenate([K[b], sk[b]]), np.concatenate([V[b], sv[b]]), wk[b], wv[b], 1 / np.sqrt(d))
+        assert attention_error(out[b], ref) <= tol
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_attention_key_splits_of_infinite_scores(dt):
+    """A split whose scores are all -inf weighs nothing beside finite ones; a row of such scores alone is
+    NaN, as softmax gives; a NaN key makes its row NaN in whatever split it lies."""
+    d, m = 64, 2000
+    bank = api.Bank(1, m, d, dtype=TORCH_DT[dt])
+    bank.k.zero_()
+    bank.v.fill_(1.0)
+    bank.v[:, 1500:] = 3.0
+    bank.occupancy.fill_(m)
+    bank.k[:, :1500, 0] = -float("inf")
+    q = torch.zeros(1, 3, d, device="cuda", dtype=TORCH_DT[dt])
+    q[:, 0, 0] = 1.0
+    q[:, 1, 1] = 1.0
+    bank.k[:, 1500:, 2] = 1.0
+    q[:, 2, 0] = 1.0
+    out = api.bank_attention(bank, q, None, None).float()
+    assert torch.allclose(out[0, 0], torch.full_like(out[0, 0], 3.0), rtol=1e-2)
+    assert out[0, 1].isnan().all()       # 0 * -inf
+    bank.k[:, 1500:, 0] = -float("inf")
+    assert api.bank_attention(bank, q, None, None).float()[0, 0].isnan().all()
+    bank.k[:, :, 0] = 0.0
+    bank.k[:, 3, 5] = float("nan")
+    assert api.bank_attention(bank, q, None, None).isnan().all()
