@@ -14,7 +14,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdensitykv.so")
 # (source, extra flags): the Gram stages are compiled once per descriptor geometry
-SOURCES = [("dkv_api.cpp", []), ("dkv_update.hip", []), ("dkv_attention.hip", []), ("dkv_sequential.hip", [])] + [
+SOURCES = [("dkv_api.cpp", []), ("dkv_update.hip", []), ("dkv_attention.hip", []), ("dkv_sequential.hip", []),
+           ("dkv_gram_f32.hip", [])] + [
     ("dkv_gram_mfma.hip", [f"-DDKV_GRAM_DESC={d}", f"-DDKV_GRAM_KV={kv}"]) for d, kv in ((64, 0), (128, 0), (128, 1), (256, 1))]
 ARCH = "gfx950"
 

@@ -1634,23 +1634,6 @@ __global__ __launch_bounds__(256) void k_gather_sorted(const void *seg_k, const 
   }
 }
 
-// Score entry point outputs from the accumulated sums.
-__global__ void k_score_out(Geom g, Workspace ws, int64_t *out_q, float *out_f) {
-  const int b = blockIdx.y, x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= g.N) return;
-  const size_t o = (size_t)b * g.N + x;
-  const int m = ws.m[b];
-  const int64_t A = ws.acol[o];
-  if (out_q) out_q[o] = A;
-  if (out_f) out_f[o] = m > 0 ? (float)(ldexp((double)A, ws.E[b] - 23) / (double)m) : 0.0f;
-}
-
-__global__ void k_density_out(Geom g, Workspace ws, int64_t *out) {
-  const int b = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ws.m[b]) return;
-  out[(size_t)b * g.Mcap + i] = ws.sub[(size_t)b * g.Mcap + i];
-}
-
 inline unsigned cdiv(int a, int b) { return (unsigned)((a + b - 1) / b); }
 
 // D is the descriptor dimension: the key dimension, or twice it for the
@@ -1731,12 +1714,10 @@ void mfma_score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g
   if (g.N > 0 && (score_q || score_f)) {
     k_score_mfma<D, P, F, KV><<<cdiv(g.N, 32 * W) * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(
         bank, seg.k, seg.v, g, p, ws);
-    k_score_out<<<dim3(cdiv(g.N, 256), g.B), 256, 0, s>>>(g, ws, score_q, score_f);
   }
   if (density) {
     k_rowsum_mfma<D, P, RS_DENSITY, F, KV><<<dim3(cdiv(g.Mcap, 32 * W), cdiv(g.Mcap, kColsPerSplit), g.B), T, 0,
                                               s>>>(bank, seg.k, seg.v, g, p, ws, density);
-    k_density_out<<<dim3(cdiv(g.Mcap, 256), g.B), 256, 0, s>>>(g, ws, density);
   }
 }
 

@@ -134,6 +134,10 @@ inline void launch_score_mfma(const dkv_bank &bank, const dkv_segment &seg, cons
   (kv ? (g.d == 128 ? launch_score_d256_kv1 : launch_score_d128_kv1)
       : (g.d == 128 ? launch_score_d128_kv0 : launch_score_d64_kv0))(bank, seg, g, p, score_q, score_f, density, ws, s);
 }
+// The Gram stages of fp32 banks (dkv_gram_f32.hip).
+enum F32Stage { kF32Score, kF32Density, kF32Cross, kF32Fixup, kF32Maint };
+void launch_gram_f32(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
+                     const dkv_update_out &out, const Workspace &ws, hipStream_t s, int stage);
 hipError_t launch_pair_weight(const float *d2, int64_t n, const Prm &p, int32_t *w,
                               hipStream_t s);
 // Within-block sequential competition after the order is known (bf16 banks).

@@ -4,8 +4,8 @@
 // sequence below, all on the caller's stream, with r* kept on the device.  The
 // Gram stages of bf16 banks run on MFMA (dkv_gram_mfma.hip: k_score_mfma,
 // k_gather_sorted, k_first_part_mfma, k_cross_plan, k_chunk_part_mfma,
-// k_cross_mfma, k_rowsum_mfma, k_maint_mfma); fp32 banks use the
-// VALU kernels of this file (k_score_gram, k_cross_gram, k_fixup, k_maint_gram).
+// k_cross_mfma, k_rowsum_mfma, k_maint_mfma); fp32 banks use
+// dkv_gram_f32.hip.
 //
 //   k_begin         clamp occupancy/budget, tested prefix R of the group (Eq. 11),
 //                   score scale 1/b of every bank state (Eq. 6), |k_x|^2 of
@@ -37,8 +37,7 @@ namespace dkv {
 
 namespace {
 
-constexpr int kThreads = 256;    // Gram kernels: one thread per row item
-constexpr int kTile = 32;        // columns staged in LDS per step
+constexpr int kThreads = 256;
 constexpr int kBig = 1024;       // one-workgroup-per-bank kernels
 constexpr uint64_t kRhoMax = (1ull << 40) - 1;
 
@@ -83,21 +82,6 @@ __device__ int block_max(int v, int *tmp) {
   for (int w = 1; w < nw; ++w) r = max(r, tmp[w]);
   __syncthreads();
   return r;
-}
-
-// Row key loaded into registers as float.
-template <int D, int DT>
-__device__ __forceinline__ void load_row(float (&kr)[D], const void *base, size_t row) {
-#pragma unroll
-  for (int j = 0; j < D; ++j) kr[j] = load_elem<DT>(base, row * D + j);
-}
-
-template <int D>
-__device__ __forceinline__ float dot_row(const float (&kr)[D], const float *col) {
-  float g = 0.0f;
-#pragma unroll
-  for (int j = 0; j < D; ++j) g = __builtin_fmaf(kr[j], col[j], g);
-  return g;
 }
 
 // ---------------------------------------------------------------------------
@@ -247,56 +231,6 @@ void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, c
 }
 
 // ---------------------------------------------------------------------------
-// k_score_gram: thread = candidate x; loop over every bank state i.
-// ---------------------------------------------------------------------------
-template <int D, int DT>
-__global__ __launch_bounds__(kThreads) void k_score_gram(dkv_bank bank, const void *seg_k, Geom g,
-                                                         Prm p, Workspace ws, int64_t *out_q,
-                                                         float *out_f) {
-  const int b = blockIdx.y, x = blockIdx.x * kThreads + threadIdx.x;
-  const int m = ws.whole[b] == 2 ? 0 : ws.m[b];
-  const bool act = x < g.N;
-  __shared__ float tk[kTile][D];
-  __shared__ float tn[kTile], tb[kTile];
-  float kr[D];
-  float nr = 0.0f;
-  if (act) {
-    load_row<D, DT>(kr, seg_k, (size_t)b * g.N + x);
-    nr = ws.cnorm[(size_t)b * g.N + x];
-  }
-  uint64_t A = 0;
-  for (int i0 = 0; i0 < m; i0 += kTile) {
-    const int nc = min(kTile, m - i0);
-    __syncthreads();
-    for (int t = threadIdx.x; t < kTile * D; t += kThreads) {
-      const int c = t / D, j = t % D;
-      tk[c][j] = c < nc ? load_elem<DT>(bank.k, ((size_t)b * g.Mcap + i0 + c) * D + j) : 0.0f;
-    }
-    if (threadIdx.x < kTile) {
-      const int c = threadIdx.x;
-      tn[c] = c < nc ? bank.knorm[(size_t)b * g.Mcap + i0 + c] : 0.0f;
-      tb[c] = c < nc ? ws.bs[(size_t)b * g.Mcap + i0 + c] : 0.0f;
-    }
-    __syncthreads();
-    if (act) {
-      uint32_t a32 = 0;
-      for (int c = 0; c < nc; ++c) {
-        const float gd = dot_row<D>(kr, tk[c]);
-        const float d2 = (nr + tn[c]) - 2.0f * gd;
-        const float w = pair_weight(d2, p.inv_sigma2, p.p);
-        a32 += q23_round(w, tb[c]);
-      }
-      A += a32;
-    }
-  }
-  if (!act) return;
-  const size_t o = (size_t)b * g.N + x;
-  ws.acol[o] = (int64_t)A;
-  if (out_q) out_q[o] = (int64_t)A;
-  if (out_f) out_f[o] = m > 0 ? (float)(ldexp((double)A, ws.E[b] - 23) / (double)m) : 0.0f;
-}
-
-// ---------------------------------------------------------------------------
 // Candidate order: unique keys (S_x << 13) | x sorted ascending (ties of S_x
 // by source index).  k_sort_chunks: a workgroup sorts a chunk of 512 keys in
 // LDS with a bitonic network (one compare-exchange per thread and stage).
@@ -395,70 +329,6 @@ __global__ __launch_bounds__(kBig) void k_sort_rank(Geom g, Workspace ws, int32_
 }
 
 // ---------------------------------------------------------------------------
-// k_cross_gram: thread = bank state i; running prefix over the ordered
-// candidates; first prefix length r with 2^k (rho_i + P_i(r)) >= T b_i.
-// ---------------------------------------------------------------------------
-template <int D, int DT>
-__global__ __launch_bounds__(kThreads) void k_cross_gram(dkv_bank bank, const void *seg_k, Geom g,
-                                                         Prm p, Workspace ws, int32_t *out_first) {
-  const int b = blockIdx.y, i = blockIdx.x * kThreads + threadIdx.x;
-  const int m = ws.m[b], R = ws.R[b];
-  if ((int)blockIdx.x * kThreads >= m || ws.whole[b]) return;  // uniform: no live state in this block
-  const bool act = i < m;
-  __shared__ float tk[kTile][D];
-  __shared__ float tn[kTile];
-  float kr[D];
-  float nr = 0.0f;
-  int64_t thr = 0;
-  const size_t row = (size_t)b * g.Mcap + i;
-  if (act) {
-    load_row<D, DT>(kr, bank.k, row);
-    nr = bank.knorm[row];
-    const int64_t lim = ((int64_t)p.tau_num * bank.base[row] + ((1ll << p.tau_shift) - 1)) >> p.tau_shift;
-    thr = lim - bank.rho[row];
-  }
-  int first = thr <= 0 ? 0 : R + 1;
-  int64_t P = 0;
-  uint32_t tile_sum = 0;
-  for (int j0 = 0; j0 < R; j0 += kTile) {
-    const int nc = min(kTile, R - j0);
-    __syncthreads();
-    for (int t = threadIdx.x; t < kTile * D; t += kThreads) {
-      const int c = t / D, j = t % D;
-      float v = 0.0f;
-      if (c < nc) {
-        const int x = ws.order[(size_t)b * g.N + j0 + c];
-        v = load_elem<DT>(seg_k, ((size_t)b * g.N + x) * D + j);
-      }
-      tk[c][j] = v;
-    }
-    if (threadIdx.x < kTile) {
-      const int c = threadIdx.x;
-      tn[c] = c < nc ? ws.cnorm[(size_t)b * g.N + ws.order[(size_t)b * g.N + j0 + c]] : 0.0f;
-    }
-    __syncthreads();
-    if (act) {
-      for (int c = 0; c < nc; ++c) {
-        const float gd = dot_row<D>(kr, tk[c]);
-        const float d2 = (nr + tn[c]) - 2.0f * gd;
-        const uint32_t W = q23_round(pair_weight(d2, p.inv_sigma2, p.p), 8388608.0f);
-        P += W;
-        tile_sum += W;
-        if (first > R && P >= thr) first = j0 + c + 1;
-        const int done = j0 + c + 1;
-        if ((done % kCkStride) == 0) {
-          ws.ck[row * ws.nck + (done / kCkStride - 1)] = tile_sum;
-          tile_sum = 0;
-        }
-      }
-    }
-  }
-  if (!act) return;
-  ws.first[row] = first;
-  if (out_first) out_first[row] = first;
-}
-
-// ---------------------------------------------------------------------------
 // k_feasible: one workgroup per group.  c_r = #{i : first_i <= r}; feasible
 // iff c_r <= e_r for every bank of the group; r* = largest feasible r.
 // ---------------------------------------------------------------------------
@@ -549,61 +419,6 @@ __global__ __launch_bounds__(kBig) void k_feas_group(Geom g, Workspace ws, int32
 }
 
 // ---------------------------------------------------------------------------
-// k_fixup: rho~_i(r*) = rho_i + the whole 64-candidate chunk sums before r*
-// + the partial chunk.
-// ---------------------------------------------------------------------------
-template <int D, int DT>
-__global__ __launch_bounds__(kThreads) void k_fixup(dkv_bank bank, const void *seg_k, Geom g, Prm p,
-                                                    Workspace ws, int64_t *out_rho_t) {
-  const int b = blockIdx.y, i = blockIdx.x * kThreads + threadIdx.x;
-  const int m = ws.m[b];
-  if ((int)blockIdx.x * kThreads >= m || ws.whole[b]) return;
-  const bool act = i < m;
-  const int rs = ws.r_star[b / g.gs];
-  const int full = rs / kCkStride;
-  __shared__ float tk[kTile][D];
-  __shared__ float tn[kTile];
-  float kr[D];
-  float nr = 0.0f;
-  int64_t P = 0;
-  const size_t row = (size_t)b * g.Mcap + i;
-  if (act) {
-    load_row<D, DT>(kr, bank.k, row);
-    nr = bank.knorm[row];
-    for (int t = 0; t < full; ++t) P += ws.ck[row * ws.nck + t];
-  }
-  for (int j0 = full * kCkStride; j0 < rs; j0 += kTile) {
-    const int nc = min(kTile, rs - j0);
-    __syncthreads();
-    for (int t = threadIdx.x; t < kTile * D; t += kThreads) {
-      const int c = t / D, j = t % D;
-      float v = 0.0f;
-      if (c < nc) {
-        const int x = ws.order[(size_t)b * g.N + j0 + c];
-        v = load_elem<DT>(seg_k, ((size_t)b * g.N + x) * D + j);
-      }
-      tk[c][j] = v;
-    }
-    if (threadIdx.x < kTile) {
-      const int c = threadIdx.x;
-      tn[c] = c < nc ? ws.cnorm[(size_t)b * g.N + ws.order[(size_t)b * g.N + j0 + c]] : 0.0f;
-    }
-    __syncthreads();
-    if (act) {
-      for (int c = 0; c < nc; ++c) {
-        const float gd = dot_row<D>(kr, tk[c]);
-        const float d2 = (nr + tn[c]) - 2.0f * gd;
-        P += q23_round(pair_weight(d2, p.inv_sigma2, p.p), 8388608.0f);
-      }
-    }
-  }
-  if (!act) return;
-  const int64_t rt = bank.rho[row] + P;
-  ws.rho_t[row] = rt;
-  if (out_rho_t) out_rho_t[row] = rt;
-}
-
-// ---------------------------------------------------------------------------
 // k_select: one workgroup per bank.  Violators at r* are evicted; the fill
 // takes the non-violators with the largest rho~(r*), ties by provenance, then
 // slot (key (2^40-1-rho~, prov, slot) ascending, found by MSB radix select).
@@ -635,7 +450,7 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   const int rs = ws.r_star[b / g.gs];
   const int e = ws.e[b];
   __shared__ unsigned char st[DKV_MAX_CAPACITY + 1];
-  __shared__ int hist[256];
+  __shared__ __attribute__((aligned(16))) int hist[256];
   __shared__ int tmp[16];
   __shared__ int sh_bucket, sh_below, sh_cnt;
   const size_t rb = (size_t)b * g.Mcap;
@@ -686,12 +501,27 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
       for (int i = threadIdx.x; i < m; i += kBig)
         if (st[i] == ST_CAND) atomicAdd(&hist[sel_digit(ws, bank, rb + i, i, pass)], 1);
       __syncthreads();
-      if (threadIdx.x == 0) {
-        int cum = 0, d = 0;
-        while (d < 255 && cum + hist[d] < need) cum += hist[d++];
-        sh_bucket = d;
-        sh_below = cum;
-        sh_cnt = hist[d];
+      // the first bucket whose cumulative count reaches `need` (more than `need`
+      // candidates are left, so there is one): wave 0, four buckets per lane (one
+      // thread adding up to 256 buckets took 2-5 us of dependent LDS reads a pass)
+      if (threadIdx.x < 64) {
+        const int4 c4 = reinterpret_cast<const int4 *>(hist)[threadIdx.x];
+        const int own = c4.x + c4.y + c4.z + c4.w;
+        int incl = own;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(incl, o, 64);
+          if ((int)threadIdx.x >= o) incl += y;
+        }
+        int cum = incl - own;
+        if (cum < need && need <= incl) {
+          const int c[4] = {c4.x, c4.y, c4.z, c4.w};
+          int d = 0;
+          while (d < 3 && cum + c[d] < need) cum += c[d++];
+          sh_bucket = 4 * (int)threadIdx.x + d;
+          sh_below = cum;
+          sh_cnt = c[d];
+        }
       }
       __syncthreads();
       const int bk = sh_bucket, below = sh_below, cnt = sh_cnt;
@@ -801,92 +631,6 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
 }
 
 // ---------------------------------------------------------------------------
-// k_maint_gram: virtual rows [0, Mcap) = pre-update slots (survivors),
-// [Mcap, Mcap + N) = admitted list entries.  Survivors: sum of weights to the
-// evicted states.  Admitted: sum of weights to the survivors and to the other
-// admitted candidates (self excluded by index).
-// ---------------------------------------------------------------------------
-template <int D, int DT>
-__global__ __launch_bounds__(kThreads) void k_maint_gram(dkv_bank bank, const void *seg_k, Geom g,
-                                                         Prm p, Workspace ws) {
-  const int b = blockIdx.y, v = blockIdx.x * kThreads + threadIdx.x;
-  const int m = ws.m[b], n_ev = ws.n_ev[b];
-  const int n_surv = m - n_ev;
-  const int rs = ws.r_star[b / g.gs];
-  const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
-  bool surv = false, adm = false;
-  if (v < g.Mcap) surv = v < m && ws.dest[rb + v] >= 0;
-  else adm = (v - g.Mcap) < rs && (v - g.Mcap) < g.N;
-  const bool act = surv || adm;
-  if (!__syncthreads_or(act)) return;
-  const bool any_adm = __syncthreads_or(adm);
-  const bool any_surv = __syncthreads_or(surv);
-  __shared__ float tk[kTile][D];
-  __shared__ float tn[kTile];
-  float kr[D];
-  float nr = 0.0f;
-  const int k_adm = v - g.Mcap;
-  if (surv) {
-    load_row<D, DT>(kr, bank.k, rb + v);
-    nr = bank.knorm[rb + v];
-  } else if (adm) {
-    const int x = ws.adm_list[nb + k_adm];
-    load_row<D, DT>(kr, seg_k, nb + x);
-    nr = ws.cnorm[nb + x];
-  }
-  // pass 0: evicted columns (survivor rows)
-  // pass 1: survivor columns (admitted rows)
-  // pass 2: admitted columns (admitted rows)
-  int64_t s_base = 0, s_adm = 0;
-  for (int pass = 0; pass < 3; ++pass) {
-    int ncol;
-    if (pass == 0) ncol = any_surv ? n_ev : 0;
-    else if (pass == 1) ncol = any_adm ? n_surv : 0;
-    else ncol = any_adm ? rs : 0;
-    const bool use = pass == 0 ? surv : adm;
-    for (int j0 = 0; j0 < ncol; j0 += kTile) {
-      const int nc = min(kTile, ncol - j0);
-      __syncthreads();
-      for (int t = threadIdx.x; t < kTile * D; t += kThreads) {
-        const int c = t / D, j = t % D;
-        float val = 0.0f;
-        if (c < nc) {
-          if (pass == 0) val = load_elem<DT>(bank.k, (rb + ws.ev_list[rb + j0 + c]) * D + j);
-          else if (pass == 1) val = load_elem<DT>(bank.k, (rb + ws.surv_list[rb + j0 + c]) * D + j);
-          else val = load_elem<DT>(seg_k, (nb + ws.adm_list[nb + j0 + c]) * D + j);
-        }
-        tk[c][j] = val;
-      }
-      if (threadIdx.x < kTile) {
-        const int c = threadIdx.x;
-        float nv = 0.0f;
-        if (c < nc) {
-          if (pass == 0) nv = bank.knorm[rb + ws.ev_list[rb + j0 + c]];
-          else if (pass == 1) nv = bank.knorm[rb + ws.surv_list[rb + j0 + c]];
-          else nv = ws.cnorm[nb + ws.adm_list[nb + j0 + c]];
-        }
-        tn[c] = nv;
-      }
-      __syncthreads();
-      if (use) {
-        for (int c = 0; c < nc; ++c) {
-          if (pass == 2 && j0 + c == k_adm) continue;  // j != x by index
-          const float d2 = (nr + tn[c]) - 2.0f * dot_row<D>(kr, tk[c]);
-          const uint32_t W = q23_round(pair_weight(d2, p.inv_sigma2, p.p), 8388608.0f);
-          if (pass == 2) s_adm += W;
-          else s_base += W;
-        }
-      }
-    }
-  }
-  if (surv) ws.sub[rb + v] = s_base;
-  if (adm) {
-    ws.sub_adm[nb + k_adm] = s_base;
-    ws.mut_adm[nb + k_adm] = s_adm;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Commit.  commit_surv: thread per surviving state: rho <- rho~(r*) minus its
 // weights to the evicted states (Supp. C); a state that closes a hole (only when
 // more states left than entered) moves with its key, value and metadata.
@@ -984,44 +728,21 @@ __global__ __launch_bounds__(kThreads) void k_commit(dkv_bank bank, dkv_segment 
   else commit_adm<D, DT>(bank, seg, g, p, ws, blockIdx.x - nx_surv);
 }
 
-// ---------------------------------------------------------------------------
-// k_bank_density: Phi over the bank of every live slot, from scratch (Eq. 3).
-// ---------------------------------------------------------------------------
-template <int D, int DT>
-__global__ __launch_bounds__(kThreads) void k_bank_density(dkv_bank bank, Geom g, Prm p, Workspace ws,
-                                                           int64_t *out) {
-  const int b = blockIdx.y, i = blockIdx.x * kThreads + threadIdx.x;
+// Score entry point outputs from the accumulated sums.
+__global__ void k_score_out(Geom g, Workspace ws, int64_t *out_q, float *out_f) {
+  const int b = blockIdx.y, x = blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= g.N) return;
+  const size_t o = (size_t)b * g.N + x;
   const int m = ws.m[b];
-  if ((int)blockIdx.x * kThreads >= m) return;
-  const bool act = i < m;
-  const size_t rb = (size_t)b * g.Mcap;
-  __shared__ float tk[kTile][D];
-  __shared__ float tn[kTile];
-  float kr[D];
-  float nr = 0.0f;
-  if (act) {
-    load_row<D, DT>(kr, bank.k, rb + i);
-    nr = bank.knorm[rb + i];
-  }
-  int64_t s = 0;
-  for (int j0 = 0; j0 < m; j0 += kTile) {
-    const int nc = min(kTile, m - j0);
-    __syncthreads();
-    for (int t = threadIdx.x; t < kTile * D; t += kThreads) {
-      const int c = t / D, j = t % D;
-      tk[c][j] = c < nc ? load_elem<DT>(bank.k, (rb + j0 + c) * D + j) : 0.0f;
-    }
-    if (threadIdx.x < kTile) tn[threadIdx.x] = (int)threadIdx.x < nc ? bank.knorm[rb + j0 + threadIdx.x] : 0.0f;
-    __syncthreads();
-    if (act) {
-      for (int c = 0; c < nc; ++c) {
-        if (j0 + c == i) continue;  // j != i by index
-        const float d2 = (nr + tn[c]) - 2.0f * dot_row<D>(kr, tk[c]);
-        s += q23_round(pair_weight(d2, p.inv_sigma2, p.p), 8388608.0f);
-      }
-    }
-  }
-  if (act) out[rb + i] = s;
+  const int64_t A = ws.acol[o];
+  if (out_q) out_q[o] = A;
+  if (out_f) out_f[o] = m > 0 ? (float)(ldexp((double)A, ws.E[b] - 23) / (double)m) : 0.0f;
+}
+
+__global__ void k_density_out(Geom g, Workspace ws, int64_t *out) {
+  const int b = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= ws.m[b]) return;
+  out[(size_t)b * g.Mcap + i] = ws.sub[(size_t)b * g.Mcap + i];
 }
 
 __global__ void k_pair_weight(const float *d2, int64_t n, Prm p, int32_t *w) {
@@ -1035,7 +756,7 @@ template <int D, int DT>
 hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
                        const dkv_update_out *outp, const Workspace &ws, hipStream_t s) {
   dkv_update_out out = outp ? *outp : dkv_update_out{};
-  // bf16 banks: Gram stages on MFMA; fp32 banks: the same stages on the VALU.
+  // the Gram stages of bf16 banks (dkv_gram_mfma.hip) or of fp32 banks (dkv_gram_f32.hip)
   constexpr bool kMfma = DT == DKV_BF16;
   // the crossings and projected densities are computed in full when they are asked for; so are the scores
   // (and the order they give), which the sequential competition needs in any case
@@ -1044,7 +765,7 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, s);
   if (g.N > 0) {
     if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 0);
-    else k_score_gram<D, DT><<<grid2(g.N, kThreads, g.B), kThreads, 0, s>>>(bank, seg.k, g, p, ws, nullptr, nullptr);
+    else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Score);
     k_sort_chunks<<<dim3((unsigned)((g.N + kChunk - 1) / kChunk), (unsigned)g.B), kSortThreads, 0, s>>>(
         g, ws, out.score_q, (p.flags & DKV_POLICY_SOURCE_ORDER) ? 1 : 0);
     {
@@ -1061,14 +782,14 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   if (g.N > 0 && kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 4);
   // with no candidates only states that already violate are found (prefix 0)
   if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 1);
-  else k_cross_gram<D, DT><<<grid2(g.Mcap, kThreads, g.B), kThreads, 0, s>>>(bank, seg.k, g, p, ws, out.first_cross);
+  else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Cross);
   k_feas_bank<<<g.B, kBig, 0, s>>>(g, ws);
   k_feas_group<<<g.G, kBig, 0, s>>>(g, ws, out.r_star);
   if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 2);
-  else k_fixup<D, DT><<<grid2(g.Mcap, kThreads, g.B), kThreads, 0, s>>>(bank, seg.k, g, p, ws, out.rho_tilde);
+  else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Fixup);
   k_select<<<g.B, kBig, 0, s>>>(bank, g, ws, out, p.flags);
   if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 3);
-  else k_maint_gram<D, DT><<<grid2(g.Mcap + g.N, kThreads, g.B), kThreads, 0, s>>>(bank, seg.k, g, p, ws);
+  else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Maint);
   {
     const int nxs = (g.Mcap + kThreads - 1) / kThreads;
     const int tok_per_wg = commit_tok_per_wg<D, DT>();
@@ -1083,14 +804,15 @@ hipError_t score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws,
                       hipStream_t s) {
   launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, s);
+  const bool scores = g.N > 0 && (score_q || score_f);
   if constexpr (DT == DKV_BF16) {
-    launch_score_mfma(bank, seg, g, p, (g.N > 0) ? score_q : nullptr, (g.N > 0) ? score_f : nullptr, density, ws, s);
+    launch_score_mfma(bank, seg, g, p, scores ? score_q : nullptr, scores ? score_f : nullptr, density, ws, s);
   } else {
-    if (g.N > 0 && (score_q || score_f))
-      k_score_gram<D, DT><<<grid2(g.N, kThreads, g.B), kThreads, 0, s>>>(bank, seg.k, g, p, ws, score_q, score_f);
-    if (density)
-      k_bank_density<D, DT><<<grid2(g.Mcap, kThreads, g.B), kThreads, 0, s>>>(bank, g, p, ws, density);
+    if (scores) launch_gram_f32(bank, seg, g, p, dkv_update_out{}, ws, s, kF32Score);
+    if (density) launch_gram_f32(bank, seg, g, p, dkv_update_out{}, ws, s, kF32Density);
   }
+  if (scores) k_score_out<<<grid2(g.N, 256, g.B), 256, 0, s>>>(g, ws, score_q, score_f);
+  if (density) k_density_out<<<grid2(g.Mcap, 256, g.B), 256, 0, s>>>(g, ws, density);
   return hipGetLastError();
 }
 
