@@ -51,7 +51,7 @@ size_t workspace_layout(int B, int G, int Mcap, int N, int d, Workspace *ws, cha
   w.mut_adm = (int64_t *)take(Bz * Nz * 8);
   w.hole_list = (int32_t *)take(Bz * Mz * 4);
   w.sk = (uint16_t *)take(Bz * Nz * (size_t)d * 4);  // ordered descriptors: up to [k; v], 2 d bf16
-  w.snorm = (float *)take(Bz * Nz * 4);
+  w.found = (uint64_t *)take(Bz * Nz * 4);
   w.baug = (uint4 *)take(Bz * Mz * 16);
   w.caug = (uint4 *)take(Bz * Nz * 16);
   w.saug = (uint4 *)take(Bz * Nz * 16);

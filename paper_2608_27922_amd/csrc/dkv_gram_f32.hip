@@ -243,6 +243,7 @@ __global__ __launch_bounds__(64) void k_fixup_f32(dkv_bank bank, const float *se
   const int v = blockIdx.x * kT + n;
   const size_t row = rb + min(v, m - 1);
   const int rs = ws.r_star[b / g.gs], full = rs / kCkStride;
+  if (rs == 0 && !out_rho_t) return;  // rho~ = rho: the commit reads rho itself
   int64_t P_ = 0;
   if (rs > full * kCkStride) {  // uniform
     const Frag<D> rf = load_frag<D>(static_cast<const float *>(bank.k) + row * D, h, -2.0f);

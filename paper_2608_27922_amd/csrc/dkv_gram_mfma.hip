@@ -11,8 +11,10 @@
 //   k_chunk_part_mfma  the chunk sums of the rest of the order, and
 //   k_cross_mfma       the whole crossing search, for the groups that the first
 //                      part leaves open (k_cross_plan, Eqs. 9-11)
-//   k_rowsum_mfma      row sums: the r* fix-up, the exact maintenance (Supp. C)
-//                      and the from-scratch bank density (Eq. 3)
+//   k_rowsum_mfma      row sums: the r* fix-up
+//   k_maint_mfma       the exact maintenance (Supp. C): row sums, and the symmetric
+//                      Gram of the admitted candidates
+//   k_density_mfma     from-scratch bank densities (Eq. 3), a symmetric Gram
 //
 // The column range of every Gram is split over workgroups (grid dimension y);
 // partial integer sums are combined with 64-bit atomic adds, which are exact
@@ -621,11 +623,9 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
 // ---------------------------------------------------------------------------
 // Row sums.  MODE selects rows, columns and where the sum goes.
 // ---------------------------------------------------------------------------
-enum RowSumMode { RS_CHUNK = 0, RS_FIXUP = 1, RS_SURV_EV = 2, RS_ADM_BASE = 3, RS_ADM_MUT = 4, RS_DENSITY = 5 };
+enum RowSumMode { RS_CHUNK = 0, RS_FIXUP = 1, RS_SURV_EV = 2, RS_ADM_BASE = 3 };
 
 constexpr int kChunksPerSplit = 1024 / kCkStride;   // RS_CHUNK: 1024 ordered candidates per workgroup
-// Ordered candidates in the first part of the crossing search (whole chunks).
-constexpr int kCrossFirst = 256;
 static_assert(kCrossFirst % kCkStride == 0, "the first part ends on a chunk boundary");
 
 // The three LDS stages of a Gram workgroup (separate arrays: with the stage
@@ -633,7 +633,7 @@ static_assert(kCrossFirst % kCkStride == 0, "the first part ends on a chunk boun
 template <int D>
 struct StageBufs {
   char *k0, *k1, *k2, *a0, *a1, *a2;
-  uint32_t *cb;  // [3][kSI] column sums of the stages (admitted x admitted only), or null
+  uint32_t *cb;  // [3][kSI] sums of the stages' streamed items (symmetric Grams only), or null
 };
 
 // DPP move (the partner lane's value) with a compile-time control.
@@ -667,7 +667,7 @@ __device__ __forceinline__ uint32_t row_transpose_tail(const uint32_t (&a)[8], i
 template <int D, int P, int MODE, bool FOLD, bool KV>
 __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *seg_k, const void *seg_v, const Geom &g,
                                             const Prm &p, const Workspace &ws, int64_t *out, int bx, int by, int bz,
-                                            const StageBufs<D> &sb, int cfirst = 0, int clim = 1 << 30) {
+                                            const StageBufs<D> &sb, int cfirst = 0) {
   constexpr int W = gram_waves<D>();
   constexpr int kRowsPerWG = 32 * W;
   const int b = bz;
@@ -678,45 +678,32 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   const Desc SK{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
   const Desc BK{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)};
   const Desc OK{ws.sk, nullptr};
-  constexpr bool kNeedEv = MODE == RS_SURV_EV || MODE == RS_ADM_BASE || MODE == RS_ADM_MUT;
+  constexpr bool kNeedEv = MODE == RS_SURV_EV || MODE == RS_ADM_BASE;
   const int n_ev = kNeedEv ? ws.n_ev[b] : 0;
   const int rs = (MODE == RS_FIXUP || kNeedEv) ? ws.r_star[b / g.gs] : 0;
   const int n_surv = m - n_ev;
   // rows
   int nrows;
-  if constexpr (MODE == RS_CHUNK || MODE == RS_FIXUP || MODE == RS_DENSITY) nrows = m;
+  if constexpr (MODE == RS_CHUNK || MODE == RS_FIXUP) nrows = m;
   else if constexpr (MODE == RS_SURV_EV) nrows = n_surv;
   else nrows = rs;
   if ((int)bx * kRowsPerWG >= nrows) return;
   if constexpr (MODE == RS_FIXUP) {
-    if (ws.whole[b]) return;  // no state survives
+    if (ws.whole[b]) return;        // no state survives
+    if (rs == 0 && !out) return;    // rho~ = rho: the commit reads rho itself
   }
   // columns of this workgroup: [c0, c1) of the mode's column list
   int c0 = 0, c1 = 0;
-  if constexpr (MODE == RS_CHUNK) {  // prefixes [cfirst, clim) of the order, 1,024 per split
-    const int R = ws.R[b];
+  if constexpr (MODE == RS_CHUNK) {  // prefixes from cfirst on, 1,024 per split
     c0 = cfirst + by * kChunksPerSplit * kCkStride;
-    c1 = min(min(R, clim), c0 + kChunksPerSplit * kCkStride);
+    c1 = min(ws.R[b], c0 + kChunksPerSplit * kCkStride);
   } else if constexpr (MODE == RS_FIXUP) {
     c0 = (rs / kCkStride) * kCkStride;
     c1 = rs;
   } else {
-    int total;
-    if constexpr (MODE == RS_SURV_EV) total = n_ev;
-    else if constexpr (MODE == RS_ADM_BASE) total = n_surv;
-    else if constexpr (MODE == RS_ADM_MUT) total = rs;
-    else total = m;
-    // admitted x admitted: half splits, since a row block only takes the
-    // columns from its own block on (finer work items balance the triangle)
-    constexpr int kSplit = MODE == RS_ADM_MUT ? kColsPerSplit / 2 : kColsPerSplit;
-    c0 = by * kSplit;
-    c1 = min(total, c0 + kSplit);
+    c0 = by * kColsPerSplit;
+    c1 = min(MODE == RS_SURV_EV ? n_ev : n_surv, c0 + kColsPerSplit);
   }
-  // admitted x admitted is symmetric (W_xy = W_yx exactly, keys on the grid):
-  // a workgroup takes the column stages from its own row block on; the diagonal
-  // block gives row sums, every stage above it row and column sums
-  constexpr bool kSym = MODE == RS_ADM_MUT;
-  if constexpr (kSym) c0 = max(c0, (int)bx * kRowsPerWG);
   if (MODE != RS_FIXUP && c0 >= c1) return;  // the fix-up always writes rho~, even for r* % 256 == 0
   const int v = bx * kRowsPerWG + wave * 32 + n;
   const bool rv = v < nrows;
@@ -753,7 +740,7 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   float rnorm = 0.0f;
   size_t out_idx = 0;
   if (rv) {
-    if constexpr (MODE == RS_CHUNK || MODE == RS_FIXUP || MODE == RS_DENSITY) {
+    if constexpr (MODE == RS_CHUNK || MODE == RS_FIXUP) {
       rrow = (int64_t)(rb + v);
       rnorm = bank.knorm[rb + v];
       out_idx = rb + v;
@@ -774,83 +761,30 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   load_row_frag<D, FOLD, KV>(rf, rsrc, rrow, rnorm, rv, -2.0f * p.inv_sigma2, p.inv_sigma2);
   // column items (absolute index j in the mode's list)
   auto row_of = [&](int j) -> int64_t {
-    if constexpr (MODE == RS_CHUNK || MODE == RS_FIXUP) return (int64_t)(nb + j);
+    if constexpr (MODE == RS_CHUNK) return (int64_t)(nb + j);
+    else if constexpr (MODE == RS_FIXUP) return (int64_t)(nb + ws.order[nb + j]);
     else if constexpr (MODE == RS_SURV_EV) return (int64_t)(rb + ws.ev_list[rb + j]);
-    else if constexpr (MODE == RS_ADM_BASE) return (int64_t)(rb + ws.surv_list[rb + j]);
-    else if constexpr (MODE == RS_ADM_MUT) return (int64_t)(nb + ws.adm_list[nb + j]);
-    else return (int64_t)(rb + j);
+    else return (int64_t)(rb + ws.surv_list[rb + j]);
   };
-  const Desc colbase = (MODE == RS_CHUNK || MODE == RS_FIXUP) ? OK : (MODE == RS_ADM_MUT ? SK : BK);
+  const Desc colbase = MODE == RS_CHUNK ? OK : (MODE == RS_FIXUP ? SK : BK);
   // the ordered candidates are stored as whole descriptors; the others are split for [K; V]
-  constexpr bool kColSplit = KV && !(MODE == RS_CHUNK || MODE == RS_FIXUP);
-  const uint4 *colaug = (MODE == RS_CHUNK || MODE == RS_FIXUP) ? ws.saug : (MODE == RS_ADM_MUT ? ws.caug : ws.baug);
+  constexpr bool kColSplit = KV && MODE != RS_CHUNK;
+  const uint4 *colaug = MODE == RS_CHUNK ? ws.saug : (MODE == RS_FIXUP ? ws.caug : ws.baug);
   // the column rows lie in bank b's candidates or in its slots
-  constexpr bool kColCand = MODE == RS_CHUNK || MODE == RS_FIXUP || MODE == RS_ADM_MUT;
+  constexpr bool kColCand = MODE == RS_CHUNK || MODE == RS_FIXUP;
   const int64_t col_row0 = kColCand ? (int64_t)nb : (int64_t)rb;
   const int col_nrows = kColCand ? g.N : g.Mcap;  // rows of that region
-  constexpr bool kDiag = (MODE == RS_ADM_MUT || MODE == RS_DENSITY);
-  // fragment reads kept ahead of the MFMAs where the registers allow it
-  constexpr int kStageAhead = (D <= 128 && (MODE == RS_CHUNK || MODE == RS_FIXUP || MODE == RS_DENSITY)) ? 4 : 0;
-  // the prefix-chunk Gram runs software-pipelined (below)
-  constexpr bool kPipe = MODE == RS_CHUNK && D <= 128;
+  // software-pipelined (below); the fix-up has one stage, and descriptor
+  // dimension 256 no registers for it
+  constexpr bool kPipe = MODE != RS_FIXUP && D <= 128;
   uint64_t S64 = 0;
   uint32_t chunk_sum = 0;
   const int ncols = c1 - c0;
   const int ns = (ncols + kSI - 1) / kSI;
   auto row_of_rel = [&](int j) -> int64_t { return row_of(c0 + j); };
-  const int wg_row0 = bx * kRowsPerWG;
-  // sum of the lane's 16 weights of one 32-column tile starting at list index j0
-  auto tile_sum = [&](const f32x16 &u, int j0, int nvalid) __attribute__((always_inline)) -> uint32_t {
-    const bool diag_tile = kDiag && (j0 < wg_row0 + kRowsPerWG) && (j0 + kCT > wg_row0);
-    if (nvalid >= kCT && !diag_tile) return lane_wsum<P, false, FOLD>(u, kCT, h);
-    uint32_t sm = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int mm = col_of_reg(q, h);
-      uint32_t raw = weight_raw<P, FOLD>(u[q], 8388608.0f);
-      bool ok = mm < nvalid;
-      if (kDiag) ok = ok && (j0 + mm != v);
-      sm += ok ? raw : kMagic;
-    }
-    return sm - 16u * kMagic;
-  };
-  // column sums of one 32-column tile above the diagonal block: every lane's 16
-  // weights (masked rows and columns as zero), the row partials by DPP
-  // butterfly, and one LDS add per lane (the two rows of each half-wave add
-  // partials of the same 16 columns); returns the lane's row sum
-  const bool rows_full = wg_row0 + kRowsPerWG <= nrows;
-  auto sym_tile = [&](const f32x16 &u, int nvalid, uint32_t *cb, int off) __attribute__((always_inline)) -> uint32_t {
-    const bool full = nvalid >= kCT && rows_full;
-    const bool b3 = (l >> 3) & 1;
-    uint32_t a[8], rsum = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      // values i and i + 8, then the first butterfly level (row mirror: lane
-      // 15 - x, bit 3 flipped)
-      uint32_t r0 = weight_raw<P, FOLD>(u[i], 8388608.0f), r1 = weight_raw<P, FOLD>(u[i + 8], 8388608.0f);
-      if (!full) {
-        r0 = (rv && col_of_reg(i, h) < nvalid) ? r0 : kMagic;
-        r1 = (rv && col_of_reg(i + 8, h) < nvalid) ? r1 : kMagic;
-      }
-      rsum += r0 + r1;
-      const uint32_t keep = b3 ? r1 : r0, send = b3 ? r0 : r1;
-      a[i] = keep + dpp_mov<0x140>(send);
-    }
-    const uint32_t csum = row_transpose_tail(a, l) - 16u * kMagic;
-    atomicAdd(&cb[off + col_of_reg(l & 15, h)], csum);
-    return rsum - 16u * kMagic;
-  };
-  // column sums of stage t (whose adds finished before the barrier just passed)
-  // to the global sums; the buffer is cleared for stage t + 3
-  auto flush_cols = [&](int t) __attribute__((always_inline)) {
-    const int j0 = c0 + t * kSI;
-    if (j0 < wg_row0 + kRowsPerWG || l >= kSI / W) return;
-    uint32_t *cb = sb.cb + (t % 3) * kSI;
-    const int idx = wave * (kSI / W) + l;
-    const uint32_t val = cb[idx];
-    cb[idx] = 0;
-    if (j0 + idx < c1 && val != 0)
-      atomicAdd(reinterpret_cast<unsigned long long *>(&ws.mut_adm[nb + j0 + idx]), (unsigned long long)val);
+  // sum of the lane's 16 weights of one 32-column tile, columns >= nvalid masked
+  auto tile_sum = [&](const f32x16 &u, int nvalid) __attribute__((always_inline)) -> uint32_t {
+    return nvalid >= kCT ? lane_wsum<P, false, FOLD>(u, kCT, h) : lane_wsum<P, true, FOLD>(u, nvalid, h);
   };
   constexpr int kOps = stage_ops<D, false, W>();
   // Stage t in buffers t % 3.  The global rows of stage t + 2 were fetched one
@@ -864,7 +798,7 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   // of one region (ordered candidates, bank slots in order) and whole-row
   // descriptors, the loads take the per-lane offsets of consecutive rows and no
   // row list is built
-  constexpr bool kSeqRows = !kColSplit && (MODE == RS_CHUNK || MODE == RS_FIXUP || MODE == RS_DENSITY);
+  constexpr bool kSeqRows = !kColSplit && MODE == RS_CHUNK;
   [[maybe_unused]] const StageOff<D, W> soff = stage_offsets<D, W>();
   auto stage_rows_for = [&](Rows &r, int st) __attribute__((always_inline)) {
     if constexpr (!kSeqRows) stage_rows<D, W>(r, st * kSI, ncols, row_of_rel);
@@ -883,22 +817,12 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
       if (t + 3 < ns) stage_rows_for(fill, t + 3);
       stage_dma_for(use, t + 2, kn, an);
     }
-    if constexpr (kSym) {
-      if (t > 0) flush_cols(t - 1);
-    }
     f32x16 u0, u1;
-    stage_u<D, kStageAhead>(kb, ab, rf, u0, u1);
+    stage_u<D, D <= 128 ? 4 : 0>(kb, ab, rf, u0, u1);
     const int nv0 = ncols - t * kSI;
     const int j0 = c0 + t * kSI;
-    uint32_t s2;
-    if (kSym && j0 >= wg_row0 + kRowsPerWG) {
-      uint32_t *cb = sb.cb + (t % 3) * kSI;
-      s2 = sym_tile(u0, nv0, cb, 0);
-      if (nv0 > kCT) s2 += sym_tile(u1, nv0 - kCT, cb, kCT);
-    } else {
-      s2 = tile_sum(u0, j0, nv0);
-      if (nv0 > kCT) s2 += tile_sum(u1, j0 + kCT, nv0 - kCT);
-    }
+    uint32_t s2 = tile_sum(u0, nv0);
+    if (nv0 > kCT) s2 += tile_sum(u1, nv0 - kCT);
     if constexpr (MODE == RS_CHUNK) {
       chunk_sum += s2;
       const bool chunk_end = ((t + 1) % (kCkStride / kSI)) == 0 || t + 1 == ns;
@@ -911,10 +835,6 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
       S64 += s2;
     }
   };
-  if constexpr (kSym) {
-    // cleared before the first stage barrier
-    for (int i = threadIdx.x; i < 3 * kSI; i += 64 * W) sb.cb[i] = 0;
-  }
   if (ns > 0) {
     stage_rows_for(rowsA, 0);
     stage_dma_for(rowsA, 0, sb.k0, sb.a0);
@@ -925,8 +845,7 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
     }
   }
   if constexpr (kPipe) {
-    // Software pipeline of the prefix-chunk Gram at the granularity of one
-    // 32-column tile: the MFMAs of the next tile run interleaved with the
+    // Software pipeline at the granularity of one 32-column tile: the MFMAs of the next tile run interleaved with the
     // epilogue of the current one, so that one wave keeps the matrix cores and
     // the VALU busy at the same time.  Stage s (tiles 2 s, 2 s + 1) uses
     // buffers s % 3 and rows (s even ? rowsA : rowsB).  Iteration t: tile 1
@@ -940,6 +859,10 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
       return tile_mfma<D>(kb, ab, half, rf, aoff);
     };
     auto store_chunk = [&](int t, uint32_t s2) __attribute__((always_inline)) {
+      if constexpr (MODE != RS_CHUNK) {
+        S64 += s2;
+        return;
+      }
       const uint32_t tot = s2 + __shfl_xor(s2, 32, 64);
       if (rv && h == 0) ws.ck[(rb + v) * ws.nck + ((c0 + t * kSI) / kCkStride)] = tot;
     };
@@ -989,20 +912,18 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
     if (ns > 0) {
       const int t = ns - 1;
       const int nv0 = ncols - t * kSI;
-      const int j0 = c0 + t * kSI;
-      uint32_t s2 = tile_sum(u, j0, nv0);
+      uint32_t s2 = tile_sum(u, nv0);
       if (nv0 > kCT) {
         // one call per buffer: the LDS arrays stay compile-time known (no generic pointers)
         f32x16 x;
         if (t % 3 == 0) x = tile_mfma_(sb.k0, sb.a0, 1);
         else if (t % 3 == 1) x = tile_mfma_(sb.k1, sb.a1, 1);
         else x = tile_mfma_(sb.k2, sb.a2, 1);
-        s2 += tile_sum(x, j0 + kCT, nv0 - kCT);
+        s2 += tile_sum(x, nv0 - kCT);
       }
       store_chunk(t, s2);
     }
-    return;
-  }
+  } else {
   // step t issues stage t + 2 with the rows fetched at step t - 1 and fetches
   // those of stage t + 3: stage t + 2 uses rowsA when t is even
   for (int t = 0; t < ns; t += 6) {
@@ -1013,12 +934,6 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
     if (t + 4 < ns) step(t + 4, sb.k1, sb.a1, sb.k0, sb.a0, rowsA, rowsB);
     if (t + 5 < ns) step(t + 5, sb.k2, sb.a2, sb.k1, sb.a1, rowsB, rowsA);
   }
-  if constexpr (kSym) {
-    if (ns > 0) {
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
-      stage_barrier();
-      flush_cols(ns - 1);
-    }
   }
   if constexpr (MODE == RS_CHUNK) return;
   if constexpr (MODE == RS_FIXUP) {
@@ -1029,7 +944,7 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   tot += __shfl_xor(tot, 32, 64);
   if (!rv || h != 0) return;
   {
-    int64_t *dst = (MODE == RS_SURV_EV || MODE == RS_DENSITY) ? ws.sub : (MODE == RS_ADM_BASE ? ws.sub_adm : ws.mut_adm);
+    int64_t *dst = MODE == RS_SURV_EV ? ws.sub : ws.sub_adm;
     atomicAdd(reinterpret_cast<unsigned long long *>(&dst[out_idx]), (unsigned long long)tot);
   }
 }
@@ -1044,99 +959,320 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
   rowsum_body<D, P, MODE, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, out, blockIdx.x, blockIdx.y, blockIdx.z, sb);
 }
 
+// ---------------------------------------------------------------------------
+// Symmetric Grams (W_xy = W_yx bit for bit, keys on the grid): each item's sum of
+// weights to the other items of one list, the admitted candidates (ADM) or a
+// bank's live slots.  A workgroup holds 32 W items, 32 per wave, as the A operand,
+// so the lane (h, n) gets the weights of streamed item n with the wave's held
+// items 8 (i / 4) + 4 h + i % 4 in register i, and both sums are cheap: the held
+// items' in 16 integer accumulators per lane (half an instruction per weight,
+// two tiles at a time; one reduction over the lanes per work item), the streamed
+// item's as the sum of the lane's 16 weights (half an instruction each), one LDS
+// add per lane and tile, and one 64-bit atomic per item and stage.  Bound by the
+// VALU (the exact epilogue); each pair is evaluated once, where an epilogue that
+// reduced the other side over the lanes tile by tile took 45 more instructions.
+//
+// Block J (items [32 W J, 32 W (J + 1))) takes its own block (both orders, each
+// item's own sum only) and, in runs of kSymStages stages, the items after it.
+// ---------------------------------------------------------------------------
+constexpr int kSymStages = 12;  // shorter runs pay the held rows' load more often, longer ones balance worse
+
+// Sum over the 16 lanes of each DPP row of the lane's 16 values: returns the row's sum of value lane % 16.
+__device__ __forceinline__ uint32_t row_transpose_sum(const uint32_t (&w)[16], int l) {
+  const bool b3 = (l >> 3) & 1;
+  uint32_t a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t keep = b3 ? w[i + 8] : w[i], send = b3 ? w[i] : w[i + 8];
+    a[i] = keep + dpp_mov<0x140>(send);  // row mirror: lane 15 - x (bit 3 flipped)
+  }
+  return row_transpose_tail(a, l);
+}
+
+// Work items of n list items in blocks of 32 W: J = 0 .. blocks - 1, each its own
+// block (run 0) and its runs after it.
+template <int W>
+__device__ __forceinline__ int sym_runs(int n, int J) {
+  const int after = n - 32 * W * (J + 1);
+  return 1 + (after > 0 ? (after + kSymStages * kSI - 1) / (kSymStages * kSI) : 0);
+}
+template <int W>
+__device__ __forceinline__ int sym_items(int n) {
+  int c = 0;
+  for (int J = 0; J * 32 * W < n; ++J) c += sym_runs<W>(n, J);
+  return c;
+}
+
+template <int D, int P, bool FOLD, bool KV, bool ADM>
+__device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k, const void *seg_v, const Geom &g,
+                                         const Prm &p, const Workspace &ws, int n_items, int item, int b,
+                                         const StageBufs<D> &sb) {
+  constexpr int W = gram_waves<D>();
+  int J = 0;
+  for (;; ++J) {
+    const int r = sym_runs<W>(n_items, J);
+    if (item < r) break;
+    item -= r;
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, h = l >> 5, n = l & 31;
+  const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
+  const Desc src = ADM ? Desc{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)}
+                       : Desc{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)};
+  const uint4 *aug = ADM ? ws.caug : ws.baug;
+  int64_t *dst = ADM ? ws.mut_adm + nb : ws.sub + rb;
+  const int64_t row0 = ADM ? (int64_t)nb : (int64_t)rb;
+  auto row_of = [&](int j) -> int64_t { return ADM ? (int64_t)(nb + ws.adm_list[nb + j]) : (int64_t)(rb + j); };
+  // streamed items [j0, j1)
+  const bool diag = item == 0;
+  const int hold0 = J * 32 * W;
+  const int j0 = diag ? hold0 : hold0 + 32 * W + (item - 1) * kSymStages * kSI;
+  const int j1 = min(n_items, j0 + (diag ? 32 * W : kSymStages * kSI));
+  const int ncols = j1 - j0, ns = (ncols + kSI - 1) / kSI;
+  // stage loads: list rows fetched one stage ahead of their use
+  StageRows<D, W> rows;
+  auto fetch = [&](int st) __attribute__((always_inline)) {
+    stage_rows<D, W>(rows, st * kSI, ncols, [&](int j) { return row_of(j0 + j); });
+  };
+  auto issue = [&](char *kd, char *ad) __attribute__((always_inline)) {
+    stage_dma<D, false, KV, W>(rows, src, aug, nullptr, kd, ad, nullptr, row0, ADM ? g.N : g.Mcap);
+  };
+  fetch(0);
+  issue(sb.k0, sb.a0);
+  if (ns > 1) {
+    fetch(1);
+    issue(sb.k1, sb.a1);
+    if (ns > 2) fetch(2);
+  }
+  for (int i = threadIdx.x; i < 3 * kSI; i += 64 * W) sb.cb[i] = 0;  // before the first stage barrier
+  // held items; past the list's end an item far from everything, whose weights round to 0
+  RowFrag<D> rf;
+  {
+    const int c = hold0 + wave * 32 + n;
+    const bool v = c < n_items;
+    const int64_t r = row_of(min(c, n_items - 1));
+    load_row_frag<D, FOLD, KV>(rf, src, r, ADM ? ws.cnorm[r] : bank.knorm[r], v, -2.0f * p.inv_sigma2, p.inv_sigma2);
+    if (!v && h == 0) {
+      constexpr uint32_t far = 0x4C80u;  // bf16 2^26: t > 2^24
+      rf.b[TileCfg<D>::kSteps] = __builtin_bit_cast(
+          bf16x8, u32x4{(uint32_t)kOne | ((uint32_t)kOne << 16), (uint32_t)kOne | (far << 16), 0u, 0u});
+    }
+  }
+  int aoff[TileCfg<D>::kSteps];
+  frag_offsets<D>(aoff);
+  // t of one 32-item streamed tile: the held items as A, the streamed ones as B
+  auto tile = [&](const char *kb, const char *ab, int half) __attribute__((always_inline)) -> f32x16 {
+    constexpr int KS = TileCfg<D>::kSteps;
+    bf16x8 y[KS + 1];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+      y[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kb + 32 * half * SCfg<D>::RB + aoff[kk]));
+    y[KS] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(ab + 16 * (32 * half + n)));
+    f32x16 x = {};
+#pragma unroll
+    for (int kk = 0; kk <= KS; ++kk) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf.b[kk], y[kk], x, 0, 0, 0);
+    return x;
+  };
+  uint32_t acc[16], tiles = 0;  // held items' sums (raw weights: each with kMagic), tiles added
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0;
+  auto raw16 = [&](const f32x16 &u, uint32_t (&w)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = weight_raw<P, FOLD>(u[i], 8388608.0f);
+  };
+  auto sum16 = [&](const uint32_t (&w)[16]) __attribute__((always_inline)) -> uint32_t {
+    uint32_t s = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += w[i];
+    return s;
+  };
+  constexpr int kOps = stage_ops<D, false, W>();
+  constexpr uint32_t kStreamBias = 2u * W * 16u * kMagic;  // of a streamed item's sum: 2 W lanes x 16 weights
+  // the sums of stage t's streamed items, complete before the barrier just passed, to the global ones
+  auto flush = [&](int t) __attribute__((always_inline)) {
+    if ((int)threadIdx.x < kSI) {
+      uint32_t *c = sb.cb + (t % 3) * kSI + threadIdx.x;
+      const uint32_t v = *c - kStreamBias;
+      *c = 0;
+      const int j = j0 + t * kSI + (int)threadIdx.x;
+      if (j < j1) atomicAdd(reinterpret_cast<unsigned long long *>(&dst[j]), (unsigned long long)v);
+    }
+  };
+  // one tile with masks: streamed items past j1, and in the own block an item with itself
+  auto masked = [&](const f32x16 &u, int t, int half) __attribute__((always_inline)) {
+    uint32_t w[16];
+    raw16(u, w);
+    const int j = t * kSI + 32 * half + n;  // streamed item, from j0
+    const bool v = j < ncols;
+    const bool own = diag && t * kSI + 32 * half == wave * 32;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      w[i] = v && !(own && n == col_of_reg(i, h)) ? w[i] : kMagic;
+      acc[i] += w[i];
+    }
+    ++tiles;
+    if (!diag) atomicAdd(&sb.cb[(t % 3) * kSI + 32 * half + n], sum16(w));
+  };
+  auto stage_wait = [&](bool more) __attribute__((always_inline)) {
+    if (more) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kOps));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+    stage_barrier();
+  };
+  if (diag || D > 128) {
+    // plain loop: wait, barrier, both tiles
+    auto step = [&](int t, const char *kb, const char *ab, char *kn, char *an) __attribute__((always_inline)) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+      stage_barrier();
+      if (t + 2 < ns) {
+        issue(kn, an);
+        if (t + 3 < ns) fetch(t + 3);
+      }
+      if (!diag && t > 0) flush(t - 1);
+      masked(tile(kb, ab, 0), t, 0);
+      masked(tile(kb, ab, 1), t, 1);
+    };
+    for (int t = 0; t < ns; t += 3) {
+      step(t, sb.k0, sb.a0, sb.k2, sb.a2);
+      if (t + 1 < ns) step(t + 1, sb.k1, sb.a1, sb.k0, sb.a0);
+      if (t + 2 < ns) step(t + 2, sb.k2, sb.a2, sb.k1, sb.a1);
+    }
+  } else if constexpr (D <= 128) {
+    // tile-granular pipeline as in the score kernel; iteration t: tile 1 of stage
+    // t beside the epilogue of tile 0, the barrier for stage t + 1, tile 0 of
+    // stage t + 1 beside the epilogue of tile 1
+    f32x16 u;
+    auto pstep = [&](int t, const char *kc, const char *ac, const char *kn, const char *an, char *kd, char *ad)
+        __attribute__((always_inline)) {
+      uint32_t w0[16], w1[16];
+      f32x16 x = tile(kc, ac, 1);
+      raw16(u, w0);
+      uint32_t s0 = sum16(w0);
+      tile_interleave<D>();
+      asm volatile("" : "+v"(s0));  // the epilogue of tile 0 stays beside the MFMAs of tile 1
+      atomicAdd(&sb.cb[(t % 3) * kSI + n], s0);
+      u = x;
+      stage_wait(t + 2 < ns);
+      if (t + 3 < ns) {
+        issue(kd, ad);
+        if (t + 4 < ns) fetch(t + 4);
+      }
+      if (t > 0) flush(t - 1);
+      x = tile(kn, an, 0);
+      raw16(u, w1);
+      uint32_t s1 = sum16(w1);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] += w0[i] + w1[i];
+      tile_interleave<D>();
+      asm volatile("" : "+v"(s1));
+      atomicAdd(&sb.cb[(t % 3) * kSI + 32 + n], s1);
+      tiles += 2;
+      u = x;
+    };
+    stage_wait(ns > 1);
+    if (ns > 2) {
+      issue(sb.k2, sb.a2);
+      if (ns > 3) fetch(3);
+    }
+    u = tile(sb.k0, sb.a0, 0);
+    for (int t = 0; t + 1 < ns; t += 3) {
+      pstep(t, sb.k0, sb.a0, sb.k1, sb.a1, sb.k0, sb.a0);
+      if (t + 2 < ns) pstep(t + 1, sb.k1, sb.a1, sb.k2, sb.a2, sb.k1, sb.a1);
+      if (t + 3 < ns) pstep(t + 2, sb.k2, sb.a2, sb.k0, sb.a0, sb.k2, sb.a2);
+    }
+    const int t = ns - 1;  // u: its tile 0
+    f32x16 x;
+    if (t % 3 == 0) x = tile(sb.k0, sb.a0, 1);
+    else if (t % 3 == 1) x = tile(sb.k1, sb.a1, 1);
+    else x = tile(sb.k2, sb.a2, 1);
+    masked(u, t, 0);
+    masked(x, t, 1);
+  }
+  if (!diag) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+    stage_barrier();
+    if (D <= 128 && ns > 1) flush(ns - 2);
+    flush(ns - 1);
+  }
+  // the held items' sums over the lanes
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] -= tiles * kMagic;
+  const uint32_t tot = row_transpose_sum(acc, l);
+  const int c = hold0 + wave * 32 + col_of_reg(l & 15, h);
+  if (c < n_items) atomicAdd(reinterpret_cast<unsigned long long *>(&dst[c]), (unsigned long long)tot);
+}
+
 // Maintenance work items (Supp. C): per bank, the (row block, column split)
-// pairs of its three Grams that hold pairs: survivors x evicted (row blocks of
-// the survivors x splits of the evicted), admitted x survivors, and admitted x
-// admitted (half splits).  A bank that admits nothing and releases nothing
-// has none.
+// pairs of survivors x evicted (row blocks of the survivors x splits of the
+// evicted) and admitted x survivors, and the items of admitted x admitted.  A
+// bank that admits nothing and releases nothing has none.
 struct MaintItems {
-  int rows_s, rows_a, n_se, n_ab, n_am;
+  int rows_s, rows_a, n_se, n_ab, rs;
 };
 // rpw: rows per workgroup of the maintenance Grams
 __device__ __forceinline__ MaintItems maint_items(const Geom &g, const Workspace &ws, int b, int rpw) {
   const int ne = ws.n_ev[b], rs = ws.r_star[b / g.gs], ns = ws.m[b] - ne;
   MaintItems it;
+  it.rs = rs;
   it.rows_s = (ns + rpw - 1) / rpw;
   it.rows_a = (rs + rpw - 1) / rpw;
   it.n_se = it.rows_s * ((ne + kColsPerSplit - 1) / kColsPerSplit);
   it.n_ab = it.rows_a * ((ns + kColsPerSplit - 1) / kColsPerSplit);
-  it.n_am = it.rows_a * ((rs + kColsPerSplit / 2 - 1) / (kColsPerSplit / 2));
   return it;
 }
 
-// Exclusive prefix of the banks' work item counts (one workgroup).
-constexpr int kPlanThreads = 1024;
-constexpr unsigned kMaintWgs = 4096;  // maintenance workgroups (3 per CU on 256 CUs, over 5 rounds)
-__global__ __launch_bounds__(kPlanThreads) void k_maint_plan(Geom g, Workspace ws, int rpw) {
-  __shared__ int32_t part[kPlanThreads];
-  int carry = 0;
-  for (int b0 = 0; b0 < g.B; b0 += kPlanThreads) {
-    const int b = b0 + (int)threadIdx.x;
-    int cnt = 0;
-    if (b < g.B) {
-      const MaintItems it = maint_items(g, ws, b, rpw);
-      cnt = it.n_se + it.n_ab + it.n_am;
-    }
-    part[threadIdx.x] = cnt;
-    __syncthreads();
-    for (int o = 1; o < kPlanThreads; o <<= 1) {  // inclusive scan
-      const int y = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0;
-      __syncthreads();
-      part[threadIdx.x] += y;
-      __syncthreads();
-    }
-    if (b < g.B) ws.maint_off[b] = carry + part[threadIdx.x] - cnt;
-    carry += part[kPlanThreads - 1];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) ws.maint_off[g.B] = carry;
-}
+// Workgroups that walk work items of unequal size: five rounds of the CUs' three each.
+constexpr unsigned kItemWgs = 4096;
 
-// The maintenance Grams of every bank over the planned work items: workgroup
-// k takes the items [k per, (k + 1) per) in bank order, per = total / grid
-// rounded up, so a frozen block (no item) costs one read per workgroup.
+// The maintenance Grams of every bank.
 template <int D, int P, bool FOLD, bool KV>
 __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_maint_mfma(
     dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws) {
-  constexpr int kRpw = 32 * gram_waves<D>();
+  constexpr int W = gram_waves<D>(), kRpw = 32 * W;
   constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
   __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
   __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[AB];
   __shared__ __attribute__((aligned(16))) uint32_t cb[3 * kSI];
+  __shared__ int pre[65];
+  if (!ws.crossed[0]) return;  // no bank admits or releases anything
   const StageBufs<D> sb{k0, k1, k2, a0, a1, a2, cb};
-  const int total = ws.maint_off[g.B];
-  const int per = (total + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int w0 = (int)blockIdx.x * per, w1 = min(total, w0 + per);
-  if (w0 >= w1) return;
-  // bank of item w0: the last bank whose first item is <= w0 (banks without
-  // items share the offset of the next bank)
-  int lo = 0, hi = g.B;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (ws.maint_off[mid] <= w0) lo = mid;
-    else hi = mid;
-  }
-  int b = lo, i = w0 - ws.maint_off[b];
-  MaintItems it = maint_items(g, ws, b, kRpw);
-  for (int w = w0; w < w1; ++w, ++i) {
-    while (i >= it.n_se + it.n_ab + it.n_am && b + 1 < g.B) {  // next bank with items
-      i -= it.n_se + it.n_ab + it.n_am;
-      it = maint_items(g, ws, ++b, kRpw);
-    }
-    __syncthreads();  // the previous item's LDS stages are done with
-    if (i < it.n_se) {
-      rowsum_body<D, P, RS_SURV_EV, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, i % it.rows_s, i / it.rows_s, b,
-                                          sb);
-    } else if (i < it.n_se + it.n_ab) {
-      const int j = i - it.n_se;
-      rowsum_body<D, P, RS_ADM_BASE, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, j % it.rows_a, j / it.rows_a, b,
-                                           sb);
-    } else {
-      const int j = i - it.n_se - it.n_ab;
-      rowsum_body<D, P, RS_ADM_MUT, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, j % it.rows_a, j / it.rows_a, b,
-                                          sb);
-    }
-  }
+  walk_items(
+      g.B, pre,
+      [&](int b) {
+        const MaintItems it = maint_items(g, ws, b, kRpw);
+        return it.n_se + it.n_ab + sym_items<W>(it.rs);
+      },
+      [&](int b, int i) __attribute__((always_inline)) {
+        const MaintItems it = maint_items(g, ws, b, kRpw);
+        __syncthreads();  // the previous item's LDS stages are done with
+        if (i < it.n_se) {
+          rowsum_body<D, P, RS_SURV_EV, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, i % it.rows_s, i / it.rows_s, b,
+                                                  sb);
+        } else if (i < it.n_se + it.n_ab) {
+          const int j = i - it.n_se;
+          rowsum_body<D, P, RS_ADM_BASE, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, j % it.rows_a, j / it.rows_a, b,
+                                                   sb);
+        } else {
+          sym_body<D, P, FOLD, KV, true>(bank, seg_k, seg_v, g, p, ws, it.rs, i - it.n_se - it.n_ab, b, sb);
+        }
+      });
+}
+
+// From-scratch densities of every bank (Eq. 3).
+template <int D, int P, bool FOLD, bool KV>
+__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_density_mfma(dkv_bank bank, Geom g,
+                                                                                                    Prm p, Workspace ws) {
+  constexpr int W = gram_waves<D>();
+  constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
+  __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
+  __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[AB];
+  __shared__ __attribute__((aligned(16))) uint32_t cb[3 * kSI];
+  __shared__ int pre[65];
+  const StageBufs<D> sb{k0, k1, k2, a0, a1, a2, cb};
+  walk_items(
+      g.B, pre, [&](int b) { return sym_items<W>(ws.m[b]); },
+      [&](int b, int i) __attribute__((always_inline)) {
+        __syncthreads();  // the previous item's LDS stages are done with
+        sym_body<D, P, FOLD, KV, false>(bank, nullptr, nullptr, g, p, ws, ws.m[b], i, b, sb);
+      });
 }
 
 // ---------------------------------------------------------------------------
@@ -1268,17 +1404,13 @@ __device__ __forceinline__ CrossFind cross_find(const CrossRow &r, const Prm &p,
 constexpr int kCrossWaveStates = 32;
 
 template <int D, int P, bool FOLD, bool KV>
-__global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_cross_mfma(dkv_bank bank, Geom g, Prm p, Workspace ws,
-                                                                            int32_t *out_first) {
+__device__ __forceinline__ void cross_body(const dkv_bank &bank, const Geom &g, const Prm &p, const Workspace &ws,
+                                           int32_t *out_first, int b, int bx) {
   static_assert(kCkStride == 64, "two 32-candidate tiles per chunk");
-  constexpr int KSW = D / 16;
-  const int b = blockIdx.y;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int grp = l / kCrossLanes, q = l % kCrossLanes, n32 = l & 31, hw = l >> 5;
-  const int i0 = (blockIdx.x * kWaves + wave) * kCrossWaveStates;
+  const int i0 = (bx * kWaves + wave) * kCrossWaveStates;
   const int m = ws.m[b], R = ws.R[b];
-  if (!ws.more[b / g.gs]) return;  // the first part decided this group
-  if ((int)blockIdx.x * kWaves * kCrossWaveStates >= m) return;  // whole workgroup (the walk has barriers)
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   const int nch = (R + kCkStride - 1) / kCkStride;
   // per state of this lane's column: whether its bound lies above rho, whether
@@ -1437,17 +1569,44 @@ done:
   }
 }
 
+template <int D, int P, bool FOLD, bool KV>
+__global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_cross_mfma(dkv_bank bank, Geom g, Prm p, Workspace ws,
+                                                                            int32_t *out_first) {
+  constexpr int kStates = kWaves * kCrossWaveStates;
+  __shared__ int pre[65];
+  walk_items(
+      g.B, pre, [&](int b) { return ws.more[b / g.gs] >= kMoreOpen ? (ws.m[b] + kStates - 1) / kStates : 0; },
+      [&](int b, int i) __attribute__((always_inline)) {
+        __syncthreads();  // the previous item's LDS is done with
+        cross_body<D, P, FOLD, KV>(bank, g, p, ws, out_first, b, i);
+      });
+}
+
 // The first part of the crossing search in one pass: the prefix-chunk Gram of
 // the workgroup's 128 bank states over the first kCrossFirst ordered
-// candidates (4 waves x 32 states as row items, one 64-candidate chunk per
-// column stage, a ring of stage buffers) stores each chunk sum as the chunk-sum Gram
-// does, and every state whose running prefix reaches its bound within a chunk
-// takes its first crossing there from the same weights, summed in candidate
-// order (the two half-waves exchange their 4-candidate group sums); states that
-// do not cross within the first part get R + 1, states already at their bound
-// 0.  The bank's crossings found are added to ws.crossed.
+// candidates (4 waves x 32 states as row items, one 64-candidate chunk, read
+// through the order, per column stage) stores each chunk sum as the chunk-sum
+// Gram does, and every state whose running prefix reaches its bound within a
+// chunk takes its first crossing there from the same weights, summed in
+// candidate order (the two half-waves exchange their 4-candidate group sums);
+// states that do not cross get R + 1, states already at their bound 0.
+//
+// c_r only grows with r, and the evictions a bank can make at a tested length,
+// max(0, m + r - M), are at most E = max(0, m + R - M): a bank with more than E
+// crossings r <= L is infeasible at every r >= L (Eqs. 9-10), so r* < L for its
+// group (Eq. 11), and the crossings r <= L decide r*, the mandatory releases
+// (first crossing <= r*) and the projected densities at r* (chunks before r*
+// only).  ws.found counts a bank's crossings per chunk, on a line of its own:
+// once they decide it after c chunks, workgroups of the bank that start later
+// stop there and add nothing, and ws.more of the group drops to c, so that the
+// second part leaves it out (unless every state's first crossing is wanted).
+// (One counter line for all groups made its atomics and loads wait in turn: 1.4 ms.)
+// Bound by the bank rows' reads where one chunk decides (360 banks of 9,280
+// states at their growth bound: 547 us with four chunks, 535 with one; a workgroup's
+// chain of dependent loads is what is left).
 template <int D, int P, bool FOLD, bool KV>
-__global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mfma(dkv_bank bank, Geom g, Prm p,
+__global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mfma(dkv_bank bank, const void *seg_k,
+                                                                                 const void *seg_v, Geom g, Prm p,
                                                                                  Workspace ws, int32_t *out_first) {
   static_assert(kCkStride == 2 * kCT, "two 32-candidate tiles per chunk");
   const int b = blockIdx.y;
@@ -1455,15 +1614,34 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
   const int m = ws.m[b], R = ws.R[b];
   if ((int)blockIdx.x * 32 * kWaves >= m || ws.whole[b]) return;  // whole workgroup (the stages have barriers)
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
+  // the chunks that decide the bank, from its crossings by chunk (kMoreOpen: not decided)
+  const int E = max(0, m + R - ws.M[b]);
+  auto decided_at = [&](uint64_t found) {
+    int sum = 0, c = 0;
+    for (; c < kMoreOpen - 1; ++c) {
+      sum += (int)(found >> (16 * c)) & 0xFFFF;
+      if (sum > E) break;
+    }
+    return c + 1;
+  };
+  const bool count = g.N > kCrossFirst && ws.more[b / g.gs] != kMoreForced;
+  uint64_t *found = ws.found + (size_t)b * kFoundStride;
+  // as known when the workgroup starts (the same for all its waves)
+  __shared__ int limit;
+  if (threadIdx.x == 0)
+    limit = count ? decided_at(__hip_atomic_load(found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : kMoreOpen;
   const int v = blockIdx.x * 32 * kWaves + wave * 32 + n;
   const bool rv = v < m;
   const int64_t row = (int64_t)(rb + min(v, m - 1));
   // the bound: the state violates once rho + P reaches ceil(T b / 2^k)
   const int64_t lim = ((int64_t)p.tau_num * bank.base[row] + ((1ll << p.tau_shift) - 1)) >> p.tau_shift;
   const int64_t thr = lim - bank.rho[row];
-  const int nch = min((R + kCkStride - 1) / kCkStride, kCrossFirst / kCkStride);
+  int nch = min((R + kCkStride - 1) / kCkStride, kCrossFirst / kCkStride);
   int first = thr > 0 ? R + 1 : 0;
   bool open = thr > 0;  // not yet crossed
+  uint64_t mine = 0;    // crossings of this wave by chunk, 16 bits each (lengths 0 count with the first)
+  const unsigned long long at0 = __ballot(hw == 0 && rv && thr <= 0);
+  mine += (uint64_t)__popcll(at0);
   if (nch > 0) {
     RowFrag<D> rf;
     load_row_frag<D, FOLD, KV>(rf, Desc{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)},
@@ -1471,25 +1649,30 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
     int aoff[TileCfg<D>::kSteps];
     frag_offsets<D>(aoff);
     constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
-    // a ring of three stage buffers (two chunks in flight), two at descriptor
-    // dimension 256, where three would leave one workgroup per CU
-    constexpr int NBUF = D <= 128 ? 3 : 2;
+    constexpr int NBUF = 2;
     __shared__ __attribute__((aligned(1024))) char kbuf[NBUF][KB];
     __shared__ __attribute__((aligned(16))) char abuf[NBUF][AB];
-    const StageOff<D> soff = stage_offsets<D>();
-    auto issue = [&](int c, int buf) __attribute__((always_inline)) {
-      stage_dma_seq<D, false>(soff, c * kCkStride, ws.sk, ws.saug, nullptr, kbuf[buf], abuf[buf], nullptr, (int64_t)nb,
-                              g.N);
+    const Desc SK{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
+    StageRows<D, kWaves> rows;
+    auto fetch = [&](int c) __attribute__((always_inline)) {
+      stage_rows<D, kWaves>(rows, c * kCkStride, R, [&](int j) { return (int64_t)(nb + ws.order[nb + j]); });
     };
-    constexpr int kOps = stage_ops<D, false>();
+    auto issue = [&](int buf) __attribute__((always_inline)) {
+      stage_dma<D, false, KV, kWaves>(rows, SK, ws.caug, nullptr, kbuf[buf], abuf[buf], nullptr, (int64_t)nb, g.N);
+    };
     uint64_t run = 0;  // the state's prefix sum before chunk c
-    for (int j = 0; j < NBUF - 1 && j < nch; ++j) issue(j, j);
+    fetch(0);
+    issue(0);
+    if (nch > 1) fetch(1);
     for (int c = 0; c < nch; ++c) {
       const int buf = c % NBUF;
-      if (NBUF == 3 && c + 1 < nch) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kOps));  // chunk c + 1 stays in flight
-      else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
       stage_barrier();  // every wave's loads of chunk c landed; every wave is done with chunk c - 1's buffer
-      if (c + NBUF - 1 < nch) issue(c + NBUF - 1, (c + NBUF - 1) % NBUF);
+      if (c == 0) nch = min(nch, __builtin_amdgcn_readfirstlane(limit));
+      if (c + 1 < nch) {
+        issue(buf ^ 1);
+        if (c + 2 < nch) fetch(c + 2);
+      }
       const f32x16 x0 = tile_mfma<D>(kbuf[buf], abuf[buf], 0, rf, aoff);
       const f32x16 x1 = tile_mfma<D>(kbuf[buf], abuf[buf], 1, rf, aoff);
       // weights in candidate order inside the lane: tile tl, register 4 k + j is
@@ -1543,6 +1726,7 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
           first = c * kCkStride + (int)cnt + 1;
           open = false;
         }
+        mine += (uint64_t)__popcll(__ballot(hit && hw == 0 && rv)) << (16 * c);
       }
       run += tot;
     }
@@ -1551,90 +1735,79 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
     ws.first[rb + v] = first;
     if (out_first) out_first[rb + v] = first;
   }
-  const unsigned long long found = __ballot(hw == 0 && rv && first <= R);
-  if (l == 0 && found) atomicAdd(&ws.crossed[b], (int)__popcll(found));
-}
-
-// Whether a group's crossing search must go on past its first part, the first
-// L = kCrossFirst ordered candidates (every crossing r <= L found there).  c_r only grows with r and the evictions a bank can make at a tested
-// length, max(0, m + r - M), are at most max(0, m + R - M); a bank with more
-// crossings than that within the first part is infeasible at every r >= L
-// (Eqs. 9-10), so r* < L for its group (Eq. 11), and the crossings within the
-// first part decide r*, the mandatory releases (first crossing <= r*) and the
-// projected densities at r* (chunks before r* only).  force: every state's
-// first crossing is wanted.
-__global__ __launch_bounds__(256) void k_cross_plan(Geom g, Workspace ws, int force) {
-  const int grp = blockIdx.x * 256 + threadIdx.x;
-  if (grp >= g.G) return;
-  const int b0 = grp * g.gs, R = ws.R[b0];
-  bool decided = R <= kCrossFirst || ws.whole[b0];  // the first part tested every prefix, or no search is needed
-  for (int j = 0; j < g.gs && !decided; ++j) {
-    const int b = b0 + j;
-    decided = ws.crossed[b] > max(0, ws.m[b] + R - ws.M[b]);
+  if (l == 0 && mine && count && (nch == 0 || limit > 1)) {
+    const uint64_t old = atomicAdd(reinterpret_cast<unsigned long long *>(found), (unsigned long long)mine);
+    const int at = decided_at(old + mine);
+    if (at < kMoreOpen && at < decided_at(old)) atomicMin(&ws.more[b / g.gs], at);
   }
-  ws.more[grp] = (!decided || (force && R > kCrossFirst)) ? 1 : 0;
 }
 
-// Chunk sums of the ordered prefixes [cfirst, clim) (splits of 1,024 from
-// cfirst): the first part of the crossing search, or (second) the rest, for the
-// groups whose first part left r* open.
+// Chunk sums of the ordered prefixes past the first part (splits of 1,024) for
+// the groups that it left open.
 template <int D, int P, bool FOLD, bool KV>
 __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_chunk_part_mfma(
-    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws, int cfirst, int clim,
-    int second) {
-  if (second && !ws.more[blockIdx.z / g.gs]) return;
-  constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
+    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws) {
+  constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB, RPW = 32 * gram_waves<D>(), CPS = kChunksPerSplit * kCkStride;
   __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
   __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[AB];
+  __shared__ int pre[65];
   const StageBufs<D> sb{k0, k1, k2, a0, a1, a2, nullptr};
-  rowsum_body<D, P, RS_CHUNK, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, blockIdx.x, blockIdx.y, blockIdx.z, sb,
-                                        cfirst, clim);
+  auto rows = [&](int b) { return (ws.m[b] + RPW - 1) / RPW; };
+  walk_items(
+      g.B, pre,
+      [&](int b) { return ws.more[b / g.gs] >= kMoreOpen ? rows(b) * ((ws.R[b] - kCrossFirst + CPS - 1) / CPS) : 0; },
+      [&](int b, int i) __attribute__((always_inline)) {
+        const int r = rows(b);
+        __syncthreads();  // the previous item's LDS stages are done with
+        rowsum_body<D, P, RS_CHUNK, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, i % r, i / r, b, sb, kCrossFirst);
+      });
 }
 
-// Candidate keys and norms in score order, so that the ordered passes stream
-// contiguous rows: one thread per 16-byte chunk of kGatherRows key rows
-// (every load and store instruction covers whole rows).
+// Candidate keys and norm steps in score order, for the groups that the first
+// part left open, so that the passes of the second stream contiguous rows: one thread per 16-byte chunk of kGatherRows key
+// rows (every load and store instruction covers whole rows).
 constexpr int kGatherRows = 4;
 
-// Positions [r0, r1) of the order (r1 <= N): the first part of the crossing
-// search reads positions below kCrossFirst only, so the rest is copied (second)
-// only for the groups whose first part left r* open.
 template <int D, bool KV>
-__global__ __launch_bounds__(256) void k_gather_sorted(const void *seg_k, const void *seg_v, Geom g, Workspace ws,
-                                                       int r0, int r1, int second) {
+__global__ __launch_bounds__(256) void k_gather_sorted(const void *seg_k, const void *seg_v, Geom g, Workspace ws) {
   constexpr int CH = D / 8;      // 16-byte chunks per bf16 row
   constexpr int RPP = 256 / CH;  // rows per workgroup pass
   static_assert(kGatherRows <= CH, "one metadata lane per row of the group");
-  const int b = blockIdx.y;
-  const int c = threadIdx.x % CH;
-  const int j0 = r0 + blockIdx.x * RPP * kGatherRows + threadIdx.x / CH;
-  const size_t nb = (size_t)b * g.N;
-  if (r0 + (int)blockIdx.x * RPP * kGatherRows >= r1) return;  // whole workgroup
-  if (second ? !ws.more[b / g.gs] : ws.whole[b] != 0) return;
   const Desc src{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
-  // loads from clamped (in-range) rows, unconditional so that they overlap
-  int xs[kGatherRows];
+  const int c = threadIdx.x % CH;
+  const int per_bank = (g.N + RPP * kGatherRows - 1) / (RPP * kGatherRows);
+  __shared__ int pre[65];
+  walk_items(
+      g.B, pre, [&](int b) { return ws.more[b / g.gs] >= kMoreOpen ? per_bank : 0; },
+      [&](int b, int i) __attribute__((always_inline)) {
+        const int j0 = i * RPP * kGatherRows + threadIdx.x / CH;
+        const size_t nb = (size_t)b * g.N;
+        // loads from clamped (in-range) rows, unconditional so that they overlap
+        int xs[kGatherRows];
 #pragma unroll
-  for (int u = 0; u < kGatherRows; ++u) xs[u] = ws.order[nb + min(j0 + u * RPP, r1 - 1)];
-  u32x4 tmp[kGatherRows];
+        for (int u = 0; u < kGatherRows; ++u) xs[u] = ws.order[nb + min(j0 + u * RPP, g.N - 1)];
+        u32x4 tmp[kGatherRows];
 #pragma unroll
-  for (int u = 0; u < kGatherRows; ++u)
-    tmp[u] = *reinterpret_cast<const u32x4 *>(desc_chunk<D, KV>(src, (int64_t)(nb + xs[u]), c));
+        for (int u = 0; u < kGatherRows; ++u)
+          tmp[u] = *reinterpret_cast<const u32x4 *>(desc_chunk<D, KV>(src, (int64_t)(nb + xs[u]), c));
 #pragma unroll
-  for (int u = 0; u < kGatherRows; ++u)
-    if (j0 + u * RPP < r1) reinterpret_cast<u32x4 *>(ws.sk + (nb + j0 + u * RPP) * D)[c] = tmp[u];
-  // lane c < kGatherRows of a row group copies the norm and norm step of row c
-  if (c < kGatherRows) {
-    const int j = j0 + c * RPP;
-    if (j < r1) {
-      const int x = ws.order[nb + j];
-      ws.snorm[nb + j] = ws.cnorm[nb + x];
-      ws.saug[nb + j] = ws.caug[nb + x];
-    }
-  }
+        for (int u = 0; u < kGatherRows; ++u)
+          if (j0 + u * RPP < g.N) reinterpret_cast<u32x4 *>(ws.sk + (nb + j0 + u * RPP) * D)[c] = tmp[u];
+        // lane c < kGatherRows of a row group copies the norm step of row c
+        if (c < kGatherRows) {
+          const int j = j0 + c * RPP;
+          if (j < g.N) ws.saug[nb + j] = ws.caug[nb + ws.order[nb + j]];
+        }
+      });
 }
 
 inline unsigned cdiv(int a, int b) { return (unsigned)((a + b - 1) / b); }
+inline unsigned grid_of(uint64_t items, unsigned most) { return (unsigned)(items < 1 ? 1 : (items < most ? items : most)); }
+// Workgroups of a Gram kernel that the 256 CUs hold at once (three per CU; one
+// of 8 waves at descriptor dimension 256): the grid of the kernels that walk
+// equal work items.
+template <int D>
+constexpr unsigned kGramWgs = gram_waves<D>() == 4 ? 3 * 256 : 256;
 
 // D is the descriptor dimension: the key dimension, or twice it for the
 // [K; V] geometry (KV: the candidates' values seg_v and bank.v are read too).
@@ -1650,27 +1823,21 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
       k_score_mfma<D, P, F, KV><<<rowsN * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(bank, seg.k, sv, g,
                                                                                                    p, ws);
       break;
-    case 4: {  // the positions the first part of the crossing search reads
-      const int r1 = min(g.N, kCrossFirst);
-      k_gather_sorted<D, KV><<<dim3(cdiv(r1, 256 / (D / 8) * kGatherRows), g.B), 256, 0, s>>>(seg.k, sv, g, ws, 0, r1,
-                                                                                             0);
-      break;
-    }
     case 1: {
       // The crossing search in two parts: the chunk sums of the first
       // kCrossFirst ordered candidates and the crossings within them; then, for
-      // the groups that this leaves open (k_cross_plan), the chunk sums of the
-      // rest and the whole search again.
-      const dim3 xgrid(cdiv(g.Mcap, kWaves * kCrossWaveStates), g.B);
-      k_first_part_mfma<D, P, F, KV><<<dim3(cdiv(g.Mcap, 32 * kWaves), g.B), 64 * kWaves, 0, s>>>(bank, g, p, ws,
-                                                                                                out.first_cross);
+      // the groups that this leaves open, the ordered copy and the chunk sums of
+      // the rest and the whole search again.
+      k_first_part_mfma<D, P, F, KV><<<dim3(cdiv(g.Mcap, 32 * kWaves), g.B), 64 * kWaves, 0, s>>>(bank, seg.k, sv, g, p,
+                                                                                                ws, out.first_cross);
       if (g.N > kCrossFirst) {
-        k_cross_plan<<<cdiv(g.G, 256), 256, 0, s>>>(g, ws, out.first_cross != nullptr ? 1 : 0);
-        k_gather_sorted<D, KV><<<dim3(cdiv(g.N - kCrossFirst, 256 / (D / 8) * kGatherRows), g.B), 256, 0, s>>>(
-            seg.k, sv, g, ws, kCrossFirst, g.N, 1);
-        k_chunk_part_mfma<D, P, F, KV><<<dim3(rowsM, cdiv(g.N - kCrossFirst, kChunksPerSplit * kCkStride), g.B), T,
-                                         0, s>>>(bank, seg.k, sv, g, p, ws, kCrossFirst, 1 << 30, 1);
-        k_cross_mfma<D, P, F, KV><<<xgrid, 64 * kWaves, 0, s>>>(bank, g, p, ws, out.first_cross);
+        const unsigned B = (unsigned)g.B;
+        k_gather_sorted<D, KV><<<grid_of((uint64_t)cdiv(g.N, 256 / (D / 8) * kGatherRows) * B, 1024), 256, 0, s>>>(
+            seg.k, sv, g, ws);
+        k_chunk_part_mfma<D, P, F, KV><<<grid_of((uint64_t)rowsM * cdiv(g.N - kCrossFirst, kChunksPerSplit * kCkStride) * B,
+                                                 kGramWgs<D>), T, 0, s>>>(bank, seg.k, sv, g, p, ws);
+        k_cross_mfma<D, P, F, KV><<<grid_of((uint64_t)cdiv(g.Mcap, kWaves * kCrossWaveStates) * B, 3 * 256),
+                                    64 * kWaves, 0, s>>>(bank, g, p, ws, out.first_cross);
       }
       break;
     }
@@ -1678,15 +1845,10 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
       k_rowsum_mfma<D, P, RS_FIXUP, F, KV><<<dim3(rowsM, 1, g.B), T, 0, s>>>(bank, seg.k, sv, g, p, ws, out.rho_tilde);
       break;
     case 3: {
-      // the work items, then a grid of at most kMaintWgs workgroups over them
-      // (evicted states <= admitted <= N: at most rowsM x splits of N, plus
-      // rowsN x (splits of Mcap + half splits of N) items per bank)
-      k_maint_plan<<<1, kPlanThreads, 0, s>>>(g, ws, 32 * W);
-      const unsigned y_ev = cdiv(g.N > 0 ? g.N : 1, kColsPerSplit), y_surv = cdiv(g.Mcap, kColsPerSplit);
-      const unsigned long long bound =
-          (unsigned long long)(rowsM * y_ev + (g.N > 0 ? rowsN : 0u) * (y_surv + 2 * y_ev)) * (unsigned)g.B;
-      const unsigned nwg = (unsigned)(bound < kMaintWgs ? (bound > 0 ? bound : 1) : kMaintWgs);
-      k_maint_mfma<D, P, F, KV><<<nwg, T, 0, s>>>(bank, seg.k, sv, g, p, ws);
+      // at most this many items per bank, but for states that violated before the update
+      const uint64_t y_ev = cdiv(g.N > 0 ? g.N : 1, kColsPerSplit), y_surv = cdiv(g.Mcap, kColsPerSplit);
+      const uint64_t items = rowsM * y_ev + (g.N > 0 ? rowsN : 0u) * (y_surv + 1 + cdiv(g.N, kSymStages * kSI));
+      k_maint_mfma<D, P, F, KV><<<grid_of(items * (unsigned)g.B, kItemWgs), T, 0, s>>>(bank, seg.k, sv, g, p, ws);
       break;
     }
     default:
@@ -1716,8 +1878,8 @@ void mfma_score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g
         bank, seg.k, seg.v, g, p, ws);
   }
   if (density) {
-    k_rowsum_mfma<D, P, RS_DENSITY, F, KV><<<dim3(cdiv(g.Mcap, 32 * W), cdiv(g.Mcap, kColsPerSplit), g.B), T, 0,
-                                              s>>>(bank, seg.k, seg.v, g, p, ws, density);
+    const uint64_t items = (uint64_t)cdiv(g.Mcap, 32 * W) * (1 + cdiv(g.Mcap, kSymStages * kSI)) * (unsigned)g.B;
+    k_density_mfma<D, P, F, KV><<<grid_of(items, kItemWgs), T, 0, s>>>(bank, g, p, ws);
   }
 }
 
@@ -1739,7 +1901,7 @@ void mfma_score_d(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, c
 #define DKV_CAT(a, b, c) DKV_CAT2(a, b, c)
 
 // Stage launchers used by the update sequence for bf16 banks:
-// 0 score, 4 ordered copy, 1 crossing, 2 r* fix-up, 3 maintenance.
+// 0 score, 1 crossing, 2 r* fix-up, 3 maintenance.
 void DKV_CAT(launch_gram_d, DKV_GRAM_DESC, DKV_GRAM_KV)(const dkv_bank &bank, const dkv_segment &seg, const Geom &g,
                                                         const Prm &p, const dkv_update_out &out, const Workspace &ws,
                                                         hipStream_t s, int stage) {

@@ -13,6 +13,10 @@ constexpr uint32_t kQ23 = 1u << 23;          // weight 1.0 in fixed point
 constexpr uint32_t kMagic = 0x4B000000u;     // bit pattern of 2^23 as binary32
 constexpr int kCkStride = 64;                // prefix checkpoint spacing (candidates)
 constexpr int kSortMax = 8192;               // padded sort size (N <= 8191)
+constexpr int kCrossFirst = 256;             // ordered candidates in the first part of the crossing search (whole chunks)
+constexpr int kFoundStride = 16;             // one 128-byte line per bank
+constexpr int kMoreOpen = kCrossFirst / kCkStride + 1;  // more: the whole order
+constexpr int kMoreForced = kMoreOpen + 1;              // more: the whole order for every state (first crossings wanted)
 
 // ---------------------------------------------------------------------------
 // Workspace: one carve of the caller's buffer, every array 256-byte aligned.
@@ -44,15 +48,16 @@ struct Workspace {
   int64_t *mut_adm;    // [B, N]   admitted: sum of weights to the other admitted
   int32_t *hole_list;  // [B, Mcap] holes closed by moving states (states violating before the update)
   uint16_t *sk;        // [B, N, d] bf16 candidate keys in score order
-  float *snorm;        // [B, N]   their norms
+  uint64_t *found;     // [B, kFoundStride] first word: crossings found in each chunk of the first part, 16 bits
+                       // each (N > kCrossFirst, so that a bank's row fits its N floats)
   uint4 *baug;         // [B, Mcap] column aug step of each bank state (column_aug)
   uint4 *caug;         // [B, N]   of each candidate, source order
   uint4 *saug;         // [B, N]   of each candidate, score order
-  int32_t *maint_off;  // [B + 1] first maintenance work item of each bank; [B] = total
-  int32_t *crossed;    // [B] states whose first crossing lies in the first part of the crossing search
-  int32_t *more;       // [G] 1 where the group's crossing search needs the prefixes past its first part
+  int32_t *maint_off;  // [B + 1] unused
+  int32_t *crossed;    // [B] first word: nonzero if some bank admits or releases a state
+  int32_t *more;       // [G] 64-candidate chunks after which the group's crossing search may end (kMoreOpen: not known)
   int32_t *whole;      // [B] the bank's group is replaced whole (k_begin); the storage of m_new, free until k_select
-  uint32_t *feas;      // [B, nfw] bit r: prefix length r feasible for this bank
+  uint32_t *feas;      // [B, nfw], row of a group's first bank: bit r: prefix length r feasible for the group
   int nfw;             // words per bank of feas
   uint64_t *skeys;     // [B, npad] sort keys, sorted within 512-key chunks
   int npad;            // N rounded up to 512
@@ -145,6 +150,43 @@ hipError_t launch_sequential(const dkv_bank &bank, const dkv_segment &seg, const
                              const dkv_update_out &out, const Workspace &ws, hipStream_t s);
 
 #if defined(__HIPCC__)
+// Work items of all banks over a fixed grid: bank b has count(b) items, numbered
+// in bank order; workgroup k takes the items k, k + grid, ... and calls
+// body(b, i) for item i of bank b (every wave walks alike, so the body may hold
+// barriers).  64 banks at a time, one per lane, with a scan over the wave kept in
+// LDS (pre, 65 words: the body's registers stay free of it; every wave writes the
+// same values).  A grid that nothing is left for costs a launch (about 5 us)
+// instead of one empty workgroup per possible item (85 us for the prefix-chunk
+// Gram of 360 banks).
+template <class Count, class Body>
+__device__ __forceinline__ void walk_items(int B, int *pre, Count count, Body body) {
+  const int l = threadIdx.x & 63;
+  int base = 0, w = (int)blockIdx.x;
+  for (int c0 = 0; c0 < B; c0 += 64) {
+    int incl = c0 + l < B ? count(c0 + l) : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o, 64);
+      if (l >= o) incl += y;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    if (w >= base + total) {
+      base += total;
+      continue;
+    }
+    __syncthreads();  // the banks before are done with pre
+    pre[1 + l] = incl;
+    if (l == 0) pre[0] = 0;
+    __syncthreads();
+    while (w < base + total) {
+      const int src = __ffsll(__ballot(pre[1 + l] > w - base)) - 1;
+      body(c0 + src, __builtin_amdgcn_readfirstlane(w - base - pre[src]));
+      w += (int)gridDim.x;
+    }
+    base += total;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Device helpers
 // ---------------------------------------------------------------------------

@@ -101,10 +101,11 @@ __device__ int block_max(int v, int *tmp) {
 // to one block.  Such a one-layer update (12 banks, budget = block = 4,680)
 // took 432 us with the score, the sort keys and the whole crossing search.
 // allow: the largest value the requested outputs permit.
+// force: every state's first crossing is wanted.
 // ---------------------------------------------------------------------------
 template <int D, int DT>
 __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g,
-                                                    Workspace ws, float inv_s2, int norms, int allow) {
+                                                    Workspace ws, float inv_s2, int norms, int allow, int force) {
   const int b = blockIdx.y;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   if (blockIdx.x > 0) {
@@ -150,9 +151,11 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
       ws.mut_adm[nb + j] = 0;
     }
     if (j < g.Mcap) {
-      ws.sub[rb + j] = 0;
       const int mj = clampi(bank.occupancy[b], 0, clampi(bank.budget[b], 0, g.Mcap));
-      if (j < mj) ws.baug[rb + j] = column_aug(bank.knorm[rb + j], inv_s2);
+      if (j < mj) {
+        ws.sub[rb + j] = 0;
+        ws.baug[rb + j] = column_aug(bank.knorm[rb + j], inv_s2);
+      }
     }
     return;
   }
@@ -215,19 +218,27 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
     ws.M[b] = Mb;
     ws.R[b] = R;
     ws.E[b] = E;
-    ws.crossed[b] = 0;
     ws.whole[b] = whole;
+    if (b == 0) ws.crossed[0] = 0;
+    if (g.N > kCrossFirst) ws.found[(size_t)b * kFoundStride] = 0;
+  }
+  if (b == g0) {  // the group's: whether the crossing search may go on past its first part, and k_feas's state
+    if (threadIdx.x == 0) {
+      ws.more[b / g.gs] = whole ? 0 : (R <= kCrossFirst ? kMoreOpen - 1 : (force ? kMoreForced : kMoreOpen));
+      ws.r_star[b / g.gs] = 0;
+    }
+    for (int w = threadIdx.x; w < ws.nfw; w += kThreads) ws.feas[(size_t)b * ws.nfw + w] = ~0u;
   }
 }
 
 template <int D, int DT>
 void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p, const Workspace &ws,
-                  bool norms, int allow_whole, hipStream_t s) {
+                  bool norms, int allow_whole, int force, hipStream_t s) {
   const int span = g.N > g.Mcap ? g.N : g.Mcap;
   // [K; V] geometry: candidate norms over the concatenated key-value rows
   const void *seg_v = (p.flags & DKV_POLICY_KV_DESCRIPTOR) ? seg.v : nullptr;
   k_begin<D, DT><<<dim3((unsigned)(1 + (span + kThreads - 1) / kThreads), (unsigned)g.B), kThreads, 0, s>>>(
-      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole);
+      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole, force);
 }
 
 // ---------------------------------------------------------------------------
@@ -245,6 +256,7 @@ constexpr int kMaxChunks = kSortMax / kChunk;
 __global__ __launch_bounds__(kSortThreads) void k_sort_chunks(Geom g, Workspace ws, int64_t *out_score,
                                                               int source_order) {
   const int b = blockIdx.y, c = blockIdx.x, t = threadIdx.x;
+  if (ws.whole[b] == 2) return;  // no order needed
   const size_t nb = (size_t)b * g.N;
   __shared__ uint64_t v[kChunk];
   // two keys per thread, clamped, unconditional loads
@@ -281,6 +293,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_chunks(Geom g, Workspace 
 template <int NCH>  // chunk slots searched (>= the number of chunks)
 __global__ __launch_bounds__(kBig) void k_sort_rank(Geom g, Workspace ws, int32_t *out_order) {
   const int b = blockIdx.y;
+  if (ws.whole[b] == 2) return;  // no order needed
   __shared__ uint64_t sk[kSortMax];
   const int np = ws.npad;
   const int nch = np / kChunk;
@@ -329,8 +342,8 @@ __global__ __launch_bounds__(kBig) void k_sort_rank(Geom g, Workspace ws, int32_
 }
 
 // ---------------------------------------------------------------------------
-// k_feasible: one workgroup per group.  c_r = #{i : first_i <= r}; feasible
-// iff c_r <= e_r for every bank of the group; r* = largest feasible r.
+// Feasibility: c_r = #{i : first_i <= r}; feasible iff c_r <= e_r for every bank
+// of the group; r* = largest feasible r.
 // ---------------------------------------------------------------------------
 __device__ void block_inclusive_scan_lds(int *a, int n, int *tmp) {
   const int per = (n + kBig - 1) / kBig;
@@ -347,11 +360,16 @@ __device__ void block_inclusive_scan_lds(int *a, int n, int *tmp) {
 }
 
 // Per bank: c_r = #{i : first_i <= r} by histogram + scan, and bit r of the
-// feasibility mask set iff c_r <= e_r = max(0, m + r - M) (Eqs. 9-10).
-__global__ __launch_bounds__(kBig) void k_feas_bank(Geom g, Workspace ws) {
-  const int b = blockIdx.x;
+// feasibility mask set iff c_r <= e_r = max(0, m + r - M) (Eqs. 9-10), ANDed into
+// the group's mask.  The group's last bank to arrive (counted in r_star, which
+// k_begin cleared) then takes r* = the largest r feasible for every bank
+// (Eq. 11) and every bank's e_{r*}.  Masks and count go through device-scope
+// atomics; the count's release / acquire orders them.
+__global__ __launch_bounds__(kBig) void k_feas(Geom g, Workspace ws, int32_t *out_rstar) {
+  const int b = blockIdx.x, grp = b / g.gs, b0 = grp * g.gs;
   __shared__ int hist[kSortMax + 1];
   __shared__ int tmp[16];
+  __shared__ int last;
   const int R = ws.R[b];
   const int m = ws.m[b], M = ws.M[b];
   const int mc = ws.whole[b] ? 0 : m;  // a bank replaced whole: every prefix counts as feasible, so r* = R
@@ -369,42 +387,24 @@ __global__ __launch_bounds__(kBig) void k_feas_bank(Geom g, Workspace ws) {
   __syncthreads();
   block_inclusive_scan_lds(hist, R + 1, tmp);
   // one wave per 64 values of r: the flags by ballot, two mask words per wave
-  uint32_t *f = ws.feas + (size_t)b * ws.nfw;
+  uint32_t *f = ws.feas + (size_t)b0 * ws.nfw;
   const int lane = threadIdx.x & 63;
   for (int w2 = threadIdx.x >> 6; 2 * w2 < ws.nfw; w2 += kBig / 64) {
     const int r = 64 * w2 + lane;
     const bool ok = r <= R && hist[r <= R ? r : 0] <= max(0, m + r - M);
     const unsigned long long bits = __ballot(ok);
-    if (lane == 0) f[2 * w2] = (uint32_t)bits;
-    if (lane == 1 && 2 * w2 + 1 < ws.nfw) f[2 * w2 + 1] = (uint32_t)(bits >> 32);
-  }
-}
-
-// Per group: r* = the largest r feasible for every bank of the group (Eq. 11).
-__global__ __launch_bounds__(kBig) void k_feas_group(Geom g, Workspace ws, int32_t *out_rstar) {
-  constexpr int kMaxWords = (DKV_MAX_CANDIDATES + 1 + 31) / 32;
-  const int grp = blockIdx.x;
-  __shared__ int tmp[16];
-  __shared__ uint32_t mask[kMaxWords];
-  const int b0 = grp * g.gs;
-  const int nfw = ws.nfw, tot = g.gs * nfw;
-  for (int w = threadIdx.x; w < nfw; w += kBig) mask[w] = ~0u;
-  __syncthreads();
-  // the group's masks are consecutive (bank j of the group, word w at j * nfw + w):
-  // AND them into LDS, four independent (clamped, unconditional) loads per round trip
-  const uint32_t *gf = ws.feas + (size_t)b0 * nfw;
-  for (int i0 = threadIdx.x; i0 < tot; i0 += 4 * kBig) {
-    uint32_t v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = gf[min(i0 + u * kBig, tot - 1)];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (i0 + u * kBig < tot) atomicAnd(&mask[(i0 + u * kBig) % nfw], v[u]);
+    const uint32_t word = lane == 0 ? (uint32_t)bits : (uint32_t)(bits >> 32);
+    if (lane < 2 && 2 * w2 + lane < ws.nfw)
+      __hip_atomic_fetch_and(&f[2 * w2 + lane], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(&ws.r_star[grp], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == g.gs - 1;
+  __syncthreads();
+  if (!last) return;
   int best = 0;
-  for (int w = threadIdx.x; w < nfw; w += kBig) {
-    const uint32_t bits = mask[w];
+  for (int w = threadIdx.x; w < ws.nfw; w += kBig) {
+    const uint32_t bits = __hip_atomic_load(&f[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (bits) best = max(best, 32 * w + 31 - __clz(bits));
   }
   best = block_max(best, tmp);
@@ -412,10 +412,7 @@ __global__ __launch_bounds__(kBig) void k_feas_group(Geom g, Workspace ws, int32
     ws.r_star[grp] = best;
     if (out_rstar) out_rstar[grp] = best;
   }
-  for (int j = threadIdx.x; j < g.gs; j += kBig) {
-    const int b = b0 + j;
-    ws.e[b] = max(0, ws.m[b] + best - ws.M[b]);
-  }
+  for (int j = threadIdx.x; j < g.gs; j += kBig) ws.e[b0 + j] = max(0, ws.m[b0 + j] + best - ws.M[b0 + j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -462,14 +459,15 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   const int perN = (N + kBig - 1) / kBig;
   const int loN = min(N, (int)threadIdx.x * perN), hiN = min(N, loN + perN);
   int rk[kPerN];
+  const int whole = ws.whole[b];  // 2: every candidate enters, no ranks
 #pragma unroll
   for (int u = 0; u < kPerN; ++u) {
-    const int r = N > 0 ? ws.rank[nb + min(loN + u, N - 1)] : INT_MAX;  // clamped, unconditional
+    const int r = whole == 2 ? 0 : rs > 0 ? ws.rank[nb + min(loN + u, N - 1)] : INT_MAX;  // clamped
     rk[u] = loN + u < hiN ? r : INT_MAX;
   }
   // violators and candidates for the fill (four independent loads per round trip)
   int nv_local = 0;
-  const bool whole = ws.whole[b] != 0;  // e = m: every state leaves, no first crossing was searched
+  // a bank replaced whole: e = m, every state leaves, and no first crossing was searched
   for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kBig) {
     int f[4];
 #pragma unroll
@@ -486,6 +484,19 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   }
   int nv;
   (void)block_excl_scan(nv_local, &nv, tmp);
+  if (rs == 0 && nv == 0) {  // nothing enters or leaves (e_0 = 0): no lists, no destinations
+    if (out.evicted)
+      for (int j = threadIdx.x; j < g.Mcap; j += kBig) out.evicted[rb + j] = -1;
+    if (out.admitted)
+      for (int j = threadIdx.x; j < N; j += kBig) out.admitted[nb + j] = -1;
+    if (threadIdx.x == 0) {
+      ws.n_ev[b] = 0;
+      bank.occupancy[b] = m;
+      if (out.n_evicted) out.n_evicted[b] = 0;
+      if (out.n_admitted) out.n_admitted[b] = 0;
+    }
+    return;
+  }
   int need = e - nv;
   if (need > 0 && need >= m - nv) {
     // every non-violator is evicted too (e = m): no ranking needed
@@ -624,6 +635,7 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   }
   if (threadIdx.x == 0) {
     ws.n_ev[b] = n_ev;
+    if (rs > 0 || n_ev > 0) ws.crossed[0] = 1;
     bank.occupancy[b] = m_new;
     if (out.n_evicted) out.n_evicted[b] = n_ev;
     if (out.n_admitted) out.n_admitted[b] = rs;
@@ -645,9 +657,13 @@ __device__ __forceinline__ void commit_surv(const dkv_bank &bank, const Geom &g,
   const int b = blockIdx.y, v = bx * kThreads + threadIdx.x;
   if (v >= ws.m[b]) return;
   const size_t rb = (size_t)b * g.Mcap;
-  const int to = ws.dest[rb + v];
+  const int rs = ws.r_star[b / g.gs];
+  const bool same = rs == 0 && ws.n_ev[b] == 0;  // nothing entered or left: every state as it is
+  if (same && !(p.flags & DKV_POLICY_REFRESH_BASE)) return;
+  const int to = same ? v : ws.dest[rb + v];
   if (to < 0) return;
-  const int64_t rho = ws.rho_t[rb + v] - ws.sub[rb + v];
+  // r* = 0: the projected density is the density
+  const int64_t rho = (rs > 0 ? ws.rho_t[rb + v] : bank.rho[rb + v]) - ws.sub[rb + v];
   if (to != v) {
     E *K = static_cast<E *>(bank.k);
     E *V = static_cast<E *>(bank.v);
@@ -762,7 +778,7 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   // (and the order they give), which the sequential competition needs in any case
   const bool seq = (p.flags & DKV_POLICY_SEQUENTIAL) != 0;
   const int allow_whole = (seq || out.first_cross || out.rho_tilde) ? 0 : ((out.order || out.score_q) ? 1 : 2);
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, out.first_cross ? 1 : 0, s);
   if (g.N > 0) {
     if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 0);
     else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Score);
@@ -771,20 +787,16 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
     {
       const dim3 grid((unsigned)((ws.npad + kBig - 1) / kBig), (unsigned)g.B);
       const int nch = ws.npad / kChunk;
-      if (nch <= 4) k_sort_rank<4><<<grid, kBig, 0, s>>>(g, ws, out.order);
-      else if (nch <= 8) k_sort_rank<8><<<grid, kBig, 0, s>>>(g, ws, out.order);
-      else if (nch <= 12) k_sort_rank<12><<<grid, kBig, 0, s>>>(g, ws, out.order);
-      else k_sort_rank<kMaxChunks><<<grid, kBig, 0, s>>>(g, ws, out.order);
+      auto rank = nch <= 4 ? k_sort_rank<4> : (nch <= 8 ? k_sort_rank<8> : (nch <= 12 ? k_sort_rank<12> : k_sort_rank<kMaxChunks>));
+      rank<<<grid, kBig, 0, s>>>(g, ws, out.order);
     }
   }
   // within-block sequential competition: the rest is one candidate per step
   if (kMfma && (p.flags & DKV_POLICY_SEQUENTIAL)) return launch_sequential(bank, seg, g, p, out, ws, s);
-  if (g.N > 0 && kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 4);
   // with no candidates only states that already violate are found (prefix 0)
   if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 1);
   else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Cross);
-  k_feas_bank<<<g.B, kBig, 0, s>>>(g, ws);
-  k_feas_group<<<g.G, kBig, 0, s>>>(g, ws, out.r_star);
+  k_feas<<<g.B, kBig, 0, s>>>(g, ws, out.r_star);
   if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 2);
   else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Fixup);
   k_select<<<g.B, kBig, 0, s>>>(bank, g, ws, out, p.flags);
@@ -803,7 +815,7 @@ template <int D, int DT>
 hipError_t score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws,
                       hipStream_t s) {
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, 0, s);
   const bool scores = g.N > 0 && (score_q || score_f);
   if constexpr (DT == DKV_BF16) {
     launch_score_mfma(bank, seg, g, p, scores ? score_q : nullptr, scores ? score_f : nullptr, density, ws, s);
