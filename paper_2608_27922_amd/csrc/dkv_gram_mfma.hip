@@ -410,7 +410,7 @@ __device__ __forceinline__ uint32_t lane_wsum(const f32x16 &u, int nvalid, int h
 constexpr int kColsPerSplit = 1024;
 
 template <int D, int P, bool FOLD, bool KV>
-__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_score_mfma(dkv_bank bank, const void *seg_k, const void *seg_v,
+__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2) void k_score_mfma(dkv_bank bank, const void *seg_k, const void *seg_v,
                                                            Geom g, Prm p, Workspace ws) {
   constexpr int W = gram_waves<D>();
   // One-dimensional grid over (row block, column split, bank), row blocks
@@ -429,8 +429,9 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
   if (c0 >= m || ws.whole[b] == 2) return;  // the order of a block that enters whole is not needed
   const int ncols = min(kColsPerSplit, m - c0);
   constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
-  __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
-  __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[AB];
+  constexpr int K2 = D <= 128 ? 1024 : KB, A2 = D <= 128 ? 16 : AB;  // third stage: descriptor dimension 256 only
+  __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[K2];
+  __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[A2];
   __shared__ __attribute__((aligned(16))) float s0[kSI], s1[kSI], s2[kSI];
   const Desc K{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
   const Desc BK{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)};
@@ -514,86 +515,76 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
   };
   stage_rows_for(0);
   stage_dma_for(0, k0, a0, s0);
-  if (ns > 1) {
-    stage_rows_for(1);
-    stage_dma_for(1, k1, a1, s1);
-    if (ns > 2) stage_rows_for(2);
-  }
+  if (ns > 1) stage_rows_for(1);
   if constexpr (D <= 128) {
-    // Tile-granular software pipeline (see tile_interleave).  Iteration t: tile 1
-    // of stage t with the epilogue of tile 0 (the score scales of both tiles
-    // read from stage t's buffer meanwhile); the wait for stage t + 1 and the
-    // barrier; stage t + 3 issued into stage t's buffers; tile 0 of stage t + 1
-    // with the epilogue of tile 1.
+    // Tile-granular software pipeline (see tile_interleave) over two stage
+    // buffers (the score scales keep three): iteration t: tile 1 of stage t with
+    // the epilogue of tile 0; the wait for stage t + 1 and the barrier; stage
+    // t + 2 issued into stage t's buffers; tile 0 of stage t + 1 with the epilogue
+    // of tile 1.
     int aoff[TileCfg<D>::kSteps];
     frag_offsets<D>(aoff);
-    auto load_bs = [&](const float *tb, float (&bsv)[16]) __attribute__((always_inline)) {
+    auto epi_full = [&](const f32x16 &u, const float *tb) __attribute__((always_inline)) -> uint32_t {
+      uint32_t sa = 0;
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
         const float4 v = *reinterpret_cast<const float4 *>(&tb[8 * gq + 4 * h]);
-        bsv[4 * gq + 0] = v.x;
-        bsv[4 * gq + 1] = v.y;
-        bsv[4 * gq + 2] = v.z;
-        bsv[4 * gq + 3] = v.w;
-      }
-    };
-    auto epi_full = [&](const f32x16 &u, const float (&bsv)[16]) __attribute__((always_inline)) -> uint32_t {
-      uint32_t sa = 0;
+        const float bsv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float tt = FOLD ? u[i] : 1.0f + u[i];
-        float tp = tt;
-        if constexpr (P >= 2) tp = tt * tt;
-        if constexpr (P == 4) tp = tp * tp;
-        const float w = clamp_weight(rcp_rn(tp));
-        sa += __float_as_uint(__builtin_fmaf(w, bsv[i], 8388608.0f));
+        for (int q = 0; q < 4; ++q) {
+          const float tt = FOLD ? u[4 * gq + q] : 1.0f + u[4 * gq + q];
+          float tp = tt;
+          if constexpr (P >= 2) tp = tt * tt;
+          if constexpr (P == 4) tp = tp * tp;
+          const float w = clamp_weight(rcp_rn(tp));
+          sa += __float_as_uint(__builtin_fmaf(w, bsv[q], 8388608.0f));
+        }
       }
       return sa - 16u * kMagic;
     };
     f32x16 u;
     auto pstep = [&](int t, const char *kc, const char *ac, const float *sc, const char *kn, const char *an, char *kd,
                      char *ad, float *sd) __attribute__((always_inline)) {
-      float b0[16], b1[16];
-      load_bs(sc, b0);
-      load_bs(sc + kCT, b1);
       f32x16 xx = tile_mfma<D>(kc, ac, 1, rf, aoff);
-      uint32_t sa = epi_full(u, b0);
-      tile_interleave<D, 11>();  // the 8 score-scale reads lead
+      uint32_t sa = epi_full(u, sc);
+      tile_interleave<D, 7>();  // the 4 score-scale reads lead
       asm volatile("" : "+v"(sa));  // the epilogue of tile 0 stays beside the MFMAs of tile 1
       u = xx;
-      if (t + 2 < ns) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kOps));
-      else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
       stage_barrier();
-      if (t + 3 < ns) {
-        stage_dma_for(t + 3, kd, ad, sd);
-        if (t + 4 < ns) stage_rows_for(t + 4);
+      if (t + 2 < ns) {
+        stage_dma_for(t + 2, kd, ad, sd);
+        if (t + 3 < ns) stage_rows_for(t + 3);
       }
       xx = tile_mfma<D>(kn, an, 0, rf, aoff);
-      sa += epi_full(u, b1);
-      tile_interleave<D>();
+      sa += epi_full(u, sc + kCT);
+      tile_interleave<D, 7>();
       u = xx;
       A64 += sa;
     };
     if (ns > 0) {
-      if (ns > 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kOps));
-      else __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
       stage_barrier();
-      if (ns > 2) {
-        stage_dma_for(2, k2, a2, s2);
-        if (ns > 3) stage_rows_for(3);
+      if (ns > 1) {
+        stage_dma_for(1, k1, a1, s1);
+        if (ns > 2) stage_rows_for(2);
       }
       u = tile_mfma<D>(k0, a0, 0, rf, aoff);
     }
-    for (int t = 0; t + 1 < ns; t += 3) {
-      pstep(t, k0, a0, s0, k1, a1, k0, a0, s0);
-      if (t + 2 < ns) pstep(t + 1, k1, a1, s1, k2, a2, k1, a1, s1);
-      if (t + 3 < ns) pstep(t + 2, k2, a2, s2, k0, a0, k2, a2, s2);
+    for (int t = 0; t + 1 < ns; t += 6) {
+      pstep(t, k0, a0, s0, k1, a1, k0, a0, s2);
+      if (t + 2 < ns) pstep(t + 1, k1, a1, s1, k0, a0, k1, a1, s0);
+      if (t + 3 < ns) pstep(t + 2, k0, a0, s2, k1, a1, k0, a0, s1);
+      if (t + 4 < ns) pstep(t + 3, k1, a1, s0, k0, a0, k1, a1, s2);
+      if (t + 5 < ns) pstep(t + 4, k0, a0, s1, k1, a1, k0, a0, s0);
+      if (t + 6 < ns) pstep(t + 5, k1, a1, s2, k0, a0, k1, a1, s1);
     }
     if (ns > 0) {  // the last stage (possibly partial): u holds its tile 0
       const int t = ns - 1;
       const int nv0 = ncols - t * kSI;
+      const float *sb = t % 3 == 0 ? s0 : (t % 3 == 1 ? s1 : s2);
       // one call per buffer: the LDS arrays stay compile-time known
-      auto last = [&](const char *kb, const char *ab, const float *sb) __attribute__((always_inline)) {
+      auto last = [&](const char *kb, const char *ab) __attribute__((always_inline)) {
         uint32_t sa;
         epi(Part{}, u, sb, nv0, sa);
         A64 += sa;
@@ -603,11 +594,14 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
           A64 += sa;
         }
       };
-      if (t % 3 == 0) last(k0, a0, s0);
-      else if (t % 3 == 1) last(k1, a1, s1);
-      else last(k2, a2, s2);
+      if (t % 2 == 0) last(k0, a0);
+      else last(k1, a1);
     }
   } else {
+  if (ns > 1) {
+    stage_dma_for(1, k1, a1, s1);
+    if (ns > 2) stage_rows_for(2);
+  }
   for (int t = 0; t < ns; t += 3) {
     step(t, k0, a0, s0, k2, a2, s2);
     if (t + 1 < ns) step(t + 1, k1, a1, s1, k0, a0, s0);
