@@ -409,7 +409,19 @@ __device__ __forceinline__ uint32_t lane_wsum(const f32x16 &u, int nvalid, int h
 // ---------------------------------------------------------------------------
 constexpr int kColsPerSplit = 1024;
 
-template <int D, int P, bool FOLD, bool KV>
+// APPROX: the sums with the hardware reciprocal in place of the correctly rounded
+// one and in binary32 within a tile, for calls that need the candidates' order
+// only: |S~ - S| <= score_tol(S~, m).  Per pair 16 instead of 26 VALU cycles, so
+// that the matrix cores bound the loop; where the bound leaves a position open,
+// k_rescore computes the exact scores (below).
+//   v_rcp_f32 is within 1 ulp (2^-23) of 1 / t^p, the correctly rounded weight
+//   within 2^-24: together 3 2^-24 per term; eight terms in a chain and the sum of
+//   the two chains add at most 9 2^-24; the exact terms are rounded to integers
+//   (1/2 each), the tile's sum once (1/2 per 32 terms and half-wave): 12 2^-24 S +
+//   (1/2 + 1/32) m, below S / 2^20 + m.
+__device__ __forceinline__ int64_t score_tol(int64_t s, int m) { return (s >> 20) + m + 2; }
+
+template <int D, int P, bool FOLD, bool KV, bool APPROX>
 __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2) void k_score_mfma(dkv_bank bank, const void *seg_k, const void *seg_v,
                                                            Geom g, Prm p, Workspace ws) {
   constexpr int W = gram_waves<D>();
@@ -458,18 +470,25 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
       bsv[4 * gq + 3] = v.w;
     }
     sa = 0;
+    float fa[2] = {0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float tt = FOLD ? u[i] : 1.0f + u[i];
       float tp = tt;
       if constexpr (P >= 2) tp = tt * tt;
       if constexpr (P == 4) tp = tp * tp;
-      const float w = clamp_weight(rcp_rn(tp));
-      uint32_t ra = __float_as_uint(__builtin_fmaf(w, bsv[i], 8388608.0f));
-      if constexpr (MASK) ra = col_of_reg(i, h) < nvalid ? ra : kMagic;
-      sa += ra;
+      if constexpr (APPROX) {
+        const float y = clamp_weight(__builtin_amdgcn_rcpf(tp));
+        fa[i & 1] = __builtin_fmaf(!MASK || col_of_reg(i, h) < nvalid ? y : 0.0f, bsv[i], fa[i & 1]);
+      } else {
+        const float w = clamp_weight(rcp_rn(tp));
+        uint32_t ra = __float_as_uint(__builtin_fmaf(w, bsv[i], 8388608.0f));
+        if constexpr (MASK) ra = col_of_reg(i, h) < nvalid ? ra : kMagic;
+        sa += ra;
+      }
     }
-    sa -= 16u * kMagic;
+    if constexpr (APPROX) sa = (uint32_t)__builtin_rintf(fa[0] + fa[1]);
+    else sa -= 16u * kMagic;
   };
   using Full = std::integral_constant<bool, false>;
   using Part = std::integral_constant<bool, true>;
@@ -526,6 +545,7 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
     frag_offsets<D>(aoff);
     auto epi_full = [&](const f32x16 &u, const float *tb) __attribute__((always_inline)) -> uint32_t {
       uint32_t sa = 0;
+      float fa[2] = {0.0f, 0.0f};
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
         const float4 v = *reinterpret_cast<const float4 *>(&tb[8 * gq + 4 * h]);
@@ -536,11 +556,15 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
           float tp = tt;
           if constexpr (P >= 2) tp = tt * tt;
           if constexpr (P == 4) tp = tp * tp;
-          const float w = clamp_weight(rcp_rn(tp));
-          sa += __float_as_uint(__builtin_fmaf(w, bsv[q], 8388608.0f));
+          if constexpr (APPROX) {
+            fa[q & 1] = __builtin_fmaf(clamp_weight(__builtin_amdgcn_rcpf(tp)), bsv[q], fa[q & 1]);
+          } else {
+            const float w = clamp_weight(rcp_rn(tp));
+            sa += __float_as_uint(__builtin_fmaf(w, bsv[q], 8388608.0f));
+          }
         }
       }
-      return sa - 16u * kMagic;
+      return APPROX ? (uint32_t)__builtin_rintf(fa[0] + fa[1]) : sa - 16u * kMagic;
     };
     f32x16 u;
     auto pstep = [&](int t, const char *kc, const char *ac, const float *sc, const char *kn, const char *an, char *kd,
@@ -612,6 +636,192 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
   if (!rv || h != 0) return;
   const size_t o = (size_t)b * g.N + x;
   atomicAdd(reinterpret_cast<unsigned long long *>(&ws.acol[o]), (unsigned long long)At);
+}
+
+// ---------------------------------------------------------------------------
+// Exact order from approximate scores.  Neighbours in the approximate order whose
+// difference is within the two bounds (score_tol grows with the score, so a clear
+// gap separates everything before it from everything after it) form clusters;
+// inside them the exact scores decide.  k_order_mark lists the members in
+// position order: first those of clusters that begin within the first part of the
+// crossing search (or, for a bank replaced whole with fewer states than
+// candidates, the cluster across position R: only the set matters), then the
+// rest, whose order only the groups that the first part leaves open need.
+// k_rescore sums their exact scores, k_order_fix places them.
+// Storage: adm_list = candidate, adm_dest = position | ambiguous with the next
+// (bit 30), n_ev / e = members in the first list / in both, sub_adm = exact sums
+// (cleared again when read); all of it is free until the selection.
+// ---------------------------------------------------------------------------
+constexpr int kOrderThreads = 1024;
+constexpr int kAmbiguous = 1 << 30;
+
+__global__ __launch_bounds__(kOrderThreads) void k_order_mark(Geom g, Workspace ws) {
+  const int b = blockIdx.x, m = ws.m[b], R = ws.R[b], N = g.N, whole = ws.whole[b];
+  const size_t nb = (size_t)b * N;
+  __shared__ int64_t S[kSortMax];
+  __shared__ int tmp[2][kOrderThreads / 64];
+  __shared__ int lo, hi;  // positions [lo, hi): whole = 1: the cluster across R; else the first list's
+  constexpr int kPer = kSortMax / kOrderThreads;
+  if (m == 0 || whole == 2) {  // every score is 0 and exact, or no order is needed
+    if (threadIdx.x == 0) ws.n_ev[b] = ws.e[b] = 0;
+    return;
+  }
+  int xs[kPer];  // positions threadIdx.x + u kOrderThreads
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) xs[u] = ws.order[nb + min((int)threadIdx.x + u * kOrderThreads, N - 1)];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t v = ws.acol[nb + xs[u]];
+    if ((int)threadIdx.x + u * kOrderThreads < N) S[threadIdx.x + u * kOrderThreads] = v;
+  }
+  if (threadIdx.x == 0) lo = whole ? 0 : -1, hi = N;
+  __syncthreads();
+  auto amb = [&](int p) {  // position p with p + 1
+    return p >= 0 && p + 1 < N && S[p + 1] - S[p] <= score_tol(S[p], m) + score_tol(S[p + 1], m);
+  };
+  const int cut = whole ? R : kCrossFirst;  // a cluster is wanted first if it reaches across (whole), or begins before, this position
+  for (int p = threadIdx.x; p < N; p += kOrderThreads)
+    if (!amb(p)) {
+      if (p >= cut - 1) atomicMin(&hi, p + 1);
+      else if (whole) atomicMax(&lo, p + 1);
+    }
+  __syncthreads();
+  if (whole && !(R > 0 && amb(R - 1))) hi = lo;  // (the same value from every thread)
+  __syncthreads();
+  const int l0 = whole ? lo : 0, l1 = hi;
+  // members in position order: each thread's contiguous positions, then a scan
+  const int per = (N + kOrderThreads - 1) / kOrderThreads;
+  const int p0 = min(N, (int)threadIdx.x * per), p1 = min(N, p0 + per);
+  int head = 0, all = 0;
+  for (int p = p0; p < p1; ++p) {
+    const bool f = (amb(p - 1) || amb(p)) && (!whole || (p >= l0 && p < l1));
+    all += f;
+    head += f && p < l1;
+  }
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  int ia = all, ih = head;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int ya = __shfl_up(ia, o, 64), yh = __shfl_up(ih, o, 64);
+    if (lane >= o) ia += ya, ih += yh;
+  }
+  if (lane == 63) tmp[0][wid] = ia, tmp[1][wid] = ih;
+  __syncthreads();
+  int k = ia - all, ta = 0, th = 0;
+  for (int w = 0; w < kOrderThreads / 64; ++w) {
+    if (w < wid) k += tmp[0][w];
+    ta += tmp[0][w];
+    th += tmp[1][w];
+  }
+  for (int p = p0; p < p1; ++p) {
+    const bool next = amb(p);
+    if (!((amb(p - 1) || next) && (!whole || (p >= l0 && p < l1)))) continue;
+    ws.adm_list[nb + k] = ws.order[nb + p];
+    ws.adm_dest[nb + k] = p | (next ? kAmbiguous : 0);
+    ++k;
+  }
+  if (threadIdx.x == 0) {
+    ws.n_ev[b] = th;
+    ws.e[b] = ta;
+  }
+}
+
+// Entries [k0, k1) of a bank's members: the first list, or (rest) the others of an open group.
+__device__ __forceinline__ void order_range(const Geom &g, const Workspace &ws, int b, int rest, int &k0, int &k1) {
+  k0 = rest ? ws.n_ev[b] : 0;
+  k1 = rest ? (ws.more[b / g.gs] >= kMoreOpen ? ws.e[b] : k0) : ws.n_ev[b];
+}
+
+// Exact scores of the listed candidates: 32 of them and 1,024 bank states per
+// work item; a wave takes every fourth tile of 32 states, straight from global
+// memory (the few rows give no reuse that LDS could serve).
+template <int D, int P, bool FOLD, bool KV>
+__global__ __launch_bounds__(256) void k_rescore(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p,
+                                                 Workspace ws, int rest) {
+  __shared__ int pre[65];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, h = l >> 5, n = l & 31;
+  const Desc SK{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
+  const Desc BK{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)};
+  auto splits = [&](int b) { return (ws.m[b] + kColsPerSplit - 1) / kColsPerSplit; };
+  walk_items(
+      g.B, pre,
+      [&](int b) {
+        int k0, k1;
+        order_range(g, ws, b, rest, k0, k1);
+        return (k1 - k0 + 31) / 32 * splits(b);
+      },
+      [&](int b, int i) __attribute__((always_inline)) {
+        constexpr int KS = TileCfg<D>::kSteps;
+        int k0, k1;
+        order_range(g, ws, b, rest, k0, k1);
+        const int ny = splits(b), k = k0 + i / ny * 32 + n, c0 = i % ny * kColsPerSplit;
+        const int c1 = min(ws.m[b], c0 + kColsPerSplit);
+        const size_t nb = (size_t)b * g.N, rb = (size_t)b * g.Mcap;
+        const bool v = k < k1;
+        const int64_t xr = (int64_t)(nb + ws.adm_list[nb + min(k, k1 - 1)]);
+        RowFrag<D> rf;
+        load_row_frag<D, FOLD, KV>(rf, SK, xr, ws.cnorm[xr], v, -2.0f * p.inv_sigma2, p.inv_sigma2);
+        uint64_t sum = 0;
+        for (int j0 = c0 + wave * kCT; j0 < c1; j0 += kWaves * kCT) {
+          const int64_t r = (int64_t)(rb + min(j0 + n, c1 - 1));
+          f32x16 u = {};
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk)
+            u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(desc_chunk<D, KV>(BK, r, 2 * kk + h))),
+                rf.b[kk], u, 0, 0, 0);
+          u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ws.baug[r]), rf.b[KS], u, 0, 0, 0);
+          uint32_t s = 0;
+#pragma unroll
+          for (int q = 0; q < 16; ++q) {
+            const int j = j0 + col_of_reg(q, h);
+            const uint32_t raw = weight_raw<P, FOLD>(u[q], ws.bs[rb + min(j, c1 - 1)]);
+            s += j < c1 ? raw - kMagic : 0u;
+          }
+          sum += s;
+        }
+        sum += __shfl_xor(sum, 32, 64);
+        if (v && h == 0) atomicAdd(reinterpret_cast<unsigned long long *>(&ws.sub_adm[xr]), (unsigned long long)sum);
+      });
+}
+
+// The members of a cluster take its positions in the order of (exact score,
+// source index); one workgroup per bank.
+__global__ __launch_bounds__(kOrderThreads) void k_order_fix(Geom g, Workspace ws, int rest) {
+  const int b = blockIdx.x;
+  const size_t nb = (size_t)b * g.N;
+  int k0, k1;
+  order_range(g, ws, b, rest, k0, k1);
+  if (k0 >= k1) return;
+  __shared__ int64_t S[kSortMax];
+  __shared__ uint32_t X[kSortMax];  // candidate, and in bit 31: ambiguous with the next position
+  for (int k = k0 + (int)threadIdx.x; k < k1; k += kOrderThreads) {
+    const int x = ws.adm_list[nb + k];
+    S[k - k0] = ws.sub_adm[nb + x];
+    ws.sub_adm[nb + x] = 0;
+    X[k - k0] = (uint32_t)x | (ws.adm_dest[nb + k] & kAmbiguous ? 0x80000000u : 0u);
+  }
+  __syncthreads();
+  const int cnt = k1 - k0;
+  for (int k = threadIdx.x; k < cnt; k += kOrderThreads) {
+    const int x = (int)(X[k] & 0x7FFFFFFFu);
+    const int64_t s = S[k];
+    int first = k, less = 0;
+    // members are listed by position, so a cluster is a run whose entries are ambiguous with their next
+    while (first > 0 && (X[first - 1] >> 31)) {
+      --first;
+      const int y = (int)(X[first] & 0x7FFFFFFFu);
+      less += S[first] < s || (S[first] == s && y < x);
+    }
+    for (int j = k; X[j] >> 31; ) {
+      ++j;
+      const int y = (int)(X[j] & 0x7FFFFFFFu);
+      less += S[j] < s || (S[j] == s && y < x);
+    }
+    const int pos = (ws.adm_dest[nb + k0 + first] & ~kAmbiguous) + less;
+    ws.order[nb + pos] = x;
+    ws.rank[nb + x] = pos;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1813,18 +2023,30 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
   const unsigned rowsM = cdiv(g.Mcap, 32 * W), rowsN = cdiv(g.N > 0 ? g.N : 1, 32 * W);
   const void *sv = seg.v;
   switch (stage) {
-    case 0:  // score; the ordered copy is launched after the sort (stage 4)
-      k_score_mfma<D, P, F, KV><<<rowsN * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(bank, seg.k, sv, g,
-                                                                                                   p, ws);
+    case kGramScore:
+    case kGramScoreApprox:
+      (stage == kGramScore ? k_score_mfma<D, P, F, KV, false> : k_score_mfma<D, P, F, KV, true>)
+          <<<rowsN * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(bank, seg.k, sv, g, p, ws);
       break;
-    case 1: {
+    case kGramOrder:
+    case kGramOrderRest: {
+      const int rest = stage == kGramOrderRest;
+      if (!rest) k_order_mark<<<g.B, kOrderThreads, 0, s>>>(g, ws);
+      k_rescore<D, P, F, KV><<<grid_of((uint64_t)cdiv(g.N, 32) * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, 2048), 256, 0,
+                               s>>>(bank, seg.k, sv, g, p, ws, rest);
+      k_order_fix<<<g.B, kOrderThreads, 0, s>>>(g, ws, rest);
+      break;
+    }
+    case kGramFirstPart:
+    case kGramSecondPart: {
       // The crossing search in two parts: the chunk sums of the first
       // kCrossFirst ordered candidates and the crossings within them; then, for
       // the groups that this leaves open, the ordered copy and the chunk sums of
       // the rest and the whole search again.
-      k_first_part_mfma<D, P, F, KV><<<dim3(cdiv(g.Mcap, 32 * kWaves), g.B), 64 * kWaves, 0, s>>>(bank, seg.k, sv, g, p,
-                                                                                                ws, out.first_cross);
-      if (g.N > kCrossFirst) {
+      if (stage == kGramFirstPart) {
+        k_first_part_mfma<D, P, F, KV><<<dim3(cdiv(g.Mcap, 32 * kWaves), g.B), 64 * kWaves, 0, s>>>(
+            bank, seg.k, sv, g, p, ws, out.first_cross);
+      } else {
         const unsigned B = (unsigned)g.B;
         k_gather_sorted<D, KV><<<grid_of((uint64_t)cdiv(g.N, 256 / (D / 8) * kGatherRows) * B, 1024), 256, 0, s>>>(
             seg.k, sv, g, ws);
@@ -1835,10 +2057,10 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
       }
       break;
     }
-    case 2:
+    case kGramFixup:
       k_rowsum_mfma<D, P, RS_FIXUP, F, KV><<<dim3(rowsM, 1, g.B), T, 0, s>>>(bank, seg.k, sv, g, p, ws, out.rho_tilde);
       break;
-    case 3: {
+    case kGramMaint: {
       // at most this many items per bank, but for states that violated before the update
       const uint64_t y_ev = cdiv(g.N > 0 ? g.N : 1, kColsPerSplit), y_surv = cdiv(g.Mcap, kColsPerSplit);
       const uint64_t items = rowsM * y_ev + (g.N > 0 ? rowsN : 0u) * (y_surv + 1 + cdiv(g.N, kSymStages * kSI));
@@ -1868,7 +2090,7 @@ void mfma_score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g
   constexpr int W = gram_waves<D>();
   const int T = 64 * W;
   if (g.N > 0 && (score_q || score_f)) {
-    k_score_mfma<D, P, F, KV><<<cdiv(g.N, 32 * W) * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(
+    k_score_mfma<D, P, F, KV, false><<<cdiv(g.N, 32 * W) * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(
         bank, seg.k, seg.v, g, p, ws);
   }
   if (density) {
@@ -1894,8 +2116,7 @@ void mfma_score_d(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, c
 #define DKV_CAT2(a, b, c) a##b##_kv##c
 #define DKV_CAT(a, b, c) DKV_CAT2(a, b, c)
 
-// Stage launchers used by the update sequence for bf16 banks:
-// 0 score, 1 crossing, 2 r* fix-up, 3 maintenance.
+// Stage launchers (GramStage) used by the update sequence for bf16 banks.
 void DKV_CAT(launch_gram_d, DKV_GRAM_DESC, DKV_GRAM_KV)(const dkv_bank &bank, const dkv_segment &seg, const Geom &g,
                                                         const Prm &p, const dkv_update_out &out, const Workspace &ws,
                                                         hipStream_t s, int stage) {

@@ -115,6 +115,12 @@ struct KvSeg {
 hipError_t launch_attention(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvSeg sink,
                             void *out, float scale, const Geom &g, void *ws, int nsplit, hipStream_t s);
 int attention_splits(const dkv_bank &bank, int nq, int nw, int ns, size_t *bytes);
+// Stages: the score (exact, or approximate with the order made exact afterwards: kGramOrder for the positions the
+// first part of the crossing search reads, kGramOrderRest for the others of open groups), the crossing search in
+// two parts, the projected densities, the maintenance.
+enum GramStage {
+  kGramScore, kGramScoreApprox, kGramOrder, kGramFirstPart, kGramOrderRest, kGramSecondPart, kGramFixup, kGramMaint
+};
 // The Gram stages of bf16 banks per descriptor geometry (dkv_gram_mfma.hip, compiled once for each): the
 // descriptor dimension is the key dimension, or twice it for the concatenated [K; V] rows.
 #define DKV_DECLARE_GRAM(D, KV)                                                                                     \

@@ -768,6 +768,8 @@ __global__ void k_pair_weight(const float *d2, int64_t n, Prm p, int32_t *w) {
 
 inline dim3 grid2(int n, int per, int B) { return dim3((unsigned)((n + per - 1) / per), (unsigned)B); }
 
+constexpr double kApproxPairs = 2e9;
+
 template <int D, int DT>
 hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
                        const dkv_update_out *outp, const Workspace &ws, hipStream_t s) {
@@ -778,10 +780,20 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   // (and the order they give), which the sequential competition needs in any case
   const bool seq = (p.flags & DKV_POLICY_SEQUENTIAL) != 0;
   const int allow_whole = (seq || out.first_cross || out.rho_tilde) ? 0 : ((out.order || out.score_q) ? 1 : 2);
+  // Large calls that ask for neither the scores nor the order take approximate
+  // scores first and exact ones only where the approximation leaves the order
+  // open (dkv_gram_mfma.hip): five more launches and a second read of the bank
+  // keys, against a third of the score's time; below about 2e9 pairs
+  // (by capacity) these cost as much as they save.
+  const bool approx = kMfma && !seq && !(p.flags & DKV_POLICY_SOURCE_ORDER) && !out.order && !out.score_q &&
+                      (double)g.B * g.Mcap * g.N >= kApproxPairs;
   launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, out.first_cross ? 1 : 0, s);
   if (g.N > 0) {
-    if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 0);
-    else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Score);
+    // in source order the scores are only reported
+    if (!(p.flags & DKV_POLICY_SOURCE_ORDER) || out.score_q) {
+      if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, approx ? kGramScoreApprox : kGramScore);
+      else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Score);
+    }
     k_sort_chunks<<<dim3((unsigned)((g.N + kChunk - 1) / kChunk), (unsigned)g.B), kSortThreads, 0, s>>>(
         g, ws, out.score_q, (p.flags & DKV_POLICY_SOURCE_ORDER) ? 1 : 0);
     {
@@ -794,13 +806,21 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   // within-block sequential competition: the rest is one candidate per step
   if (kMfma && (p.flags & DKV_POLICY_SEQUENTIAL)) return launch_sequential(bank, seg, g, p, out, ws, s);
   // with no candidates only states that already violate are found (prefix 0)
-  if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 1);
-  else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Cross);
+  if (kMfma) {
+    if (approx) launch_gram_mfma(bank, seg, g, p, out, ws, s, kGramOrder);
+    launch_gram_mfma(bank, seg, g, p, out, ws, s, kGramFirstPart);
+    if (g.N > kCrossFirst) {
+      if (approx) launch_gram_mfma(bank, seg, g, p, out, ws, s, kGramOrderRest);
+      launch_gram_mfma(bank, seg, g, p, out, ws, s, kGramSecondPart);
+    }
+  } else {
+    launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Cross);
+  }
   k_feas<<<g.B, kBig, 0, s>>>(g, ws, out.r_star);
-  if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 2);
+  if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, kGramFixup);
   else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Fixup);
   k_select<<<g.B, kBig, 0, s>>>(bank, g, ws, out, p.flags);
-  if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, 3);
+  if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, kGramMaint);
   else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Maint);
   {
     const int nxs = (g.Mcap + kThreads - 1) / kThreads;
