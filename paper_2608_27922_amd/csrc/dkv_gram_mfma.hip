@@ -1193,18 +1193,43 @@ __device__ __forceinline__ uint32_t row_transpose_sum(const uint32_t (&w)[16], i
   return row_transpose_tail(a, l);
 }
 
-// Work items of n list items in blocks of 32 W: J = 0 .. blocks - 1, each its own
-// block (run 0) and its runs after it.
+// Work items of n list items in blocks of 32 W: block J's runs over the items after
+// it, then every block's own.  A run spans S = kSymStages kSI / (32 W) blocks, so
+// block J with k blocks after it has ceil(k / S) runs (a last block that is not
+// full leaves that as it is), and the items of the blocks with at most k blocks
+// after them are a closed form: no walk over the blocks per item (up to 74 dependent
+// scalar steps at 9,360 items).
 template <int W>
-__device__ __forceinline__ int sym_runs(int n, int J) {
-  const int after = n - 32 * W * (J + 1);
-  return 1 + (after > 0 ? (after + kSymStages * kSI - 1) / (kSymStages * kSI) : 0);
+constexpr int kSymBlocks = kSymStages * kSI / (32 * W);
+template <int W>
+__host__ __device__ constexpr int sym_before(int k) {  // runs of the blocks with at most k blocks after them
+  constexpr int S = kSymBlocks<W>;
+  const int q = k / S, r = k % S;
+  return S * q * (q + 1) / 2 + r * (q + 1);
 }
 template <int W>
-__device__ __forceinline__ int sym_items(int n) {
-  int c = 0;
-  for (int J = 0; J * 32 * W < n; ++J) c += sym_runs<W>(n, J);
-  return c;
+__host__ __device__ constexpr int sym_items(int n) {
+  const int nb = (n + 32 * W - 1) / (32 * W);
+  return nb + (nb > 0 ? sym_before<W>(nb - 1) : 0);
+}
+// Item -> block J and run (-1: the block's own).
+template <int W>
+__device__ __forceinline__ void sym_item(int n, int item, int &J, int &run) {
+  static_assert(kSymStages * kSI % (32 * W) == 0, "runs of whole blocks");
+  constexpr int S = kSymBlocks<W>;
+  const int nb = (n + 32 * W - 1) / (32 * W), off = sym_before<W>(nb - 1);
+  if (item >= off) {
+    J = item - off;
+    run = -1;
+    return;
+  }
+  // blocks with q S + 1 .. (q + 1) S blocks after them have q + 1 runs each
+  int q = (int)((__builtin_sqrtf(1.0f + 8.0f / S * (float)item) - 1.0f) * 0.5f);
+  while (S * q * (q + 1) / 2 > item) --q;
+  while (S * (q + 1) * (q + 2) / 2 <= item) ++q;
+  const int t = item - S * q * (q + 1) / 2, u = t / (q + 1);
+  J = nb - 2 - S * q - u;
+  run = t - u * (q + 1);
 }
 
 template <int D, int P, bool FOLD, bool KV, bool ADM>
@@ -1212,12 +1237,8 @@ __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k
                                          const Prm &p, const Workspace &ws, int n_items, int item, int b,
                                          const StageBufs<D> &sb) {
   constexpr int W = gram_waves<D>();
-  int J = 0;
-  for (;; ++J) {
-    const int r = sym_runs<W>(n_items, J);
-    if (item < r) break;
-    item -= r;
-  }
+  int J, run;
+  sym_item<W>(n_items, item, J, run);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, h = l >> 5, n = l & 31;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   const Desc src = ADM ? Desc{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)}
@@ -1227,24 +1248,28 @@ __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k
   const int64_t row0 = ADM ? (int64_t)nb : (int64_t)rb;
   auto row_of = [&](int j) -> int64_t { return ADM ? (int64_t)(nb + ws.adm_list[nb + j]) : (int64_t)(rb + j); };
   // streamed items [j0, j1)
-  const bool diag = item == 0;
+  const bool diag = run < 0;
   const int hold0 = J * 32 * W;
-  const int j0 = diag ? hold0 : hold0 + 32 * W + (item - 1) * kSymStages * kSI;
+  const int j0 = diag ? hold0 : hold0 + 32 * W + run * kSymStages * kSI;
   const int j1 = min(n_items, j0 + (diag ? 32 * W : kSymStages * kSI));
   const int ncols = j1 - j0, ns = (ncols + kSI - 1) / kSI;
-  // stage loads: list rows fetched one stage ahead of their use
+  // stage loads: a bank's slots in order take the per-lane offsets of consecutive
+  // rows; list rows are fetched one stage ahead of their use
+  constexpr bool kSeq = !ADM && !KV;
   StageRows<D, W> rows;
+  [[maybe_unused]] const StageOff<D, W> soff = stage_offsets<D, W>();
   auto fetch = [&](int st) __attribute__((always_inline)) {
-    stage_rows<D, W>(rows, st * kSI, ncols, [&](int j) { return row_of(j0 + j); });
+    if constexpr (!kSeq) stage_rows<D, W>(rows, st * kSI, ncols, [&](int j) { return row_of(j0 + j); });
   };
-  auto issue = [&](char *kd, char *ad) __attribute__((always_inline)) {
-    stage_dma<D, false, KV, W>(rows, src, aug, nullptr, kd, ad, nullptr, row0, ADM ? g.N : g.Mcap);
+  auto issue = [&](int st, char *kd, char *ad) __attribute__((always_inline)) {
+    if constexpr (kSeq) stage_dma_seq<D, false, W>(soff, j0 + st * kSI, src.k, aug, nullptr, kd, ad, nullptr, row0, g.Mcap);
+    else stage_dma<D, false, KV, W>(rows, src, aug, nullptr, kd, ad, nullptr, row0, ADM ? g.N : g.Mcap);
   };
   fetch(0);
-  issue(sb.k0, sb.a0);
+  issue(0, sb.k0, sb.a0);
   if (ns > 1) {
     fetch(1);
-    issue(sb.k1, sb.a1);
+    issue(1, sb.k1, sb.a1);
     if (ns > 2) fetch(2);
   }
   for (int i = threadIdx.x; i < 3 * kSI; i += 64 * W) sb.cb[i] = 0;  // before the first stage barrier
@@ -1327,7 +1352,7 @@ __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k
       __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
       stage_barrier();
       if (t + 2 < ns) {
-        issue(kn, an);
+        issue(t + 2, kn, an);
         if (t + 3 < ns) fetch(t + 3);
       }
       if (!diag && t > 0) flush(t - 1);
@@ -1356,7 +1381,7 @@ __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k
       u = x;
       stage_wait(t + 2 < ns);
       if (t + 3 < ns) {
-        issue(kd, ad);
+        issue(t + 3, kd, ad);
         if (t + 4 < ns) fetch(t + 4);
       }
       if (t > 0) flush(t - 1);
@@ -1373,7 +1398,7 @@ __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k
     };
     stage_wait(ns > 1);
     if (ns > 2) {
-      issue(sb.k2, sb.a2);
+      issue(2, sb.k2, sb.a2);
       if (ns > 3) fetch(3);
     }
     u = tile(sb.k0, sb.a0, 0);

@@ -99,3 +99,30 @@ def test_attention_key_splits_of_infinite_scores(dt):
     bank.k[:, :, 0] = 0.0
     bank.k[:, 3, 5] = float("nan")
     assert api.bank_attention(bank, q, None, None).isnan().all()
+
+
+@pytest.mark.parametrize("d,kv", [(64, False), (128, False), (128, True)])
+@pytest.mark.parametrize("m", [1, 63, 128, 129, 896, 897, 1793])  # blocks of 128 (256) held items, runs of 768 streamed ones
+def test_densities_at_run_edges(d, kv, m):
+    """From-scratch densities as a symmetric Gram against direct sums over pairs: every pair once, whatever
+    number of held blocks and streamed runs the list has (whole numbers: keys on the grid, t exact)."""
+    _log(f"densities d={d} kv={kv} m={m}")
+    g = torch.Generator(device="cuda").manual_seed(7 * m + d)
+    prm = api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0)
+    bank = api.Bank(2, 1800, d)
+    rows = (torch.randint(-40, 41, (2, m, 2, d), generator=g, device="cuda") / 64.0).to(torch.bfloat16)
+    bank.k[:, :m], bank.v[:, :m] = rows[:, :, 0], rows[:, :, 1]
+    desc = rows.flatten(2) if kv else rows[:, :, 0]
+    bank.knorm[:, :m] = desc.float().square().sum(-1)
+    bank.base.fill_(1 << 23)
+    bank.occupancy.fill_(m)
+    seg = torch.zeros(2, 1, d, device="cuda", dtype=torch.bfloat16)
+    dens = api.score(bank, seg, seg, prm, want_density=True)[2]
+    for b in range(2):
+        x = desc[b].double().cpu()
+        d2 = (x * x).sum(-1)[:, None] + (x * x).sum(-1)[None] - 2.0 * x @ x.T  # exact on the grid
+        t = (1.0 + d2.float() / 32.0)  # exact in binary32
+        w = (1.0 / (t * t).double()).float()  # correctly rounded reciprocal of the rounded square
+        W = torch.round(w.double() * 2.0 ** 23).long()
+        W.fill_diagonal_(0)
+        assert torch.equal(dens[b, :m].cpu(), W.sum(-1)), f"bank {b}"
