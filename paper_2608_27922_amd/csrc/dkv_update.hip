@@ -244,7 +244,9 @@ void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, c
 // ---------------------------------------------------------------------------
 // Candidate order: unique keys (S_x << 13) | x sorted ascending (ties of S_x
 // by source index).  k_sort_chunks: a workgroup sorts a chunk of 512 keys in
-// LDS with a bitonic network (one compare-exchange per thread and stage).
+// LDS with a bitonic network (one compare-exchange per thread and stage; a chunk
+// of n keys needs the stages of the next power of two only, the rest is padding
+// in place already).  Up to 512 candidates that is the whole order.
 // k_sort_rank: the rank of a key is its position in its own chunk plus the
 // number of smaller keys in every other chunk, found by branch-free binary
 // searches that run in lockstep over all chunks (ten dependent LDS rounds).
@@ -253,8 +255,10 @@ constexpr int kChunk = 512;
 constexpr int kSortThreads = kChunk / 2;
 constexpr int kMaxChunks = kSortMax / kChunk;
 
+// ONE: the call has one chunk, whose positions are the ranks (no k_sort_rank).
+template <bool ONE>
 __global__ __launch_bounds__(kSortThreads) void k_sort_chunks(Geom g, Workspace ws, int64_t *out_score,
-                                                              int source_order) {
+                                                              int32_t *out_order, int source_order) {
   const int b = blockIdx.y, c = blockIdx.x, t = threadIdx.x;
   if (ws.whole[b] == 2) return;  // no order needed
   const size_t nb = (size_t)b * g.N;
@@ -272,7 +276,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_chunks(Geom g, Workspace 
     if (out_score && idx < g.N) out_score[nb + idx] = A[u];
   }
   __syncthreads();
-  for (int k = 2; k <= kChunk; k <<= 1) {
+  const int n = min(kChunk, g.N - c * kChunk);
+  for (int k = 2; k < 2 * n && k <= kChunk; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
       // the t-th index i with bit j clear, against i + j; ascending where bit k of i is clear
       const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
@@ -284,6 +289,18 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_chunks(Geom g, Workspace 
       }
       __syncthreads();
     }
+  }
+  if constexpr (ONE) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = t + u * kSortThreads;
+      if (r >= g.N) continue;
+      const int x = (int)(v[r] & 0x1FFFull);
+      ws.order[nb + r] = x;
+      ws.rank[nb + x] = r;
+      if (out_order) out_order[nb + r] = x;
+    }
+    return;
   }
   const size_t base = (size_t)b * ws.npad + (size_t)c * kChunk;
 #pragma unroll
@@ -372,11 +389,19 @@ __global__ __launch_bounds__(kBig) void k_feas(Geom g, Workspace ws, int32_t *ou
   __shared__ int last;
   const int R = ws.R[b];
   const int m = ws.m[b], M = ws.M[b];
-  const int mc = ws.whole[b] ? 0 : m;  // a bank replaced whole: every prefix counts as feasible, so r* = R
+  if (ws.whole[b]) {  // a group replaced whole (of all its banks or none): r* = R, nothing to search
+    if (b != b0) return;
+    if (threadIdx.x == 0) {
+      ws.r_star[grp] = R;
+      if (out_rstar) out_rstar[grp] = R;
+    }
+    for (int j = threadIdx.x; j < g.gs; j += kBig) ws.e[b0 + j] = max(0, ws.m[b0 + j] + R - ws.M[b0 + j]);
+    return;
+  }
   for (int r = threadIdx.x; r <= R; r += kBig) hist[r] = 0;
   __syncthreads();
   // four independent (clamped, unconditional) loads per round trip
-  for (int i0 = threadIdx.x; i0 < mc; i0 += 4 * kBig) {
+  for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kBig) {
     int t[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) t[u] = ws.first[(size_t)b * g.Mcap + min(i0 + u * kBig, m - 1)];
@@ -462,12 +487,47 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
   const int whole = ws.whole[b];  // 2: every candidate enters, no ranks
 #pragma unroll
   for (int u = 0; u < kPerN; ++u) {
-    const int r = whole == 2 ? 0 : rs > 0 ? ws.rank[nb + min(loN + u, N - 1)] : INT_MAX;  // clamped
+    const int r = whole != 2 && rs > 0 ? ws.rank[nb + min(loN + u, N - 1)] : INT_MAX;  // clamped
     rk[u] = loN + u < hiN ? r : INT_MAX;
+  }
+  if (whole) {
+    // Every state leaves and R = M candidates (fewer only into a bank that held
+    // none) take the slots in order: no fill, no survivors, no holes.  The lists
+    // are written side by side instead of in runs per thread (12 banks of 4,680:
+    // 13.7 us by the general path).
+    for (int i = threadIdx.x; i < m; i += kBig) {
+      ws.ev_list[rb + i] = i;
+      ws.dest[rb + i] = -1;
+    }
+    for (int k = threadIdx.x; k < rs; k += kBig) ws.adm_dest[nb + k] = k;
+    if (whole == 2) {
+      for (int k = threadIdx.x; k < rs; k += kBig) ws.adm_list[nb + k] = k;
+    } else {
+      int ca = 0, n_adm;
+#pragma unroll
+      for (int u = 0; u < kPerN; ++u) ca += rk[u] < rs;
+      int pa = block_excl_scan(ca, &n_adm, tmp);
+#pragma unroll
+      for (int u = 0; u < kPerN; ++u)
+        if (rk[u] < rs) ws.adm_list[nb + pa++] = loN + u;
+    }
+    if (out.evicted)
+      for (int j = threadIdx.x; j < g.Mcap; j += kBig) out.evicted[rb + j] = j < m ? j : -1;
+    if (out.admitted) {
+      __syncthreads();
+      for (int j = threadIdx.x; j < N; j += kBig) out.admitted[nb + j] = j < rs ? ws.adm_list[nb + j] : -1;
+    }
+    if (threadIdx.x == 0) {
+      ws.n_ev[b] = m;
+      if (rs > 0 || m > 0) ws.crossed[0] = 1;
+      bank.occupancy[b] = rs;
+      if (out.n_evicted) out.n_evicted[b] = m;
+      if (out.n_admitted) out.n_admitted[b] = rs;
+    }
+    return;
   }
   // violators and candidates for the fill (four independent loads per round trip)
   int nv_local = 0;
-  // a bank replaced whole: e = m, every state leaves, and no first crossing was searched
   for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kBig) {
     int f[4];
 #pragma unroll
@@ -476,7 +536,7 @@ __global__ __launch_bounds__(kBig) void k_select(dkv_bank bank, Geom g, Workspac
     for (int u = 0; u < 4; ++u) {
       const int i = i0 + u * kBig;
       if (i < m) {
-        const bool v = !no_mandatory && !whole && f[u] <= rs;
+        const bool v = !no_mandatory && f[u] <= rs;
         st[i] = v ? ST_VIOL : ST_CAND;
         nv_local += v;
       }
@@ -794,9 +854,12 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
       if (kMfma) launch_gram_mfma(bank, seg, g, p, out, ws, s, approx ? kGramScoreApprox : kGramScore);
       else launch_gram_f32(bank, seg, g, p, out, ws, s, kF32Score);
     }
-    k_sort_chunks<<<dim3((unsigned)((g.N + kChunk - 1) / kChunk), (unsigned)g.B), kSortThreads, 0, s>>>(
-        g, ws, out.score_q, (p.flags & DKV_POLICY_SOURCE_ORDER) ? 1 : 0);
-    {
+    const int source_order = (p.flags & DKV_POLICY_SOURCE_ORDER) ? 1 : 0;
+    if (g.N <= kChunk) {
+      k_sort_chunks<true><<<dim3(1, (unsigned)g.B), kSortThreads, 0, s>>>(g, ws, out.score_q, out.order, source_order);
+    } else {
+      k_sort_chunks<false><<<dim3((unsigned)((g.N + kChunk - 1) / kChunk), (unsigned)g.B), kSortThreads, 0, s>>>(
+          g, ws, out.score_q, out.order, source_order);
       const dim3 grid((unsigned)((ws.npad + kBig - 1) / kBig), (unsigned)g.B);
       const int nch = ws.npad / kChunk;
       auto rank = nch <= 4 ? k_sort_rank<4> : (nch <= 8 ? k_sort_rank<8> : (nch <= 12 ? k_sort_rank<12> : k_sort_rank<kMaxChunks>));
