@@ -1177,9 +1177,11 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
 // reduced the other side over the lanes tile by tile took 45 more instructions.
 //
 // Block J (items [32 W J, 32 W (J + 1))) takes its own block (both orders, each
-// item's own sum only) and, in runs of kSymStages stages, the items after it.
+// item's own sum only) and, in runs of several stages, the items after it.
 // ---------------------------------------------------------------------------
-constexpr int kSymStages = 12;  // shorter runs pay the held rows' load more often, longer ones balance worse
+// Stages per run: shorter runs pay the held rows' load more often, longer ones
+// balance worse (sym_stages picks).
+constexpr int kSymLong = 12, kSymShort = 4;
 
 // Sum over the 16 lanes of each DPP row of the lane's 16 values: returns the row's sum of value lane % 16.
 __device__ __forceinline__ uint32_t row_transpose_sum(const uint32_t (&w)[16], int l) {
@@ -1194,37 +1196,38 @@ __device__ __forceinline__ uint32_t row_transpose_sum(const uint32_t (&w)[16], i
 }
 
 // Work items of n list items in blocks of 32 W: block J's runs over the items after
-// it, then every block's own.  A run spans S = kSymStages kSI / (32 W) blocks, so
+// it, then every block's own.  A run of st stages spans S = st kSI / (32 W) blocks, so
 // block J with k blocks after it has ceil(k / S) runs (a last block that is not
 // full leaves that as it is), and the items of the blocks with at most k blocks
 // after them are a closed form: no walk over the blocks per item (up to 74 dependent
 // scalar steps at 9,360 items).
+template <int W, int ST>
+constexpr int kSymBlocks = ST * kSI / (32 * W);
 template <int W>
-constexpr int kSymBlocks = kSymStages * kSI / (32 * W);
-template <int W>
-__host__ __device__ constexpr int sym_before(int k) {  // runs of the blocks with at most k blocks after them
-  constexpr int S = kSymBlocks<W>;
-  const int q = k / S, r = k % S;
-  return S * q * (q + 1) / 2 + r * (q + 1);
+__host__ __device__ constexpr int sym_before(int k, int st) {  // runs of the blocks with at most k blocks after them
+  static_assert(kSymShort * kSI % (32 * W) == 0 && kSymLong % kSymShort == 0, "runs of whole blocks");
+  constexpr int SL = kSymBlocks<W, kSymLong>, SS = kSymBlocks<W, kSymShort>;
+  const int S = st == kSymLong ? SL : SS, q = st == kSymLong ? k / SL : k / SS;  // divisions by constants
+  return S * q * (q + 1) / 2 + (k - S * q) * (q + 1);
 }
 template <int W>
-__host__ __device__ constexpr int sym_items(int n) {
+__host__ __device__ constexpr int sym_items(int n, int st) {
   const int nb = (n + 32 * W - 1) / (32 * W);
-  return nb + (nb > 0 ? sym_before<W>(nb - 1) : 0);
+  return nb + (nb > 0 ? sym_before<W>(nb - 1, st) : 0);
 }
 // Item -> block J and run (-1: the block's own).
 template <int W>
-__device__ __forceinline__ void sym_item(int n, int item, int &J, int &run) {
-  static_assert(kSymStages * kSI % (32 * W) == 0, "runs of whole blocks");
-  constexpr int S = kSymBlocks<W>;
-  const int nb = (n + 32 * W - 1) / (32 * W), off = sym_before<W>(nb - 1);
+__device__ __forceinline__ void sym_item(int n, int st, int item, int &J, int &run) {
+  constexpr int SL = kSymBlocks<W, kSymLong>, SS = kSymBlocks<W, kSymShort>;
+  const int S = st == kSymLong ? SL : SS;
+  const int nb = (n + 32 * W - 1) / (32 * W), off = sym_before<W>(nb - 1, st);
   if (item >= off) {
     J = item - off;
     run = -1;
     return;
   }
   // blocks with q S + 1 .. (q + 1) S blocks after them have q + 1 runs each
-  int q = (int)((__builtin_sqrtf(1.0f + 8.0f / S * (float)item) - 1.0f) * 0.5f);
+  int q = (int)((__builtin_sqrtf(1.0f + (st == kSymLong ? 8.0f / SL : 8.0f / SS) * (float)item) - 1.0f) * 0.5f);
   while (S * q * (q + 1) / 2 > item) --q;
   while (S * (q + 1) * (q + 2) / 2 <= item) ++q;
   const int t = item - S * q * (q + 1) / 2, u = t / (q + 1);
@@ -1232,13 +1235,24 @@ __device__ __forceinline__ void sym_item(int n, int item, int &J, int &run) {
   run = t - u * (q + 1);
 }
 
+// Stages per run of B symmetric Grams of up to n items: short runs where long ones
+// leave workgroup slots of the chip empty (32 banks x 999, d = 64: maintenance 512
+// long items on 768 slots, update 91 us; with short ones 75 us including 10 us of
+// the sort's).  Above a round the length matters little (12 x 4,680: 127 us with
+// 12 stages, 126 with 8; densities of 12 x 9,360: 380 and 390).
+template <int W>
+inline int sym_stages(uint64_t B, int n) {
+  const uint64_t items = B * (uint64_t)sym_items<W>(n, kSymLong), slots = W == kWaves ? 3 * 256 : 256;
+  return items >= slots ? kSymLong : kSymShort;
+}
+
 template <int D, int P, bool FOLD, bool KV, bool ADM>
 __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k, const void *seg_v, const Geom &g,
-                                         const Prm &p, const Workspace &ws, int n_items, int item, int b,
+                                         const Prm &p, const Workspace &ws, int n_items, int st, int item, int b,
                                          const StageBufs<D> &sb) {
   constexpr int W = gram_waves<D>();
   int J, run;
-  sym_item<W>(n_items, item, J, run);
+  sym_item<W>(n_items, st, item, J, run);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, h = l >> 5, n = l & 31;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   const Desc src = ADM ? Desc{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)}
@@ -1250,8 +1264,8 @@ __device__ __forceinline__ void sym_body(const dkv_bank &bank, const void *seg_k
   // streamed items [j0, j1)
   const bool diag = run < 0;
   const int hold0 = J * 32 * W;
-  const int j0 = diag ? hold0 : hold0 + 32 * W + run * kSymStages * kSI;
-  const int j1 = min(n_items, j0 + (diag ? 32 * W : kSymStages * kSI));
+  const int j0 = diag ? hold0 : hold0 + 32 * W + run * st * kSI;
+  const int j1 = min(n_items, j0 + (diag ? 32 * W : st * kSI));
   const int ncols = j1 - j0, ns = (ncols + kSI - 1) / kSI;
   // stage loads: a bank's slots in order take the per-lane offsets of consecutive
   // rows; list rows are fetched one stage ahead of their use
@@ -1454,7 +1468,7 @@ constexpr unsigned kItemWgs = 4096;
 // The maintenance Grams of every bank.
 template <int D, int P, bool FOLD, bool KV>
 __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_maint_mfma(
-    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws) {
+    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws, int st) {
   constexpr int W = gram_waves<D>(), kRpw = 32 * W;
   constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
   __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
@@ -1467,7 +1481,7 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
       g.B, pre,
       [&](int b) {
         const MaintItems it = maint_items(g, ws, b, kRpw);
-        return it.n_se + it.n_ab + sym_items<W>(it.rs);
+        return it.n_se + it.n_ab + sym_items<W>(it.rs, st);
       },
       [&](int b, int i) __attribute__((always_inline)) {
         const MaintItems it = maint_items(g, ws, b, kRpw);
@@ -1480,7 +1494,8 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
           rowsum_body<D, P, RS_ADM_BASE, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, j % it.rows_a, j / it.rows_a, b,
                                                    sb);
         } else {
-          sym_body<D, P, FOLD, KV, true>(bank, seg_k, seg_v, g, p, ws, it.rs, i - it.n_se - it.n_ab, b, sb);
+          sym_body<D, P, FOLD, KV, true>(bank, seg_k, seg_v, g, p, ws, it.rs, st, i - it.n_se - it.n_ab, b,
+                                          sb);
         }
       });
 }
@@ -1488,7 +1503,7 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
 // From-scratch densities of every bank (Eq. 3).
 template <int D, int P, bool FOLD, bool KV>
 __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_density_mfma(dkv_bank bank, Geom g,
-                                                                                                    Prm p, Workspace ws) {
+                                                                                                    Prm p, Workspace ws, int st) {
   constexpr int W = gram_waves<D>();
   constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
   __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
@@ -1497,10 +1512,10 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2)
   __shared__ int pre[65];
   const StageBufs<D> sb{k0, k1, k2, a0, a1, a2, cb};
   walk_items(
-      g.B, pre, [&](int b) { return sym_items<W>(ws.m[b]); },
+      g.B, pre, [&](int b) { return sym_items<W>(ws.m[b], st); },
       [&](int b, int i) __attribute__((always_inline)) {
         __syncthreads();  // the previous item's LDS stages are done with
-        sym_body<D, P, FOLD, KV, false>(bank, nullptr, nullptr, g, p, ws, ws.m[b], i, b, sb);
+        sym_body<D, P, FOLD, KV, false>(bank, nullptr, nullptr, g, p, ws, ws.m[b], st, i, b, sb);
       });
 }
 
@@ -2088,8 +2103,9 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
     case kGramMaint: {
       // at most this many items per bank, but for states that violated before the update
       const uint64_t y_ev = cdiv(g.N > 0 ? g.N : 1, kColsPerSplit), y_surv = cdiv(g.Mcap, kColsPerSplit);
-      const uint64_t items = rowsM * y_ev + (g.N > 0 ? rowsN : 0u) * (y_surv + 1 + cdiv(g.N, kSymStages * kSI));
-      k_maint_mfma<D, P, F, KV><<<grid_of(items * (unsigned)g.B, kItemWgs), T, 0, s>>>(bank, seg.k, sv, g, p, ws);
+      const int n_adm = g.N < g.Mcap ? g.N : g.Mcap, st = sym_stages<W>((unsigned)g.B, n_adm);
+      const uint64_t items = rowsM * y_ev + (g.N > 0 ? rowsN : 0u) * y_surv + sym_items<W>(n_adm, st);
+      k_maint_mfma<D, P, F, KV><<<grid_of(items * (unsigned)g.B, kItemWgs), T, 0, s>>>(bank, seg.k, sv, g, p, ws, st);
       break;
     }
     default:
@@ -2119,8 +2135,9 @@ void mfma_score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g
         bank, seg.k, seg.v, g, p, ws);
   }
   if (density) {
-    const uint64_t items = (uint64_t)cdiv(g.Mcap, 32 * W) * (1 + cdiv(g.Mcap, kSymStages * kSI)) * (unsigned)g.B;
-    k_density_mfma<D, P, F, KV><<<grid_of(items, kItemWgs), T, 0, s>>>(bank, g, p, ws);
+    const int st = sym_stages<W>((unsigned)g.B, g.Mcap);
+    const uint64_t items = (uint64_t)sym_items<W>(g.Mcap, st) * (unsigned)g.B;
+    k_density_mfma<D, P, F, KV><<<grid_of(items, kItemWgs), T, 0, s>>>(bank, g, p, ws, st);
   }
 }
 

@@ -126,3 +126,14 @@ def test_densities_at_run_edges(d, kv, m):
         W = torch.round(w.double() * 2.0 ** 23).long()
         W.fill_diagonal_(0)
         assert torch.equal(dens[b, :m].cpu(), W.sum(-1)), f"bank {b}"
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 256, 511, 512, 513, 1025, 2048, 2049])
+@pytest.mark.parametrize("source_order", [False, True])
+def test_order_at_sort_edges(n, source_order):
+    """The candidates' order and its committed update at the sizes where the sort changes its route or its
+    number of stages; the first block meets empty banks, so all its scores tie."""
+    _log(f"order n={n} source_order={source_order}")
+    cfg = synth.Config(heads=2, d=64, dtype="bf16", n_cand=n, budget=max(600, n), group_size=2, **SMALL)
+    flags = api.POLICY_SOURCE_ORDER if source_order else 0
+    _run_rollout(cfg, 2, api.Params(sigma2_log2=4, flags=flags), dup_every=1)
