@@ -85,7 +85,7 @@ __device__ int block_max(int v, int *tmp) {
 }
 
 // ---------------------------------------------------------------------------
-// k_begin: grid (1 + ceil(max(N, Mcap) / 256), B).  Workgroup 0 of a bank
+// k_begin: grid (1 + ceil(max(N, Mcap) / 512), B).  Workgroup 0 of a bank
 // clamps occupancy and budget, fixes the tested prefix R of its group (Eq. 11)
 // and the score exponent E, then writes the score scale of every live state
 // (Eq. 6); the other workgroups compute candidate norms, the column aug steps
@@ -103,49 +103,87 @@ __device__ int block_max(int v, int *tmp) {
 // allow: the largest value the requested outputs permit.
 // force: every state's first crossing is wanted.
 // ---------------------------------------------------------------------------
+// The candidate rows come through LDS, a wave's 64 rows in parts of 128 bytes: a
+// lane that read its own row from memory took 16 bytes of 64 different lines per
+// load.  Workgroup 0's chain of loads is what small calls wait for: the group's
+// budgets are read side by side, eight baselines per thread are in flight (12 banks
+// replaced whole: update 128.0 -> 125.5 us; scores and densities of 12 x 9,360 states
+// 388 -> 383 us).
+template <int DT>
+constexpr int kBeginThreads = DT == DKV_BF16 ? 512 : 256;  // (the small fp32 banks gain nothing from more)
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Squared norms of rows [row0, row0 + 64) of src (nrow of them, at least 1; D
+// bf16), one per lane, added to s in element order.  buf: 8 KB of the wave's own.
+template <int D>
+__device__ __forceinline__ void add_row_norms(const uint16_t *src, int nrow, char *buf, float &s) {
+  const int l = threadIdx.x & 63;
+  constexpr int kAllDone = 7 << 4;  // s_waitcnt: no vector-memory and no LDS operation outstanding
+  for (int part = 0; part < D / 64; ++part) {
+    const uint16_t *base = src + 64 * part;
+    // the buffer ends with the last row, so rows past it read as zero; row r's 16-byte chunk c lies at chunk c ^ (r % 8)
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), (short)0,
+                                                                        ((nrow - 1) * D + 64) * 2, 0x00020000);
+    __builtin_amdgcn_s_waitcnt(kAllDone);  // the reads of the part before
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int r = 8 * q + (l >> 3);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(buf + 1024 * q), 16, r * D * 2 + 16 * ((l & 7) ^ (r & 7)),
+                                               0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(kAllDone);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(buf + 128 * l + 16 * (c ^ (l & 7)));
+      const uint32_t w4[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float lo = __uint_as_float(w4[e] << 16), hi = __uint_as_float(w4[e] & 0xFFFF0000u);
+        s = __builtin_fmaf(lo, lo, s);
+        s = __builtin_fmaf(hi, hi, s);
+      }
+    }
+  }
+}
+
 template <int D, int DT>
-__global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g,
-                                                    Workspace ws, float inv_s2, int norms, int allow, int force) {
+__global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g,
+                                                         Workspace ws, float inv_s2, int norms, int allow, int force) {
   const int b = blockIdx.y;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   if (blockIdx.x > 0) {
-    const int j = (blockIdx.x - 1) * kThreads + threadIdx.x;
-    if (j < g.N) {
-      if (norms) {
-        // |k|^2 (then + |v|^2 for the [K; V] geometry) in element order, 16-byte loads
-        float s = 0.0f;
-        if constexpr (DT == DKV_BF16) {
-          for (int part = 0; part < (seg_v ? 2 : 1); ++part) {
-            const uint4 *src =
-                reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(part ? seg_v : seg_k) + (nb + j) * D);
-            uint4 x[D / 8];
-#pragma unroll
-            for (int q = 0; q < D / 8; ++q) x[q] = src[q];
-#pragma unroll
-            for (int q = 0; q < D / 8; ++q) {
-              const uint32_t w4[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float lo = __uint_as_float(w4[e] << 16), hi = __uint_as_float(w4[e] & 0xFFFF0000u);
-                s = __builtin_fmaf(lo, lo, s);
-                s = __builtin_fmaf(hi, hi, s);
-              }
-            }
-          }
-        } else {
-          const float4 *src = reinterpret_cast<const float4 *>(static_cast<const float *>(seg_k) + (nb + j) * D);
-#pragma unroll 8
-          for (int q = 0; q < D / 4; ++q) {
-            const float4 x = src[q];
-            s = __builtin_fmaf(x.x, x.x, s);
-            s = __builtin_fmaf(x.y, x.y, s);
-            s = __builtin_fmaf(x.z, x.z, s);
-            s = __builtin_fmaf(x.w, x.w, s);
-          }
+    const int j0 = (blockIdx.x - 1) * kBeginThreads<DT>, j = j0 + threadIdx.x;
+    if (norms) {
+      float s = 0.0f;
+      if constexpr (DT == DKV_BF16) {
+        // |k|^2 (then + |v|^2 for the [K; V] geometry) in element order
+        __shared__ __attribute__((aligned(16))) char rows[kBeginThreads<DT> / 64][8192];
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r0 = j0 + 64 * wave;
+        if (r0 < g.N) {
+          add_row_norms<D>(static_cast<const uint16_t *>(seg_k) + (nb + r0) * D, min(64, g.N - r0), rows[wave], s);
+          if (seg_v)
+            add_row_norms<D>(static_cast<const uint16_t *>(seg_v) + (nb + r0) * D, min(64, g.N - r0), rows[wave], s);
         }
+      } else if (j < g.N) {
+        const float4 *src = reinterpret_cast<const float4 *>(static_cast<const float *>(seg_k) + (nb + j) * D);
+#pragma unroll 8
+        for (int q = 0; q < D / 4; ++q) {
+          const float4 x = src[q];
+          s = __builtin_fmaf(x.x, x.x, s);
+          s = __builtin_fmaf(x.y, x.y, s);
+          s = __builtin_fmaf(x.z, x.z, s);
+          s = __builtin_fmaf(x.w, x.w, s);
+        }
+      }
+      if (j < g.N) {
         ws.cnorm[nb + j] = s;
         ws.caug[nb + j] = column_aug(s, inv_s2);
       }
+    }
+    if (j < g.N) {
       ws.acol[nb + j] = 0;
       ws.sub_adm[nb + j] = 0;
       ws.mut_adm[nb + j] = 0;
@@ -161,31 +199,37 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
   }
   const int Mb = clampi(bank.budget[b], 0, g.Mcap);
   const int m = clampi(bank.occupancy[b], 0, Mb);
-  // Tested prefix lengths 0..R: R = min(N, every budget of the group).
+  // Tested prefix lengths 0..R: R = min(N, every budget of the group).  Each wave
+  // reads the group's budgets and occupancies, one bank per lane (where a few
+  // lanes hold banks, the minimum is read from them instead of reduced).
   int R = g.N;
-  const int g0 = (b / g.gs) * g.gs;
-  for (int j = 0; j < g.gs; ++j) R = min(R, clampi(bank.budget[g0 + j], 0, g.Mcap));
-  int whole = allow;
-  for (int j = 0; j < g.gs; ++j) {
-    const int Mj = clampi(bank.budget[g0 + j], 0, g.Mcap);
-    if (R != Mj && clampi(bank.occupancy[g0 + j], 0, Mj) > 0) whole = 0;
+  const int g0 = (b / g.gs) * g.gs, lane = threadIdx.x & 63;
+  for (int j = lane; j < g.gs; j += 64) R = min(R, clampi(bank.budget[g0 + j], 0, g.Mcap));
+  if (g.gs <= 4) {
+    R = min(min(__builtin_amdgcn_readlane(R, 0), __builtin_amdgcn_readlane(R, 1)),
+            min(__builtin_amdgcn_readlane(R, 2), __builtin_amdgcn_readlane(R, 3)));
+  } else {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) R = min(R, __shfl_xor(R, o, 64));
   }
+  bool some = false;  // a bank of the group that holds states is not replaced whole
+  for (int j = lane; j < g.gs; j += 64) {
+    const int Mj = clampi(bank.budget[g0 + j], 0, g.Mcap);
+    some |= R != Mj && clampi(bank.occupancy[g0 + j], 0, Mj) > 0;
+  }
+  int whole = __any(some) ? 0 : allow;
   if (whole > 1 && R < g.N) whole = 1;
   // Score scale exponent E: binary exponent of max_i fp32(2^23 / b_i), i.e. of
   // the value at the smallest baseline (the division and rounding are monotone).
-  __shared__ long long redb[kThreads / 64];
+  __shared__ long long redb[kBeginThreads<DT> / 64];
+  constexpr int kU = 8;  // independent loads per round trip
   long long mn = LLONG_MAX;
-  // four independent loads per round trip
-  for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kThreads) {
-    long long bq[4];
+  for (int i0 = threadIdx.x; i0 < m; i0 += kU * kBeginThreads<DT>) {
+    long long bq[kU];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * kThreads;
-      const long long bv = bank.base[rb + min(i, m - 1)];  // clamped, unconditional
-      bq[u] = i < m ? bv : LLONG_MAX;
-    }
+    for (int u = 0; u < kU; ++u) bq[u] = bank.base[rb + min(i0 + u * kBeginThreads<DT>, m - 1)];  // clamped, unconditional
 #pragma unroll
-    for (int u = 0; u < 4; ++u) mn = bq[u] < mn ? bq[u] : mn;
+    for (int u = 0; u < kU; ++u) mn = bq[u] < mn ? bq[u] : mn;  // (a state read twice changes no minimum)
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -194,22 +238,20 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
   }
   if ((threadIdx.x & 63) == 0) redb[threadIdx.x >> 6] = mn;
   __syncthreads();
-  for (int w = 0; w < kThreads / 64; ++w) mn = redb[w] < mn ? redb[w] : mn;
+#pragma unroll
+  for (int w = 0; w < kBeginThreads<DT> / 64; ++w) mn = redb[w] < mn ? redb[w] : mn;
   int E = 0;
   if (m > 0) {
     const long long bi = mn < 1 ? 1 : mn;
     frexpf((float)(8388608.0 / (double)bi), &E);
   }
-  for (int i0 = threadIdx.x; i0 < m; i0 += 4 * kThreads) {
-    long long bq[4];
+  for (int i0 = threadIdx.x; i0 < m; i0 += kU * kBeginThreads<DT>) {
+    long long bq[kU];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * kThreads;
-      bq[u] = bank.base[rb + min(i, m - 1)];  // clamped, unconditional
-    }
+    for (int u = 0; u < kU; ++u) bq[u] = bank.base[rb + min(i0 + u * kBeginThreads<DT>, m - 1)];  // clamped, unconditional
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * kThreads;
+    for (int u = 0; u < kU; ++u) {
+      const int i = i0 + u * kBeginThreads<DT>;
       if (i < m) ws.bs[rb + i] = score_scale(bq[u], E);
     }
   }
@@ -227,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void k_begin(dkv_bank bank, const void *s
       ws.more[b / g.gs] = whole ? 0 : (R <= kCrossFirst ? kMoreOpen - 1 : (force ? kMoreForced : kMoreOpen));
       ws.r_star[b / g.gs] = 0;
     }
-    for (int w = threadIdx.x; w < ws.nfw; w += kThreads) ws.feas[(size_t)b * ws.nfw + w] = ~0u;
+    for (int w = threadIdx.x; w < ws.nfw; w += kBeginThreads<DT>) ws.feas[(size_t)b * ws.nfw + w] = ~0u;
   }
 }
 
@@ -237,7 +279,7 @@ void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, c
   const int span = g.N > g.Mcap ? g.N : g.Mcap;
   // [K; V] geometry: candidate norms over the concatenated key-value rows
   const void *seg_v = (p.flags & DKV_POLICY_KV_DESCRIPTOR) ? seg.v : nullptr;
-  k_begin<D, DT><<<dim3((unsigned)(1 + (span + kThreads - 1) / kThreads), (unsigned)g.B), kThreads, 0, s>>>(
+  k_begin<D, DT><<<dim3((unsigned)(1 + (span + kBeginThreads<DT> - 1) / kBeginThreads<DT>), (unsigned)g.B), kBeginThreads<DT>, 0, s>>>(
       bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole, force);
 }
 
