@@ -1920,24 +1920,26 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
       const f32x16 x0 = tile_mfma<D>(kbuf[buf], abuf[buf], 0, rf, aoff);
       const f32x16 x1 = tile_mfma<D>(kbuf[buf], abuf[buf], 1, rf, aoff);
       // weights in candidate order inside the lane: tile tl, register 4 k + j is
-      // candidate 32 tl + 8 k + 4 hw + j of the chunk; candidates past R weigh nothing
+      // candidate 32 tl + 8 k + 4 hw + j of the chunk; candidates past R weigh
+      // nothing.  The weights stay raw (each with kMagic, taken off their sums), and
+      // only a chunk that R cuts is masked: 6 instead of 9 instructions per weight.
       const int nvalid = min(kCkStride, R - c * kCkStride);
       uint32_t w[2][16], gsum[2][4];
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
+      for (int tl = 0; tl < 2; ++tl)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          gsum[tl][k] = 0;
+        for (int i = 0; i < 16; ++i) w[tl][i] = weight_raw<P, FOLD>(tl ? x1[i] : x0[i], 8388608.0f);
+      if (nvalid < kCkStride) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            uint32_t W = weight_raw<P, FOLD>(tl ? x1[4 * k + j] : x0[4 * k + j], 8388608.0f) - kMagic;
-            asm volatile("" : "+v"(W));  // computed for every lane, then masked
-            W = 32 * tl + 8 * k + 4 * hw + j < nvalid ? W : 0u;
-            w[tl][4 * k + j] = W;
-            gsum[tl][k] += W;
-          }
-        }
+        for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) w[tl][i] = 32 * tl + col_of_reg(i, hw) < nvalid ? w[tl][i] : kMagic;
       }
+#pragma unroll
+      for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          gsum[tl][k] = w[tl][4 * k] + w[tl][4 * k + 1] + w[tl][4 * k + 2] + w[tl][4 * k + 3] - 4u * kMagic;
       uint32_t lane_tot = 0;
 #pragma unroll
       for (int tl = 0; tl < 2; ++tl)
@@ -1959,7 +1961,7 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
             uint32_t q = pr + (hw ? other : 0u);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              q += w[tl][4 * k + j];
+              q += w[tl][4 * k + j] - kMagic;
               cnt += q <= nd1 ? 1u : 0u;
             }
             pr += gsum[tl][k] + other;
