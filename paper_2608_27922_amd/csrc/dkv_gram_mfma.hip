@@ -4,13 +4,13 @@
 // of "row" items against a stream of "column" items and reduces them per row:
 //
 //   k_score_mfma       rows = candidates, columns = bank states:
-//                      S_x = sum_i RNE(w_ix bs_i), Wcol_x = sum_i W_ix  (Eq. 6)
+//                      S_x = sum_i RNE(w_ix bs_i)  (Eq. 6)
 //   k_first_part_mfma  per bank state, over the first 256 ordered candidates:
 //                      64-candidate chunk sums (the prefix checkpoints of
 //                      Eqs. 8-9) and the first prefix that reaches tau b
 //   k_chunk_part_mfma  the chunk sums of the rest of the order, and
 //   k_cross_mfma       the whole crossing search, for the groups that the first
-//                      part leaves open (k_cross_plan, Eqs. 9-11)
+//                      part leaves open (Eqs. 9-11)
 //   k_rowsum_mfma      row sums: the r* fix-up
 //   k_maint_mfma       the exact maintenance (Supp. C): row sums, and the symmetric
 //                      Gram of the admitted candidates

@@ -3,20 +3,22 @@
 // One update of every bank from one block (Supp. C, Algorithm 1) is the kernel
 // sequence below, all on the caller's stream, with r* kept on the device.  The
 // Gram stages of bf16 banks run on MFMA (dkv_gram_mfma.hip: k_score_mfma,
-// k_gather_sorted, k_first_part_mfma, k_cross_plan, k_chunk_part_mfma,
-// k_cross_mfma, k_rowsum_mfma, k_maint_mfma); fp32 banks use
+// k_order_mark, k_rescore, k_order_fix, k_first_part_mfma, k_gather_sorted,
+// k_chunk_part_mfma, k_cross_mfma, k_rowsum_mfma, k_maint_mfma); fp32 banks use
 // dkv_gram_f32.hip.
 //
 //   k_begin         clamp occupancy/budget, tested prefix R of the group (Eq. 11),
 //                   score scale 1/b of every bank state (Eq. 6), |k_x|^2 of
 //                   every candidate, norm steps, cleared accumulators
-//   score           S_x = sum_i RNE(w_ix / b_i scaled) and Wcol_x = sum_i W_ix (Eq. 6)
-//   k_sort_chunks   stable ascending order of S_x, ties by source index (Alg. 1):
-//   k_sort_rank     512-key chunks sorted in LDS, then ranked by search
+//   score           S_x = sum_i RNE(w_ix / b_i scaled) (Eq. 6)
+//   k_order_count   stable ascending order of S_x, ties by source index (Alg. 1):
+//                   ranks counted in one launch, or for more candidates
+//   k_sort_chunks   512-key chunks sorted in LDS, then
+//   k_sort_rank     ranked by search
 //   crossing        prefix sums over the ordered candidates (64-candidate
 //                   chunk sums), first violating prefix of every bank state (Eqs. 8-9)
-//   k_feas_bank     c_r for every r and the flags c_r <= e_r (Eqs. 9-10)
-//   k_feas_group    r* of each group (Eq. 11)
+//   k_feas          c_r for every r, the flags c_r <= e_r (Eqs. 9-10), and r* of
+//                   each group (Eq. 11)
 //   fix-up          projected density rho~(r*) of every bank state
 //   k_select        mandatory + densest eviction (Sec. 3.4 step 3), commit plan
 //   maintenance     weights to the evicted and to the co-admitted states (Supp. C)

@@ -137,3 +137,43 @@ def test_order_at_sort_edges(n, source_order):
     cfg = synth.Config(heads=2, d=64, dtype="bf16", n_cand=n, budget=max(600, n), group_size=2, **SMALL)
     flags = api.POLICY_SOURCE_ORDER if source_order else 0
     _run_rollout(cfg, 2, api.Params(sigma2_log2=4, flags=flags), dup_every=1)
+
+
+@pytest.mark.parametrize("kv,B,gs,n,budgets", [
+    (False, 8, 4, 8191, (300, 700, 300, 300)),   # unequal budgets: the general search up to R = 300
+    (False, 8, 2, 8191, (300, 300)),             # replaced whole: the order matters across position 300 only
+    (False, 64, 2, 1000, (1400, 1500)),          # growing, then at its budget: every order position may matter
+    (True, 64, 2, 1000, (1400, 1500)),
+])
+def test_approximate_scores_give_the_exact_order(kv, B, gs, n, budgets):
+    """Calls of at least 2e9 pairs (by capacity) that ask for no scores order their candidates by approximate
+    ones; asking for them takes the exact route.  Same decisions and banks, with duplicated and nearly
+    duplicated candidates so that many neighbours in the order are closer than the error bound."""
+    _log(f"approximate scores kv={kv} B={B} n={n} budgets={budgets}")
+    d, cap = 64, 32767
+    assert B * cap * n >= 2e9
+    prm = api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0)
+    bud = torch.tensor([budgets[b % gs] for b in range(B)], dtype=torch.int32)
+    banks = [api.Bank(B, cap, d, group_size=gs, budget=bud) for _ in range(2)]
+    g = torch.Generator(device="cuda").manual_seed(n + B)
+    for t in range(4):
+        centres = torch.randn(B, 16, d, generator=g, device="cuda") / d ** 0.5
+        pick = torch.randint(0, 16, (B, n, 1), generator=g, device="cuda").expand(B, n, d)
+        k = torch.gather(centres, 1, pick) + 0.1 * torch.randn(B, n, d, generator=g, device="cuda")
+        k = (torch.clamp(torch.round(k * 64), -127, 127) / 64)
+        k[:, 1::2] = k[:, 0::2][:, : n // 2]                     # exact ties ...
+        k[:, 3::4, 0] = torch.clamp(k[:, 3::4, 0] + 1 / 64, -1.9, 1.9)  # ... half of them moved by one grid step
+        k = (torch.round(k * 64) / 64).to(torch.bfloat16).contiguous()
+        v = (torch.round(torch.randn(B, n, d, generator=g, device="cuda") * 16) / 64).to(torch.bfloat16)
+        outs = [api.UpdateOut(banks[i], n, trace=i == 1) for i in range(2)]
+        for i in range(2):
+            api.update_bank(banks[i], k, v, t, prm, out=outs[i])
+        assert torch.equal(outs[0].r_star, outs[1].r_star), f"block {t}"
+        for name in ("admitted", "evicted"):
+            assert torch.equal(getattr(outs[0], name), getattr(outs[1], name)), f"block {t} {name}"
+        assert torch.equal(banks[0].occupancy, banks[1].occupancy)
+        m = int(banks[0].occupancy.max())
+        live = torch.arange(m, device="cuda")[None] < banks[0].occupancy[:, None]
+        for name in ("k", "v", "knorm", "rho", "base", "prov"):
+            x, y = (getattr(bk, name)[:, :m][live] for bk in banks)
+            assert torch.equal(x, y), f"block {t} {name}"
