@@ -452,7 +452,9 @@ __device__ void block_inclusive_scan_lds(int *a, int n, int *tmp) {
 // the group's mask.  The group's last bank to arrive (counted in r_star, which
 // k_begin cleared) then takes r* = the largest r feasible for every bank
 // (Eq. 11) and every bank's e_{r*}.  Masks and count go through device-scope
-// atomics; the count's release / acquire orders them.
+// atomics.  The count's release waits for its own wave's memory operations only,
+// and the workgroup barrier waits for none: each wave takes its ANDs' results, so
+// that they are done when it reaches the barrier, before the count.
 __global__ __launch_bounds__(kBig) void k_feas(Geom g, Workspace ws, int32_t *out_rstar) {
   const int b = blockIdx.x, grp = b / g.gs, b0 = grp * g.gs;
   __shared__ int hist[kSortMax + 1];
@@ -485,14 +487,16 @@ __global__ __launch_bounds__(kBig) void k_feas(Geom g, Workspace ws, int32_t *ou
   // one wave per 64 values of r: the flags by ballot, two mask words per wave
   uint32_t *f = ws.feas + (size_t)b0 * ws.nfw;
   const int lane = threadIdx.x & 63;
+  uint32_t seen = 0;
   for (int w2 = threadIdx.x >> 6; 2 * w2 < ws.nfw; w2 += kBig / 64) {
     const int r = 64 * w2 + lane;
     const bool ok = r <= R && hist[r <= R ? r : 0] <= max(0, m + r - M);
     const unsigned long long bits = __ballot(ok);
     const uint32_t word = lane == 0 ? (uint32_t)bits : (uint32_t)(bits >> 32);
     if (lane < 2 && 2 * w2 + lane < ws.nfw)
-      __hip_atomic_fetch_and(&f[2 * w2 + lane], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      seen |= __hip_atomic_fetch_and(&f[2 * w2 + lane], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  asm volatile("" ::"v"(seen) : "memory");  // every AND of this wave has returned
   __syncthreads();
   if (threadIdx.x == 0)
     last = __hip_atomic_fetch_add(&ws.r_star[grp], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == g.gs - 1;
