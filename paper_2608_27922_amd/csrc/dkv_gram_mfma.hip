@@ -478,8 +478,10 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
       if constexpr (P >= 2) tp = tt * tt;
       if constexpr (P == 4) tp = tp * tp;
       if constexpr (APPROX) {
-        const float y = clamp_weight(__builtin_amdgcn_rcpf(tp));
-        fa[i & 1] = __builtin_fmaf(!MASK || col_of_reg(i, h) < nvalid ? y : 0.0f, bsv[i], fa[i & 1]);
+        const float f = __builtin_fmaf(clamp_weight(__builtin_amdgcn_rcpf(tp)), bsv[i], fa[i & 1]);
+        // the sum is selected, not the weight: the scales past the last live state are whatever the workspace
+        // held, and 0 times an infinity or a NaN is a NaN
+        fa[i & 1] = !MASK || col_of_reg(i, h) < nvalid ? f : fa[i & 1];
       } else {
         const float w = clamp_weight(rcp_rn(tp));
         uint32_t ra = __float_as_uint(__builtin_fmaf(w, bsv[i], 8388608.0f));

@@ -13,8 +13,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2608_27922_amd import api, synth  # noqa: E402
-from gpu_util import TORCH_DT, attention_error, dev, host  # noqa: E402
-from oracle import attention  # noqa: E402
+from gpu_util import (TORCH_DT, assert_bank_equal, attention_error, dev, host, oracle_params,  # noqa: E402
+                      oracle_step)
+from oracle import BankState, attention  # noqa: E402
 from test_gpu_parity import POLICY_FLAGS, SMALL, _log, _run_rollout  # noqa: E402
 
 
@@ -177,3 +178,54 @@ def test_approximate_scores_give_the_exact_order(kv, B, gs, n, budgets):
         for name in ("k", "v", "knorm", "rho", "base", "prov"):
             x, y = (getattr(bk, name)[:, :m][live] for bk in banks)
             assert torch.equal(x, y), f"block {t} {name}"
+
+
+def _against_oracle(B, cap, d, gs, budgets, blocks, prm, stale=False):
+    """Updates without the order or the scores among their outputs against the oracle.  blocks(t, obanks):
+    [B, n, d] float32 keys and values of block t.  stale: unused bank slots and the workspace hold NaNs."""
+    bud = np.array([budgets[b % gs] for b in range(B)], np.int32)
+    bank = api.Bank(B, cap, d, group_size=gs, budget=torch.from_numpy(bud))
+    if stale:
+        for x in (bank.k, bank.v, bank.knorm):
+            x.fill_(float("nan"))
+    obanks = [BankState.empty(int(x), d) for x in bud]
+    t = 0
+    while (kv := blocks(t, obanks)) is not None:
+        K, V = kv
+        n = K.shape[1]
+        out, ws = api.UpdateOut(bank, n), api.alloc_workspace(bank, n, prm.flags)
+        if stale:
+            ws.fill_(255)
+        api.update_bank(bank, dev(K, "bf16"), dev(V, "bf16"), t, prm, workspace=ws, out=out)
+        obanks, recs = oracle_step(obanks, K, V, t, oracle_params(prm), gs)
+        for g, rec in enumerate(recs):
+            assert int(out.r_star[g]) == rec.r_star, f"block {t} group {g}"
+            for j, hr in enumerate(rec.heads):
+                b = g * gs + j
+                for name, ref in (("admitted", hr.admitted), ("evicted", hr.evicted)):
+                    got = getattr(out, name)[b].cpu().numpy()
+                    assert np.array_equal(got[got >= 0], ref), f"block {t} bank {b}: {name}"
+        for b in range(B):
+            assert_bank_equal(bank, b, obanks[b], ctx=f"block {t}", kv=bool(prm.flags & api.POLICY_KV_DESCRIPTOR))
+        t += 1
+
+
+@pytest.mark.parametrize("d,kv", [(64, False), (128, False), (64, True)])
+@pytest.mark.parametrize("gs,budgets", [(1, (300,)), (2, (300, 415))])
+def test_approximate_scores_read_no_stale_scale(d, kv, gs, budgets):
+    """Approximate scores (calls of at least 2e9 pairs by capacity) where the banks end inside a tile of 32 states
+    and what lies behind them, in the bank and in the workspace, is NaN."""
+    _log(f"stale workspace d={d} kv={kv} budgets={budgets}")
+    B, cap, n = 8, 32767, 8191
+    rng = np.random.default_rng(d + gs)
+    centres = rng.standard_normal((B, 12, d)) / d ** 0.5
+
+    def blocks(t, obanks):
+        if t == 3:
+            return None
+        x = centres[np.arange(B)[:, None], rng.integers(0, 12, (B, n))] + 0.1 * rng.standard_normal((B, n, d))
+        return [(np.clip(np.rint(y * 64), -127, 127) / 64).astype(np.float32)
+                for y in (x, rng.standard_normal((B, n, d)))]
+
+    _against_oracle(B, cap, d, gs, budgets, blocks,
+                    api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0), stale=True)
