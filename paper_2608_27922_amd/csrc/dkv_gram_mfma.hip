@@ -1845,7 +1845,8 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_cross_mfma(dk
 // only).  ws.found counts a bank's crossings per chunk, on a line of its own:
 // once they decide it after c chunks, workgroups of the bank that start later
 // stop there and add nothing, and ws.more of the group drops to c, so that the
-// second part leaves it out (unless every state's first crossing is wanted).
+// second part leaves it out; unless every state's first crossing is wanted, when
+// every workgroup walks all the chunks.
 // (One counter line for all groups made its atomics and loads wait in turn: 1.4 ms.)
 // Bound by the bank rows' reads where one chunk decides (360 banks of 9,280
 // states at their growth bound: 547 us with four chunks, 535 with one; a workgroup's
@@ -1870,7 +1871,9 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
     }
     return c + 1;
   };
-  const bool count = g.N > kCrossFirst && ws.more[b / g.gs] != kMoreForced;
+  // with every state's first crossing wanted, nothing is counted: no workgroup stops early, whatever R is, and
+  // `more` stays as k_begin left it
+  const bool count = g.N > kCrossFirst && !out_first;
   uint64_t *found = ws.found + (size_t)b * kFoundStride;
   // as known when the workgroup starts (the same for all its waves)
   __shared__ int limit;

@@ -16,7 +16,6 @@ constexpr int kSortMax = 8192;               // padded sort size (N <= 8191)
 constexpr int kCrossFirst = 256;             // ordered candidates in the first part of the crossing search (whole chunks)
 constexpr int kFoundStride = 16;             // one 128-byte line per bank
 constexpr int kMoreOpen = kCrossFirst / kCkStride + 1;  // more: the whole order
-constexpr int kMoreForced = kMoreOpen + 1;              // more: the whole order for every state (first crossings wanted)
 
 // ---------------------------------------------------------------------------
 // Workspace: one carve of the caller's buffer, every array 256-byte aligned.

@@ -103,7 +103,6 @@ __device__ int block_max(int v, int *tmp) {
 // to one block.  Such a one-layer update (12 banks, budget = block = 4,680)
 // took 432 us with the score, the sort keys and the whole crossing search.
 // allow: the largest value the requested outputs permit.
-// force: every state's first crossing is wanted.
 // ---------------------------------------------------------------------------
 // The candidate rows come through LDS, a wave's 64 rows in parts of 128 bytes: a
 // lane that read its own row from memory took 16 bytes of 64 different lines per
@@ -153,7 +152,7 @@ __device__ __forceinline__ void add_row_norms(const uint16_t *src, int nrow, cha
 
 template <int D, int DT>
 __global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g,
-                                                         Workspace ws, float inv_s2, int norms, int allow, int force) {
+                                                         Workspace ws, float inv_s2, int norms, int allow) {
   const int b = blockIdx.y;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   if (blockIdx.x > 0) {
@@ -268,7 +267,7 @@ __global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, cons
   }
   if (b == g0) {  // the group's: whether the crossing search may go on past its first part, and k_feas's state
     if (threadIdx.x == 0) {
-      ws.more[b / g.gs] = whole ? 0 : (R <= kCrossFirst ? kMoreOpen - 1 : (force ? kMoreForced : kMoreOpen));
+      ws.more[b / g.gs] = whole ? 0 : (R <= kCrossFirst ? kMoreOpen - 1 : kMoreOpen);
       ws.r_star[b / g.gs] = 0;
     }
     for (int w = threadIdx.x; w < ws.nfw; w += kBeginThreads<DT>) ws.feas[(size_t)b * ws.nfw + w] = ~0u;
@@ -277,12 +276,12 @@ __global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, cons
 
 template <int D, int DT>
 void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p, const Workspace &ws,
-                  bool norms, int allow_whole, int force, hipStream_t s) {
+                  bool norms, int allow_whole, hipStream_t s) {
   const int span = g.N > g.Mcap ? g.N : g.Mcap;
   // [K; V] geometry: candidate norms over the concatenated key-value rows
   const void *seg_v = (p.flags & DKV_POLICY_KV_DESCRIPTOR) ? seg.v : nullptr;
   k_begin<D, DT><<<dim3((unsigned)(1 + (span + kBeginThreads<DT> - 1) / kBeginThreads<DT>), (unsigned)g.B), kBeginThreads<DT>, 0, s>>>(
-      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole, force);
+      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole);
 }
 
 // ---------------------------------------------------------------------------
@@ -922,7 +921,7 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   // (by capacity) these cost as much as they save.
   const bool approx = kMfma && !seq && !(p.flags & DKV_POLICY_SOURCE_ORDER) && !out.order && !out.score_q &&
                       (double)g.B * g.Mcap * g.N >= kApproxPairs;
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, out.first_cross ? 1 : 0, s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, s);
   if (g.N > 0) {
     // in source order the scores are only reported
     if (!(p.flags & DKV_POLICY_SOURCE_ORDER) || out.score_q) {
@@ -975,7 +974,7 @@ template <int D, int DT>
 hipError_t score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws,
                       hipStream_t s) {
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, 0, s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, s);
   const bool scores = g.N > 0 && (score_q || score_f);
   if constexpr (DT == DKV_BF16) {
     launch_score_mfma(bank, seg, g, p, scores ? score_q : nullptr, scores ? score_f : nullptr, density, ws, s);

@@ -13,8 +13,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 from paper_2608_27922_amd import api, synth  # noqa: E402
-from gpu_util import (TORCH_DT, assert_bank_equal, attention_error, dev, host, oracle_params,  # noqa: E402
-                      oracle_step)
+from gpu_util import (TORCH_DT, assert_bank_equal, assert_trace_equal, attention_error, dev, host,  # noqa: E402
+                      oracle_params, oracle_step)
 from oracle import BankState, attention  # noqa: E402
 from test_gpu_parity import POLICY_FLAGS, SMALL, _log, _run_rollout  # noqa: E402
 
@@ -229,3 +229,38 @@ def test_approximate_scores_read_no_stale_scale(d, kv, gs, budgets):
 
     _against_oracle(B, cap, d, gs, budgets, blocks,
                     api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0), stale=True)
+
+
+def test_first_crossings_within_short_prefixes():
+    """First crossings wanted, more than 256 candidates, R <= 256 (a small bank in each group) and banks whose
+    crossings rule r* out at once: states of workgroups that start after that was known (2,000 workgroups of 128
+    states, more than the chip holds at a time) get theirs as well."""
+    _log("first crossings of short prefixes")
+    G, m, d, n, R = 12, 20001, 64, 300, 200
+    rng = np.random.default_rng(5)
+    grid = lambda *s: (np.clip(np.rint(rng.standard_normal(s) * 8), -127, 127) / 64).astype(np.float32)
+    prm = api.Params(sigma2_log2=5)
+    budgets = np.tile(np.array([R, m + 300], np.int32), G)  # E = max(0, m + R - M) = 0: one crossing decides a bank
+    bank = api.Bank(2 * G, m + 300, d, group_size=2, budget=torch.from_numpy(budgets))
+    base = rng.integers(1 << 30, 1 << 31, (G, m))
+    rho = 2 * base - rng.integers(1, 220 << 23, (G, m))      # spread over the first 256 candidates and past them
+    prov = np.broadcast_to(np.arange(m, dtype=np.int64), (G, m))
+    K, V = grid(G, m, d), grid(G, m, d)
+    obanks = [BankState.empty(R, d) for _ in range(2 * G)]
+    for i in range(G):
+        obanks[2 * i + 1] = BankState(budget=m + 300, K=K[i].astype(np.float64), V=V[i], rho=rho[i], base=base[i],
+                                      prov=prov[i])
+    bank.k[1::2, :m], bank.v[1::2, :m] = dev(K, "bf16"), dev(V, "bf16")
+    bank.knorm[1::2, :m] = torch.from_numpy((K.astype(np.float64) ** 2).sum(-1).astype(np.float32)).cuda()
+    for name, x in (("rho", rho), ("base", base), ("prov", prov)):
+        getattr(bank, name)[1::2, :m] = torch.from_numpy(x.copy()).cuda()
+    bank.occupancy[1::2] = m
+    sk, sv = grid(2 * G, n, d), grid(2 * G, n, d)
+    out = api.UpdateOut(bank, n, trace=True)
+    api.update_bank(bank, dev(sk, "bf16"), dev(sv, "bf16"), 1, prm, out=out)
+    new, recs = oracle_step(obanks, sk, sv, 1, oracle_params(prm), 2)
+    first = np.concatenate([r.heads[1].first_cross for r in recs])
+    assert len(np.unique((first[first <= R] + 63) // 64)) == 4  # crossings in every chunk of the prefix
+    assert_trace_equal(out, recs, 2, obanks, n)
+    for b in range(2 * G):
+        assert_bank_equal(bank, b, new[b])
