@@ -413,7 +413,7 @@ constexpr int kColsPerSplit = 1024;
 // one and in binary32 within a tile, for calls that need the candidates' order
 // only: |S~ - S| <= score_tol(S~, m).  Per pair 16 instead of 26 VALU cycles, so
 // that the matrix cores bound the loop; where the bound leaves a position open,
-// k_rescore computes the exact scores (below).
+// k_rescore computes the exact scores (below).  Which banks take it: k_score_probe.
 //   v_rcp_f32 is within 1 ulp (2^-23) of 1 / t^p, the correctly rounded weight
 //   within 2^-24: together 3 2^-24 per term; eight terms in a chain and the sum of
 //   the two chains add at most 9 2^-24; the exact terms are rounded to integers
@@ -421,34 +421,44 @@ constexpr int kColsPerSplit = 1024;
 //   (1/2 + 1/32) m, below S / 2^20 + m.
 __device__ __forceinline__ int64_t score_tol(int64_t s, int m) { return (s >> 20) + m + 2; }
 
-template <int D, int P, bool FOLD, bool KV, bool APPROX>
-__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2) void k_score_mfma(dkv_bank bank, const void *seg_k, const void *seg_v,
-                                                           Geom g, Prm p, Workspace ws) {
+// The LDS stages of a score workgroup: column keys and aug steps (the third stage at
+// descriptor dimension 256 only) and score scales.
+template <int D>
+struct ScoreBufs {
+  char *k0, *k1, *k2, *a0, *a1, *a2;
+  float *s0, *s1, *s2;
+};
+template <int D>
+constexpr int score_key2() { return D <= 128 ? 1024 : SCfg<D>::KEYB; }
+template <int D>
+constexpr int score_aug2() { return D <= 128 ? 16 : SCfg<D>::AUGB; }
+#define DKV_SCORE_BUFS(sb)                                                                                        \
+  __shared__ __attribute__((aligned(1024))) char sb##_k0[SCfg<D>::KEYB], sb##_k1[SCfg<D>::KEYB], sb##_k2[score_key2<D>()]; \
+  __shared__ __attribute__((aligned(16))) char sb##_a0[SCfg<D>::AUGB], sb##_a1[SCfg<D>::AUGB], sb##_a2[score_aug2<D>()];   \
+  __shared__ __attribute__((aligned(16))) float sb##_s0[kSI], sb##_s1[kSI], sb##_s2[kSI];                             \
+  const ScoreBufs<D> sb{sb##_k0, sb##_k1, sb##_k2, sb##_a0, sb##_a1, sb##_a2, sb##_s0, sb##_s1, sb##_s2}
+
+// Rows of a score work item: 32 W of the bank's candidates in order from 32 W bx
+// on; entries [e0, e1) of its list from e0 + 32 W bx on; or 32 W of them spread
+// over the block, whose sums go to `probe`.
+enum ScoreRows { ROWS_ALL, ROWS_LIST, ROWS_PROBE };
+
+// Scores of a work item's candidates over the states [c0, c0 + ncols) of bank b.
+template <int D, int P, bool FOLD, bool KV, bool APPROX, int ROWS>
+__device__ __forceinline__ void score_item(const dkv_bank &bank, const void *seg_k, const void *seg_v, const Geom &g,
+                                           const Prm &p, const Workspace &ws, int b, int bx, int c0, int ncols,
+                                           const ScoreBufs<D> &sb, int e0, int e1, uint64_t *probe) {
   constexpr int W = gram_waves<D>();
-  // One-dimensional grid over (row block, column split, bank), row blocks
-  // fastest.  Workgroup L is dispatched to XCD L % 8; ranking the workgroups
-  // XCD by XCD (r = workgroups on lower XCDs + L / 8) keeps all the work items
-  // of a bank on one XCD, in order, so that its keys and the candidates' stay
-  // in that XCD's L2.
-  const int nx = (g.N + 32 * W - 1) / (32 * W), ny = (g.Mcap + kColsPerSplit - 1) / kColsPerSplit;
-  const int T = (int)gridDim.x, L = (int)blockIdx.x, xcd = L % 8;
-  const int r = xcd * (T / 8) + min(xcd, T % 8) + L / 8;
-  const int b = r / (nx * ny), by = (r / nx) % ny, bx = r % nx;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, h = l >> 5, n = l & 31;
-  const int x = bx * 32 * W + wave * 32 + n;
-  const int m = ws.m[b];
-  const int c0 = by * kColsPerSplit;
-  if (c0 >= m || ws.whole[b] == 2) return;  // the order of a block that enters whole is not needed
-  const int ncols = min(kColsPerSplit, m - c0);
-  constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
-  constexpr int K2 = D <= 128 ? 1024 : KB, A2 = D <= 128 ? 16 : AB;  // third stage: descriptor dimension 256 only
-  __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[K2];
-  __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[A2];
-  __shared__ __attribute__((aligned(16))) float s0[kSI], s1[kSI], s2[kSI];
+  const int x = e0 + bx * 32 * W + wave * 32 + n;
+  char *const k0 = sb.k0, *const k1 = sb.k1, *const k2 = sb.k2, *const a0 = sb.a0, *const a1 = sb.a1, *const a2 = sb.a2;
+  float *const s0 = sb.s0, *const s1 = sb.s1, *const s2 = sb.s2;
   const Desc K{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
   const Desc BK{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)};
-  const bool rv = x < g.N;
-  const size_t xr = (size_t)b * g.N + (rv ? x : 0);
+  const bool rv = x < e1;
+  size_t xr = (size_t)b * g.N + (rv ? x : 0);
+  if constexpr (ROWS == ROWS_LIST) xr = (size_t)b * g.N + ws.adm_list[(size_t)b * g.N + min(x, e1 - 1)];
+  if constexpr (ROWS == ROWS_PROBE) xr = (size_t)b * g.N + x * g.N / (32 * W);
   RowFrag<D> rf;
   load_row_frag<D, FOLD, KV>(rf, K, (int64_t)xr, rv ? ws.cnorm[xr] : 0.0f, rv, -2.0f * p.inv_sigma2, p.inv_sigma2);
   const size_t rb = (size_t)b * g.Mcap + c0;
@@ -636,8 +646,93 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
   }
   const uint64_t At = A64 + __shfl_xor(A64, 32, 64);
   if (!rv || h != 0) return;
-  const size_t o = (size_t)b * g.N + x;
-  atomicAdd(reinterpret_cast<unsigned long long *>(&ws.acol[o]), (unsigned long long)At);
+  if constexpr (ROWS == ROWS_PROBE) probe[x] = At;
+  else atomicAdd(reinterpret_cast<unsigned long long *>(&(ROWS == ROWS_LIST ? ws.sub_adm : ws.acol)[xr]), (unsigned long long)At);
+}
+
+template <int D, int P, bool FOLD, bool KV, bool APPROX>
+__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2) void k_score_mfma(
+    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws) {
+  constexpr int W = gram_waves<D>();
+  // One-dimensional grid over (row block, column split, bank), row blocks
+  // fastest.  Workgroup L is dispatched to XCD L % 8; ranking the workgroups
+  // XCD by XCD (r = workgroups on lower XCDs + L / 8) keeps all the work items
+  // of a bank on one XCD, in order, so that its keys and the candidates' stay
+  // in that XCD's L2.
+  const int nx = (g.N + 32 * W - 1) / (32 * W), ny = (g.Mcap + kColsPerSplit - 1) / kColsPerSplit;
+  const int T = (int)gridDim.x, L = (int)blockIdx.x, xcd = L % 8;
+  const int r = xcd * (T / 8) + min(xcd, T % 8) + L / 8;
+  const int b = r / (nx * ny), by = (r / nx) % ny, bx = r % nx;
+  const int m = ws.m[b];
+  const int c0 = by * kColsPerSplit;
+  if (c0 >= m || ws.whole[b] == 2) return;  // the order of a block that enters whole is not needed
+  DKV_SCORE_BUFS(sb);
+  const int ncols = min(kColsPerSplit, m - c0);
+  if (APPROX && !ws.exact[b])
+    score_item<D, P, FOLD, KV, true, ROWS_ALL>(bank, seg_k, seg_v, g, p, ws, b, bx, c0, ncols, sb, 0, g.N, nullptr);
+  else
+    score_item<D, P, FOLD, KV, false, ROWS_ALL>(bank, seg_k, seg_v, g, p, ws, b, bx, c0, ncols, sb, 0, g.N, nullptr);
+}
+
+// Whether a bank's scores are worth approximating (exact[b] = 0).
+//   Where the order is needed beyond its head, as in a group whose crossing
+// search goes on past the first part, the exact scores of the open neighbours cost
+// more than the approximation saves (48 full banks of 9,360 states, 18 to 28% of
+// the candidates open: update 2,340 -> 2,580 us).  So the bank's group has to be
+// replaced whole, or one of its banks has to be near its bound (k_begin).
+//   And the share of neighbours in the order that the error bound leaves open has
+// to be small.  It is estimated from the exact scores of 32 W candidates spread
+// over the block, over the bank's first states: in the sorted sample the distance
+// of eight places gives the local spacing, scaled to the whole block and bank.
+// Estimate and truth were 0.11 and 0.09 for clustered keys, 0.20 and 0.15 without
+// clusters, 0.81 and 0.59 with one baseline at a tenth of the next (the scores' unit
+// follows the smallest), 1.0 and 1.0 with tied candidates; a bank that turned out
+// open throughout took twice the exact score's time.
+constexpr int kProbeStates = 256;
+constexpr float kProbeMax = 0.25f;
+
+template <int D, int P, bool FOLD, bool KV>
+__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2) void k_score_probe(
+    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws) {
+  constexpr int W = gram_waves<D>(), S = 32 * W, kApart = 8;
+  const int b = blockIdx.x, t = threadIdx.x, m = ws.m[b];
+  // an order that is needed beyond the first part (or one position) pays for more exact scores than it saves
+  bool near = ws.whole[b] != 0;
+  const int g0 = (b / g.gs) * g.gs;
+  for (int j = t & 63; j < g.gs; j += 64) near |= ws.n_ev[g0 + j] != 0;
+  near = __any(near);
+  if (g.N < S || m == 0 || ws.whole[b] == 2 || !near) {  // too few to judge; nothing to score; not worth it
+    if (t == 0) ws.exact[b] = g.N < S || !near;
+    return;
+  }
+  DKV_SCORE_BUFS(sb);
+  __shared__ uint64_t raw[S], sorted[S];
+  __shared__ float part[W];
+  const int ncols = min(kProbeStates, m);
+  score_item<D, P, FOLD, KV, false, ROWS_PROBE>(bank, seg_k, seg_v, g, p, ws, b, 0, 0, ncols, sb, 0, S, raw);
+  __syncthreads();
+  if (t < S) {
+    const uint64_t s = raw[t];
+    int r = 0;
+    for (int j = 0; j < S; ++j) r += raw[j] < s || (raw[j] == s && j < t);
+    sorted[r] = s;
+  }
+  __syncthreads();
+  float open = 0.0f;
+  if (t + kApart < S) {
+    const float up = (float)m / (float)ncols;
+    const float tol = 2.0f * (float)score_tol((int64_t)((float)sorted[t] * up), m);
+    const float gap = (float)(sorted[t + kApart] - sorted[t]) * up * ((float)S / ((float)kApart * (float)g.N));
+    open = tol < gap ? tol / gap : 1.0f;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) open += __shfl_xor(open, o, 64);
+  if ((t & 63) == 0) part[t >> 6] = open;
+  __syncthreads();
+  if (t == 0) {
+    for (int w = 1; w < W; ++w) open += part[w];
+    ws.exact[b] = open > kProbeMax * (S - kApart);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -656,6 +751,7 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
 // ---------------------------------------------------------------------------
 constexpr int kOrderThreads = 1024;
 constexpr int kAmbiguous = 1 << 30;
+constexpr int kWalkMax = 16;  // steps to either side; beyond, the whole list is sorted
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_mark(Geom g, Workspace ws) {
   const int b = blockIdx.x, m = ws.m[b], R = ws.R[b], N = g.N, whole = ws.whole[b];
@@ -664,7 +760,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_mark(Geom g, Workspace 
   __shared__ int tmp[2][kOrderThreads / 64];
   __shared__ int lo, hi;  // positions [lo, hi): whole = 1: the cluster across R; else the first list's
   constexpr int kPer = kSortMax / kOrderThreads;
-  if (m == 0 || whole == 2) {  // every score is 0 and exact, or no order is needed
+  if (m == 0 || whole == 2 || ws.exact[b]) {  // every score is exact, or no order is needed
     if (threadIdx.x == 0) ws.n_ev[b] = ws.e[b] = 0;
     return;
   }
@@ -734,93 +830,101 @@ __device__ __forceinline__ void order_range(const Geom &g, const Workspace &ws, 
   k1 = rest ? (ws.more[b / g.gs] >= kMoreOpen ? ws.e[b] : k0) : ws.n_ev[b];
 }
 
-// Exact scores of the listed candidates: 32 of them and 1,024 bank states per
-// work item; a wave takes every fourth tile of 32 states, straight from global
-// memory (the few rows give no reuse that LDS could serve).
+// Exact scores of the listed candidates, with the score kernel's tiles (32 W of
+// them and 1,024 bank states per work item).
 template <int D, int P, bool FOLD, bool KV>
-__global__ __launch_bounds__(256) void k_rescore(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p,
-                                                 Workspace ws, int rest) {
+__global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_rescore(
+    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws, int rest) {
+  constexpr int kRpw = 32 * gram_waves<D>();
   __shared__ int pre[65];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, h = l >> 5, n = l & 31;
-  const Desc SK{static_cast<const uint16_t *>(seg_k), static_cast<const uint16_t *>(seg_v)};
-  const Desc BK{static_cast<const uint16_t *>(bank.k), static_cast<const uint16_t *>(bank.v)};
-  auto splits = [&](int b) { return (ws.m[b] + kColsPerSplit - 1) / kColsPerSplit; };
+  DKV_SCORE_BUFS(sb);
+  auto blocks = [&](int k0, int k1) { return (k1 - k0 + kRpw - 1) / kRpw; };
   walk_items(
       g.B, pre,
       [&](int b) {
         int k0, k1;
         order_range(g, ws, b, rest, k0, k1);
-        return (k1 - k0 + 31) / 32 * splits(b);
+        return blocks(k0, k1) * ((ws.m[b] + kColsPerSplit - 1) / kColsPerSplit);
       },
       [&](int b, int i) __attribute__((always_inline)) {
-        constexpr int KS = TileCfg<D>::kSteps;
         int k0, k1;
         order_range(g, ws, b, rest, k0, k1);
-        const int ny = splits(b), k = k0 + i / ny * 32 + n, c0 = i % ny * kColsPerSplit;
-        const int c1 = min(ws.m[b], c0 + kColsPerSplit);
-        const size_t nb = (size_t)b * g.N, rb = (size_t)b * g.Mcap;
-        const bool v = k < k1;
-        const int64_t xr = (int64_t)(nb + ws.adm_list[nb + min(k, k1 - 1)]);
-        RowFrag<D> rf;
-        load_row_frag<D, FOLD, KV>(rf, SK, xr, ws.cnorm[xr], v, -2.0f * p.inv_sigma2, p.inv_sigma2);
-        uint64_t sum = 0;
-        for (int j0 = c0 + wave * kCT; j0 < c1; j0 += kWaves * kCT) {
-          const int64_t r = (int64_t)(rb + min(j0 + n, c1 - 1));
-          f32x16 u = {};
-#pragma unroll
-          for (int kk = 0; kk < KS; ++kk)
-            u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(desc_chunk<D, KV>(BK, r, 2 * kk + h))),
-                rf.b[kk], u, 0, 0, 0);
-          u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ws.baug[r]), rf.b[KS], u, 0, 0, 0);
-          uint32_t s = 0;
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            const int j = j0 + col_of_reg(q, h);
-            const uint32_t raw = weight_raw<P, FOLD>(u[q], ws.bs[rb + min(j, c1 - 1)]);
-            s += j < c1 ? raw - kMagic : 0u;
-          }
-          sum += s;
-        }
-        sum += __shfl_xor(sum, 32, 64);
-        if (v && h == 0) atomicAdd(reinterpret_cast<unsigned long long *>(&ws.sub_adm[xr]), (unsigned long long)sum);
+        const int nx = blocks(k0, k1), c0 = i / nx * kColsPerSplit;
+        __syncthreads();  // the previous item's LDS stages are done with
+        score_item<D, P, FOLD, KV, false, ROWS_LIST>(bank, seg_k, seg_v, g, p, ws, b, i % nx, c0,
+                                                     min(kColsPerSplit, ws.m[b] - c0), sb, k0, k1, nullptr);
       });
 }
 
 // The members of a cluster take its positions in the order of (exact score,
-// source index); one workgroup per bank.
+// source index); one workgroup per bank.  A member counts the smaller ones of
+// its cluster while the clusters are short.  With a longer one (nearly tied
+// scores: a block of equal rows, or one state whose baseline is far below the
+// others') the whole list is sorted instead: clusters are separated by a gap
+// that the error bound does not reach, so in the order of the exact scores the
+// list's k-th member takes its k-th position.
 __global__ __launch_bounds__(kOrderThreads) void k_order_fix(Geom g, Workspace ws, int rest) {
   const int b = blockIdx.x;
   const size_t nb = (size_t)b * g.N;
   int k0, k1;
   order_range(g, ws, b, rest, k0, k1);
   if (k0 >= k1) return;
-  __shared__ int64_t S[kSortMax];
+  __shared__ uint64_t S[kSortMax];
   __shared__ uint32_t X[kSortMax];  // candidate, and in bit 31: ambiguous with the next position
   for (int k = k0 + (int)threadIdx.x; k < k1; k += kOrderThreads) {
     const int x = ws.adm_list[nb + k];
-    S[k - k0] = ws.sub_adm[nb + x];
+    S[k - k0] = (uint64_t)ws.sub_adm[nb + x];
     ws.sub_adm[nb + x] = 0;
     X[k - k0] = (uint32_t)x | (ws.adm_dest[nb + k] & kAmbiguous ? 0x80000000u : 0u);
   }
   __syncthreads();
   const int cnt = k1 - k0;
-  for (int k = threadIdx.x; k < cnt; k += kOrderThreads) {
+  bool walked = true;
+  for (int k = threadIdx.x; k < cnt && walked; k += kOrderThreads) {
     const int x = (int)(X[k] & 0x7FFFFFFFu);
-    const int64_t s = S[k];
-    int first = k, less = 0;
+    const uint64_t s = S[k];
+    int first = k, j = k, less = 0;
     // members are listed by position, so a cluster is a run whose entries are ambiguous with their next
-    while (first > 0 && (X[first - 1] >> 31)) {
+    while (first > 0 && (X[first - 1] >> 31) && k - first < kWalkMax) {
       --first;
       const int y = (int)(X[first] & 0x7FFFFFFFu);
       less += S[first] < s || (S[first] == s && y < x);
     }
-    for (int j = k; X[j] >> 31; ) {
+    while (X[j] >> 31 && j - k < kWalkMax) {
       ++j;
       const int y = (int)(X[j] & 0x7FFFFFFFu);
       less += S[j] < s || (S[j] == s && y < x);
     }
-    const int pos = (ws.adm_dest[nb + k0 + first] & ~kAmbiguous) + less;
+    walked = !(first > 0 && X[first - 1] >> 31) && !(X[j] >> 31);
+    if (walked) {
+      const int pos = (ws.adm_dest[nb + k0 + first] & ~kAmbiguous) + less;
+      ws.order[nb + pos] = x;
+      ws.rank[nb + x] = pos;
+    }
+  }
+  if (__syncthreads_and(walked)) return;
+  // bitonic sort of (score, source index), padded to a power of two
+  int n2 = kOrderThreads;
+  while (n2 < cnt) n2 *= 2;
+  for (int k = threadIdx.x; k < n2; k += kOrderThreads)
+    S[k] = k < cnt ? (S[k] << 13) | (X[k] & 0x1FFFu) : ~0ull;
+  __syncthreads();
+  for (int len = 2; len <= n2; len <<= 1) {
+    for (int d = len >> 1; d > 0; d >>= 1) {
+      for (int t = threadIdx.x; t < n2 / 2; t += kOrderThreads) {
+        // the t-th index i with bit d clear, against i + d; ascending where bit len of i is clear
+        const int i = ((t & ~(d - 1)) << 1) | (t & (d - 1));
+        const uint64_t x = S[i], y = S[i + d];
+        if (((i & len) == 0) == (x > y)) {
+          S[i] = y;
+          S[i + d] = x;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  for (int k = threadIdx.x; k < cnt; k += kOrderThreads) {
+    const int x = (int)(S[k] & 0x1FFFu), pos = ws.adm_dest[nb + k0 + k] & ~kAmbiguous;
     ws.order[nb + pos] = x;
     ws.rank[nb + x] = pos;
   }
@@ -2070,8 +2174,10 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
   const unsigned rowsM = cdiv(g.Mcap, 32 * W), rowsN = cdiv(g.N > 0 ? g.N : 1, 32 * W);
   const void *sv = seg.v;
   switch (stage) {
-    case kGramScore:
     case kGramScoreApprox:
+      k_score_probe<D, P, F, KV><<<g.B, T, 0, s>>>(bank, seg.k, sv, g, p, ws);
+      [[fallthrough]];
+    case kGramScore:
       (stage == kGramScore ? k_score_mfma<D, P, F, KV, false> : k_score_mfma<D, P, F, KV, true>)
           <<<rowsN * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, T, 0, s>>>(bank, seg.k, sv, g, p, ws);
       break;
@@ -2079,7 +2185,7 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
     case kGramOrderRest: {
       const int rest = stage == kGramOrderRest;
       if (!rest) k_order_mark<<<g.B, kOrderThreads, 0, s>>>(g, ws);
-      k_rescore<D, P, F, KV><<<grid_of((uint64_t)cdiv(g.N, 32) * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, 2048), 256, 0,
+      k_rescore<D, P, F, KV><<<grid_of((uint64_t)rowsN * cdiv(g.Mcap, kColsPerSplit) * (unsigned)g.B, kGramWgs<D>), T, 0,
                                s>>>(bank, seg.k, sv, g, p, ws, rest);
       k_order_fix<<<g.B, kOrderThreads, 0, s>>>(g, ws, rest);
       break;

@@ -52,7 +52,7 @@ struct Workspace {
   uint4 *baug;         // [B, Mcap] column aug step of each bank state (column_aug)
   uint4 *caug;         // [B, N]   of each candidate, source order
   uint4 *saug;         // [B, N]   of each candidate, score order
-  int32_t *maint_off;  // [B + 1] unused
+  int32_t *exact;      // [B] approximate scores are not worth it for the bank (k_score_probe)
   int32_t *crossed;    // [B] first word: nonzero if some bank admits or releases a state
   int32_t *more;       // [G] 64-candidate chunks after which the group's crossing search may end (kMoreOpen: not known)
   int32_t *whole;      // [B] the bank's group is replaced whole (k_begin); the storage of m_new, free until k_select

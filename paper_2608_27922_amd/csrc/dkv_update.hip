@@ -103,6 +103,13 @@ __device__ int block_max(int v, int *tmp) {
 // to one block.  Such a one-layer update (12 banks, budget = block = 4,680)
 // took 432 us with the score, the sort keys and the whole crossing search.
 // allow: the largest value the requested outputs permit.
+//
+// near (n_ev, where the call may approximate its scores): more states than the
+// bank can release stand so close to their bound that the first part of the
+// crossing search will very likely decide the bank (k_first_part_mfma): the first
+// 256 candidates, the ones of lowest score, would have to weigh less than a
+// quarter of what the bank's own states weigh on average.  A guess that costs
+// time when it is wrong, and nothing else.
 // ---------------------------------------------------------------------------
 // The candidate rows come through LDS, a wave's 64 rows in parts of 128 bytes: a
 // lane that read its own row from memory took 16 bytes of 64 different lines per
@@ -152,7 +159,8 @@ __device__ __forceinline__ void add_row_norms(const uint16_t *src, int nrow, cha
 
 template <int D, int DT>
 __global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, const void *seg_k, const void *seg_v, Geom g,
-                                                         Workspace ws, float inv_s2, int norms, int allow) {
+                                                         Workspace ws, Prm p, int norms, int allow, int approx) {
+  const float inv_s2 = p.inv_sigma2;
   const int b = blockIdx.y;
   const size_t rb = (size_t)b * g.Mcap, nb = (size_t)b * g.N;
   if (blockIdx.x > 0) {
@@ -246,14 +254,36 @@ __global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, cons
     const long long bi = mn < 1 ? 1 : mn;
     frexpf((float)(8388608.0 / (double)bi), &E);
   }
+  int close = 0;
   for (int i0 = threadIdx.x; i0 < m; i0 += kU * kBeginThreads<DT>) {
     long long bq[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) bq[u] = bank.base[rb + min(i0 + u * kBeginThreads<DT>, m - 1)];  // clamped, unconditional
+    if (approx) {
+      long long rq[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) rq[u] = bank.rho[rb + min(i0 + u * kBeginThreads<DT>, m - 1)];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const long long thr = ((p.tau_num * bq[u] + ((1ll << p.tau_shift) - 1)) >> p.tau_shift) - rq[u];
+        close += i0 + u * kBeginThreads<DT> < m && (float)thr * (float)m <= 0.25f * kCrossFirst * (float)rq[u];
+      }
+    }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int i = i0 + u * kBeginThreads<DT>;
       if (i < m) ws.bs[rb + i] = score_scale(bq[u], E);
+    }
+  }
+  if (approx) {
+    __shared__ int redc[kBeginThreads<DT> / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) close += __shfl_xor(close, o, 64);
+    if ((threadIdx.x & 63) == 0) redc[threadIdx.x >> 6] = close;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < kBeginThreads<DT> / 64; ++w) close += redc[w];
+      ws.n_ev[b] = close > max(0, m + R - Mb);
     }
   }
   if (threadIdx.x == 0) {
@@ -276,12 +306,12 @@ __global__ __launch_bounds__(kBeginThreads<DT>) void k_begin(dkv_bank bank, cons
 
 template <int D, int DT>
 void launch_begin(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p, const Workspace &ws,
-                  bool norms, int allow_whole, hipStream_t s) {
+                  bool norms, int allow_whole, int approx, hipStream_t s) {
   const int span = g.N > g.Mcap ? g.N : g.Mcap;
   // [K; V] geometry: candidate norms over the concatenated key-value rows
   const void *seg_v = (p.flags & DKV_POLICY_KV_DESCRIPTOR) ? seg.v : nullptr;
   k_begin<D, DT><<<dim3((unsigned)(1 + (span + kBeginThreads<DT> - 1) / kBeginThreads<DT>), (unsigned)g.B), kBeginThreads<DT>, 0, s>>>(
-      bank, seg.k, seg_v, g, ws, p.inv_sigma2, norms ? 1 : 0, allow_whole);
+      bank, seg.k, seg_v, g, ws, p, norms ? 1 : 0, allow_whole, approx);
 }
 
 // ---------------------------------------------------------------------------
@@ -902,7 +932,7 @@ __global__ void k_pair_weight(const float *d2, int64_t n, Prm p, int32_t *w) {
 
 inline dim3 grid2(int n, int per, int B) { return dim3((unsigned)((n + per - 1) / per), (unsigned)B); }
 
-constexpr double kApproxPairs = 2e9;
+constexpr double kApproxPairs = 1e10;
 
 template <int D, int DT>
 hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
@@ -914,14 +944,18 @@ hipError_t update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom 
   // (and the order they give), which the sequential competition needs in any case
   const bool seq = (p.flags & DKV_POLICY_SEQUENTIAL) != 0;
   const int allow_whole = (seq || out.first_cross || out.rho_tilde) ? 0 : ((out.order || out.score_q) ? 1 : 2);
-  // Large calls that ask for neither the scores nor the order take approximate
-  // scores first and exact ones only where the approximation leaves the order
-  // open (dkv_gram_mfma.hip): five more launches and a second read of the bank
-  // keys, against a third of the score's time; below about 2e9 pairs
-  // (by capacity) these cost as much as they save.
+  // Large calls that ask for neither the scores nor the order may take
+  // approximate scores first and exact ones only where the approximation leaves
+  // the order open (dkv_gram_mfma.hip).  k_score_probe decides for each bank: it
+  // pays where the order is needed at its head only and few neighbours are too
+  // close (360 frozen banks of 9,300 states x 4,680 candidates: update 5.45 ->
+  // 5.14 ms, 360 head-wise banks 4.30 -> 4.08).  The six launches cost 25 to 30 us
+  // where it does not (24 banks of 9,000 states, 1.0e9 pairs: 410 -> 437 us; 96
+  // growing banks, 2.1e9: 2,315 -> 2,320), so calls below 1e10 pairs (by capacity,
+  // of which banks in use hold about half) score exactly from the start.
   const bool approx = kMfma && !seq && !(p.flags & DKV_POLICY_SOURCE_ORDER) && !out.order && !out.score_q &&
                       (double)g.B * g.Mcap * g.N >= kApproxPairs;
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0, allow_whole, approx ? 1 : 0, s);
   if (g.N > 0) {
     // in source order the scores are only reported
     if (!(p.flags & DKV_POLICY_SOURCE_ORDER) || out.score_q) {
@@ -974,7 +1008,7 @@ template <int D, int DT>
 hipError_t score_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &g, const Prm &p,
                       int64_t *score_q, float *score_f, int64_t *density, const Workspace &ws,
                       hipStream_t s) {
-  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, s);
+  launch_begin<D, DT>(bank, seg, g, p, ws, g.N > 0 && (score_q || score_f), 0, 0, s);
   const bool scores = g.N > 0 && (score_q || score_f);
   if constexpr (DT == DKV_BF16) {
     launch_score_mfma(bank, seg, g, p, scores ? score_q : nullptr, scores ? score_f : nullptr, density, ws, s);

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 from paper_2608_27922_amd import api, synth  # noqa: E402
 from gpu_util import (TORCH_DT, assert_bank_equal, assert_trace_equal, attention_error, dev, host,  # noqa: E402
                       oracle_params, oracle_step)
-from oracle import BankState, attention  # noqa: E402
+from oracle import BankState, attention, pair_d2, weight_q23  # noqa: E402
 from test_gpu_parity import POLICY_FLAGS, SMALL, _log, _run_rollout  # noqa: E402
 
 
@@ -141,18 +141,18 @@ def test_order_at_sort_edges(n, source_order):
 
 
 @pytest.mark.parametrize("kv,B,gs,n,budgets", [
-    (False, 8, 4, 8191, (300, 700, 300, 300)),   # unequal budgets: the general search up to R = 300
-    (False, 8, 2, 8191, (300, 300)),             # replaced whole: the order matters across position 300 only
-    (False, 64, 2, 1000, (1400, 1500)),          # growing, then at its budget: every order position may matter
-    (True, 64, 2, 1000, (1400, 1500)),
+    (False, 40, 4, 8191, (300, 700, 300, 300)),   # unequal budgets: the general search up to R = 300
+    (False, 40, 2, 8191, (300, 300)),             # replaced whole: the order matters across position 300 only
+    (False, 320, 2, 1000, (1400, 1500)),          # growing, then at its budget: every order position may matter
+    (True, 320, 2, 1000, (1400, 1500)),
 ])
 def test_approximate_scores_give_the_exact_order(kv, B, gs, n, budgets):
-    """Calls of at least 2e9 pairs (by capacity) that ask for no scores order their candidates by approximate
+    """Calls of at least 1e10 pairs (by capacity) that ask for no scores may order their candidates by approximate
     ones; asking for them takes the exact route.  Same decisions and banks, with duplicated and nearly
     duplicated candidates so that many neighbours in the order are closer than the error bound."""
     _log(f"approximate scores kv={kv} B={B} n={n} budgets={budgets}")
     d, cap = 64, 32767
-    assert B * cap * n >= 2e9
+    assert B * cap * n >= 1e10
     prm = api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0)
     bud = torch.tensor([budgets[b % gs] for b in range(B)], dtype=torch.int32)
     banks = [api.Bank(B, cap, d, group_size=gs, budget=bud) for _ in range(2)]
@@ -180,55 +180,87 @@ def test_approximate_scores_give_the_exact_order(kv, B, gs, n, budgets):
             assert torch.equal(x, y), f"block {t} {name}"
 
 
-def _against_oracle(B, cap, d, gs, budgets, blocks, prm, stale=False):
-    """Updates without the order or the scores among their outputs against the oracle.  blocks(t, obanks):
-    [B, n, d] float32 keys and values of block t.  stale: unused bank slots and the workspace hold NaNs."""
-    bud = np.array([budgets[b % gs] for b in range(B)], np.int32)
-    bank = api.Bank(B, cap, d, group_size=gs, budget=torch.from_numpy(bud))
-    if stale:
-        for x in (bank.k, bank.v, bank.knorm):
-            x.fill_(float("nan"))
-    obanks = [BankState.empty(int(x), d) for x in bud]
-    t = 0
-    while (kv := blocks(t, obanks)) is not None:
-        K, V = kv
-        n = K.shape[1]
-        out, ws = api.UpdateOut(bank, n), api.alloc_workspace(bank, n, prm.flags)
-        if stale:
-            ws.fill_(255)
-        api.update_bank(bank, dev(K, "bf16"), dev(V, "bf16"), t, prm, workspace=ws, out=out)
-        obanks, recs = oracle_step(obanks, K, V, t, oracle_params(prm), gs)
-        for g, rec in enumerate(recs):
-            assert int(out.r_star[g]) == rec.r_star, f"block {t} group {g}"
-            for j, hr in enumerate(rec.heads):
-                b = g * gs + j
-                for name, ref in (("admitted", hr.admitted), ("evicted", hr.evicted)):
-                    got = getattr(out, name)[b].cpu().numpy()
-                    assert np.array_equal(got[got >= 0], ref), f"block {t} bank {b}: {name}"
-        for b in range(B):
-            assert_bank_equal(bank, b, obanks[b], ctx=f"block {t}", kv=bool(prm.flags & api.POLICY_KV_DESCRIPTOR))
-        t += 1
-
-
 @pytest.mark.parametrize("d,kv", [(64, False), (128, False), (64, True)])
-@pytest.mark.parametrize("gs,budgets", [(1, (300,)), (2, (300, 415))])
-def test_approximate_scores_read_no_stale_scale(d, kv, gs, budgets):
-    """Approximate scores (calls of at least 2e9 pairs by capacity) where the banks end inside a tile of 32 states
-    and what lies behind them, in the bank and in the workspace, is NaN."""
-    _log(f"stale workspace d={d} kv={kv} budgets={budgets}")
-    B, cap, n = 8, 32767, 8191
-    rng = np.random.default_rng(d + gs)
-    centres = rng.standard_normal((B, 12, d)) / d ** 0.5
+def test_approximate_scores_read_no_stale_scale(d, kv):
+    """Approximate scores (calls of at least 1e10 pairs by capacity, banks replaced whole by a larger block) where
+    the banks end inside a tile of 32 states and what lies behind them, in the bank and in the workspace, is NaN."""
+    _log(f"stale workspace d={d} kv={kv}")
+    B, cap, n, check = 40, 32767, 8191, (0, 19, 39)
+    assert B * cap * n >= 1e10
+    rng = np.random.default_rng(d)
+    prm = api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0)
+    bank = api.Bank(B, cap, d, budget=torch.full((B,), 300, dtype=torch.int32))
+    for x in (bank.k, bank.v, bank.knorm):
+        x.fill_(float("nan"))
+    obanks = [BankState.empty(300, d) for _ in check]
+    for t in range(2):
+        K, V = _spread_rows(rng, B, n, d), _spread_rows(rng, B, n, d)
+        ws = api.alloc_workspace(bank, n, prm.flags).fill_(255)
+        api.update_bank(bank, dev(K, "bf16"), dev(V, "bf16"), t, prm, workspace=ws, out=api.UpdateOut(bank, n))
+        obanks, _ = oracle_step(obanks, K[list(check)], V[list(check)], t, oracle_params(prm), 1)
+        for b, ob in zip(check, obanks):
+            assert_bank_equal(bank, b, ob, ctx=f"block {t}", kv=kv)
 
-    def blocks(t, obanks):
-        if t == 3:
-            return None
-        x = centres[np.arange(B)[:, None], rng.integers(0, 12, (B, n))] + 0.1 * rng.standard_normal((B, n, d))
-        return [(np.clip(np.rint(y * 64), -127, 127) / 64).astype(np.float32)
-                for y in (x, rng.standard_normal((B, n, d)))]
 
-    _against_oracle(B, cap, d, gs, budgets, blocks,
-                    api.Params(sigma2_log2=5, flags=api.POLICY_KV_DESCRIPTOR if kv else 0), stale=True)
+def _spread_rows(rng, B, n, d):
+    """[B, n, d] float32 rows on the key grid whose distances to one another, and so their scores, vary widely."""
+    c = rng.standard_normal((B, 12, d)) / 3.0
+    x = c[np.arange(B)[:, None], rng.integers(0, 12, (B, n))] * rng.uniform(0.2, 1.0, (B, n, 1))
+    x += rng.uniform(0.05, 0.4, (B, n, 1)) * rng.standard_normal((B, n, d))
+    return (np.clip(np.rint(x * 64), -127, 127) / 64).astype(np.float32)
+
+
+def _near_banks(B, cap, m, d, prm, candidates, reach, seed):
+    """Banks of m states that all stand near their bound (next to their densities), so that calls may approximate
+    their scores; the nearest takes `reach` candidates of mean weight.  Returns the bank and the oracle's."""
+    rng = np.random.default_rng(seed)
+    bank = api.Bank(B, cap, d, group_size=2)
+    K, V = _spread_rows(rng, B, m, d), _spread_rows(rng, B, m, d)
+    obanks, op = [], oracle_params(prm)
+    for b in range(B):
+        k = K[b].astype(np.float64)
+        w = weight_q23(pair_d2(k, candidates[b, ::16].astype(np.float64)), op).mean(1)  # mean weight to the block
+        thr = (w * reach * rng.uniform(1.0, 2.0, m)).astype(np.int64) // 2 * 2 + 2
+        rho = np.full(m, 1 << 38, np.int64)
+        obanks.append(BankState(budget=cap, K=k, V=V[b], rho=rho, base=(rho + thr) // 2,
+                                prov=np.arange(m, dtype=np.int64)))
+        for name in ("rho", "base", "prov"):
+            getattr(bank, name)[b, :m] = torch.from_numpy(getattr(obanks[b], name)).cuda()
+    bank.k[:, :m], bank.v[:, :m] = dev(K, "bf16"), dev(V, "bf16")
+    bank.knorm[:, :m] = torch.from_numpy((K.astype(np.float64) ** 2).sum(-1).astype(np.float32)).cuda()
+    bank.occupancy.fill_(m)
+    return bank, obanks
+
+
+@pytest.mark.parametrize("reach", [20, 900])  # the first part of the crossing search decides; it leaves the groups open
+@pytest.mark.parametrize("rows", ["spread", "triples", "hidden run", "tied"])
+def test_approximate_order_against_the_oracle(rows, reach):
+    """The order from approximate scores at m > 0: distinct scores, short clusters, one cluster of 8,063 candidates
+    that the 128 sampled ones do not show (the list is sorted), all scores tied (the exact scores at once)."""
+    _log(f"approximate order rows={rows} reach={reach}")
+    B, cap, m, d, n = 40, 32767, 1001, 64, 8191
+    assert B * cap * n >= 1e10
+    prm = api.Params(sigma2_log2=5)
+    rng = np.random.default_rng(reach)
+    k, v = _spread_rows(rng, B, n, d), _spread_rows(rng, B, n, d)
+    if rows == "triples":
+        k[:, 1::3], k[:, 2::3] = k[:, 0::3][:, : k[:, 1::3].shape[1]], k[:, 0::3][:, : k[:, 2::3].shape[1]]
+    elif rows != "spread":
+        keep = np.arange(128) * n // 128 if rows == "hidden run" else np.zeros(0, int)
+        same = np.repeat(k[:, 5:6], n, 1)
+        same[:, keep] = k[:, keep]
+        k = same
+    bank, obanks = _near_banks(B, cap, m, d, prm, k, reach, 3)
+    out = api.UpdateOut(bank, n)
+    api.update_bank(bank, dev(k, "bf16"), dev(v, "bf16"), 1, prm, out=out)
+    for i in (0, 7, B // 2 - 1):  # groups
+        b = [2 * i, 2 * i + 1]
+        new, (rec,) = oracle_step([obanks[x] for x in b], k[b], v[b], 1, oracle_params(prm), 2)
+        assert (rec.r_star < 256) == (reach == 20) and int(out.r_star[i]) == rec.r_star, f"group {i}"
+        for j in range(2):
+            got = out.admitted[b[j]].cpu().numpy()
+            assert np.array_equal(got[got >= 0], rec.heads[j].admitted), f"bank {b[j]}: admitted"
+            assert_bank_equal(bank, b[j], new[j])
 
 
 def test_first_crossings_within_short_prefixes():
