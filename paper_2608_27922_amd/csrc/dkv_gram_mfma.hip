@@ -935,7 +935,6 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_fix(Geom g, Workspace w
 // ---------------------------------------------------------------------------
 enum RowSumMode { RS_CHUNK = 0, RS_FIXUP = 1, RS_SURV_EV = 2, RS_ADM_BASE = 3 };
 
-constexpr int kChunksPerSplit = 1024 / kCkStride;   // RS_CHUNK: 1024 ordered candidates per workgroup
 static_assert(kCrossFirst % kCkStride == 0, "the first part ends on a chunk boundary");
 
 // The three LDS stages of a Gram workgroup (separate arrays: with the stage
@@ -977,7 +976,7 @@ __device__ __forceinline__ uint32_t row_transpose_tail(const uint32_t (&a)[8], i
 template <int D, int P, int MODE, bool FOLD, bool KV>
 __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *seg_k, const void *seg_v, const Geom &g,
                                             const Prm &p, const Workspace &ws, int64_t *out, int bx, int by, int bz,
-                                            const StageBufs<D> &sb, int cfirst = 0) {
+                                            const StageBufs<D> &sb, int cfirst = 0, int per = 0) {
   constexpr int W = gram_waves<D>();
   constexpr int kRowsPerWG = 32 * W;
   const int b = bz;
@@ -1004,9 +1003,9 @@ __device__ __forceinline__ void rowsum_body(const dkv_bank &bank, const void *se
   }
   // columns of this workgroup: [c0, c1) of the mode's column list
   int c0 = 0, c1 = 0;
-  if constexpr (MODE == RS_CHUNK) {  // prefixes from cfirst on, 1,024 per split
-    c0 = cfirst + by * kChunksPerSplit * kCkStride;
-    c1 = min(ws.R[b], c0 + kChunksPerSplit * kCkStride);
+  if constexpr (MODE == RS_CHUNK) {  // prefixes from cfirst on, `per` (whole chunks) per split
+    c0 = cfirst + by * per;
+    c1 = min(ws.R[b], c0 + per);
   } else if constexpr (MODE == RS_FIXUP) {
     c0 = (rs / kCkStride) * kCkStride;
     c1 = rs;
@@ -1922,14 +1921,9 @@ done:
 template <int D, int P, bool FOLD, bool KV>
 __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_cross_mfma(dkv_bank bank, Geom g, Prm p, Workspace ws,
                                                                             int32_t *out_first) {
-  constexpr int kStates = kWaves * kCrossWaveStates;
-  __shared__ int pre[65];
-  walk_items(
-      g.B, pre, [&](int b) { return ws.more[b / g.gs] >= kMoreOpen ? (ws.m[b] + kStates - 1) / kStates : 0; },
-      [&](int b, int i) __attribute__((always_inline)) {
-        __syncthreads();  // the previous item's LDS is done with
-        cross_body<D, P, FOLD, KV>(bank, g, p, ws, out_first, b, i);
-      });
+  const int b = blockIdx.y;
+  if (ws.more[b / g.gs] < kMoreOpen || (int)blockIdx.x * kWaves * kCrossWaveStates >= ws.m[b]) return;
+  cross_body<D, P, FOLD, KV>(bank, g, p, ws, out_first, b, blockIdx.x);
 }
 
 // The first part of the crossing search in one pass: the prefix-chunk Gram of
@@ -2097,25 +2091,22 @@ __global__ __launch_bounds__(64 * kWaves, D <= 128 ? 3 : 2) void k_first_part_mf
   }
 }
 
-// Chunk sums of the ordered prefixes past the first part (splits of 1,024) for
-// the groups that it left open.
+// Chunk sums of the ordered prefixes past the first part for the groups that it
+// left open: one workgroup per 32 W states and split of `per` candidates.  (Over
+// a fixed grid whose workgroups walked the open groups' items, this and the search
+// after it kept 20 to 40 registers more and ran in lockstep: 64 full banks of 9,360
+// states, d = 64: 685 us against 612 and 350 against 278; 48 of d = 128: 699
+// against 635 and 402 against 369; 12 of [K; V] rows: the search 248 against 171.)
 template <int D, int P, bool FOLD, bool KV>
 __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 3 : 2) void k_chunk_part_mfma(
-    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws) {
-  constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB, RPW = 32 * gram_waves<D>(), CPS = kChunksPerSplit * kCkStride;
+    dkv_bank bank, const void *seg_k, const void *seg_v, Geom g, Prm p, Workspace ws, int per) {
+  constexpr int KB = SCfg<D>::KEYB, AB = SCfg<D>::AUGB;
+  if (ws.more[blockIdx.z / g.gs] < kMoreOpen) return;
   __shared__ __attribute__((aligned(1024))) char k0[KB], k1[KB], k2[KB];
   __shared__ __attribute__((aligned(16))) char a0[AB], a1[AB], a2[AB];
-  __shared__ int pre[65];
   const StageBufs<D> sb{k0, k1, k2, a0, a1, a2, nullptr};
-  auto rows = [&](int b) { return (ws.m[b] + RPW - 1) / RPW; };
-  walk_items(
-      g.B, pre,
-      [&](int b) { return ws.more[b / g.gs] >= kMoreOpen ? rows(b) * ((ws.R[b] - kCrossFirst + CPS - 1) / CPS) : 0; },
-      [&](int b, int i) __attribute__((always_inline)) {
-        const int r = rows(b);
-        __syncthreads();  // the previous item's LDS stages are done with
-        rowsum_body<D, P, RS_CHUNK, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, i % r, i / r, b, sb, kCrossFirst);
-      });
+  rowsum_body<D, P, RS_CHUNK, FOLD, KV>(bank, seg_k, seg_v, g, p, ws, nullptr, blockIdx.x, blockIdx.y, blockIdx.z, sb,
+                                        kCrossFirst, per);
 }
 
 // Candidate keys and norm steps in score order, for the groups that the first
@@ -2164,6 +2155,9 @@ inline unsigned grid_of(uint64_t items, unsigned most) { return (unsigned)(items
 template <int D>
 constexpr unsigned kGramWgs = gram_waves<D>() == 4 ? 3 * 256 : 256;
 
+// Workgroups that the chunk sums are split into at least, if they have the work.
+constexpr uint64_t kChunkWgs = 49152;
+
 // D is the descriptor dimension: the key dimension, or twice it for the
 // [K; V] geometry (KV: the candidates' values seg_v and bank.v are read too).
 template <int D, int P, bool F, bool KV>
@@ -2203,10 +2197,16 @@ void mfma_update_impl(const dkv_bank &bank, const dkv_segment &seg, const Geom &
         const unsigned B = (unsigned)g.B;
         k_gather_sorted<D, KV><<<grid_of((uint64_t)cdiv(g.N, 256 / (D / 8) * kGatherRows) * B, 1024), 256, 0, s>>>(
             seg.k, sv, g, ws);
-        k_chunk_part_mfma<D, P, F, KV><<<grid_of((uint64_t)rowsM * cdiv(g.N - kCrossFirst, kChunksPerSplit * kCkStride) * B,
-                                                 kGramWgs<D>), T, 0, s>>>(bank, seg.k, sv, g, p, ws);
-        k_cross_mfma<D, P, F, KV><<<grid_of((uint64_t)cdiv(g.Mcap, kWaves * kCrossWaveStates) * B, 3 * 256),
-                                    64 * kWaves, 0, s>>>(bank, g, p, ws, out.first_cross);
+        // splits of 1,024 candidates, longer ones where the workgroups are many (an empty one costs 0.3 ns: 85 us
+        // for 360 decided banks in splits of 1,024)
+        const unsigned rest = (unsigned)(g.N - kCrossFirst), most = cdiv((int)rest, 1024);
+        const uint64_t want = (kChunkWgs + (uint64_t)rowsM * B - 1) / ((uint64_t)rowsM * B);
+        const unsigned splits = want < most ? (unsigned)want : most;
+        const unsigned per = cdiv(cdiv((int)rest, (int)splits), kCkStride) * kCkStride;
+        k_chunk_part_mfma<D, P, F, KV><<<dim3(rowsM, cdiv((int)rest, (int)per), B), T, 0, s>>>(bank, seg.k, sv, g, p, ws,
+                                                                                              (int)per);
+        k_cross_mfma<D, P, F, KV><<<dim3(cdiv(g.Mcap, kWaves * kCrossWaveStates), B), 64 * kWaves, 0, s>>>(
+            bank, g, p, ws, out.first_cross);
       }
       break;
     }
