@@ -17,6 +17,15 @@ namespace {
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
+// The host sizes the splits of a call by the capacity.  Of them a bank takes as
+// many as leave the first at least LEAST of its `total` tiles, one at least; the
+// others end at once and leave no result.  (12 banks of capacity 18,720 that hold
+// nothing yet, 64 queries, a window of 64: 15.5 us, 19.7 with every split at work,
+// 10.3 without splits; 2 such fp32 banks 14.5, 39.7 and 31.8.)
+template <int LEAST>
+__device__ __forceinline__ int splits_used(int total, int nsplit) {
+  return max(1, min(nsplit, LEAST > 1 ? (total - 1) / (LEAST - 1) : total));
+}
 // Tiles [t0, t1) of one split: the splits of a (bank, query block) take equal runs.
 __device__ __forceinline__ void split_range(int total, int nsplit, int split, int &t0, int &t1) {
   const int per = (total + nsplit - 1) / nsplit;
@@ -54,6 +63,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kRWaves = 4;
 constexpr int kRQ = 32 * kRWaves;  // queries per workgroup
 constexpr int kRK = 32;            // keys per tile
+constexpr int kRLeast = 1;         // tiles of a split
+constexpr int kFK = 64;            // bf16 path: keys per tile
+constexpr int kFLeast = 4;         // and tiles of a split
 
 template <int D>
 __global__ __launch_bounds__(64 * kRWaves, 1) void k_attn_f32(dkv_bank bank, const float *__restrict__ q, int nq,
@@ -70,8 +82,10 @@ __global__ __launch_bounds__(64 * kRWaves, 1) void k_attn_f32(dkv_bank bank, con
   const int m = clampi(bank.occupancy[b], 0, M);
   const int nw = win.n, ns = sink.n;
   const int nt0 = (m + kRK - 1) / kRK, nt1 = nt0 + (nw + kRK - 1) / kRK;
+  const int total = nt1 + (ns + kRK - 1) / kRK, used = splits_used<kRLeast>(total, nsplit);
+  if (split >= used) return;
   int tb, nt;
-  split_range(nt1 + (ns + kRK - 1) / kRK, nsplit, split, tb, nt);
+  split_range(total, used, split, tb, nt);
   const size_t qrow = (size_t)b * nq + (qv ? qi : nq - 1);
   float4 qf[KC];
 #pragma unroll
@@ -170,15 +184,24 @@ __global__ __launch_bounds__(64 * kRWaves, 1) void k_attn_f32(dkv_bank bank, con
 // (c: the factor of the maxima's unit to log2), divided by the common sum.
 // One wave per row group: D / 4 lanes per row, 16-byte loads.
 template <int D, int DT>
-__global__ __launch_bounds__(256) void k_attn_combine(Part part, int nsplit, size_t rows, void *out, float c) {
+__global__ __launch_bounds__(256) void k_attn_combine(dkv_bank bank, Part part, int nsplit, size_t rows, int nq, int nw,
+                                                      int ns, void *out, float c) {
   constexpr int LR = D / 4;
   const size_t row = (size_t)blockIdx.x * (256 / LR) + threadIdx.x / LR;
   const int j = 4 * (threadIdx.x % LR);
   if (row >= rows) return;
-  float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part.ml[s * rows + row].x);
-  float l = 0.0f, a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int s = 0; s < nsplit; ++s) {
+  // the splits that the row's bank took (few rows: a split call has at most some thousand workgroups)
+  constexpr int K = DT == DKV_BF16 ? kFK : kRK;
+  const uint32_t b = (uint32_t)row / (uint32_t)nq;
+  const int m = clampi(bank.occupancy[b], 0, clampi(bank.budget[b], 0, bank.capacity));
+  const int used = splits_used<DT == DKV_BF16 ? kFLeast : kRLeast>((m + K - 1) / K + (nw + K - 1) / K + (ns + K - 1) / K, nsplit);
+  const float2 ml0 = part.ml[row];  // read while `used` is on its way
+  const float4 x0 = *reinterpret_cast<const float4 *>(part.o + row * D + j);
+  float M = ml0.x;
+  for (int s = 1; s < used; ++s) M = fmaxf(M, part.ml[s * rows + row].x);
+  const float w0 = ml0.x == M ? 1.0f : __builtin_amdgcn_exp2f((ml0.x - M) * c);
+  float l = ml0.y * w0, a[4] = {x0.x * w0, x0.y * w0, x0.z * w0, x0.w * w0};
+  for (int s = 1; s < used; ++s) {
     const float2 ml = part.ml[s * rows + row];
     const float4 x = *reinterpret_cast<const float4 *>(part.o + (s * rows + row) * D + j);
     const float w = ml.x == M ? 1.0f : __builtin_amdgcn_exp2f((ml.x - M) * c);
@@ -225,7 +248,6 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kFWaves = 8;
 constexpr int kFQ = 32 * kFWaves;  // queries per workgroup
-constexpr int kFK = 64;            // keys per tile
 constexpr int kFStages = 3;        // K/V tiles resident in LDS (2 in flight while 1 is used)
 // Word 3 of a raw buffer resource: 32-bit data format, no swizzle, no
 // thread-id addressing.
@@ -370,7 +392,11 @@ __global__ __launch_bounds__(64 * kFWaves, 1) void k_attn_mfma(dkv_bank bank, co
   const int nt1 = nt0 + (nw + kFK - 1) / kFK;
   // this split's tiles [tb, nt)
   int tb = 0, nt = nt1 + (ns + kFK - 1) / kFK;
-  if constexpr (SPLIT) split_range(nt, nsplit, split, tb, nt);
+  if constexpr (SPLIT) {
+    const int used = splits_used<kFLeast>(nt, nsplit);
+    if (split >= used) return;  // whole workgroup
+    split_range(nt, used, split, tb, nt);
+  }
   auto nvalid_of = [&](int t) {
     return t < nt0 ? min(kFK, m - t * kFK) : (t < nt1 ? min(kFK, nw - (t - nt0) * kFK) : min(kFK, ns - (t - nt1) * kFK));
   };
@@ -557,7 +583,7 @@ constexpr int kMaxSplit = 64;
 int attn_splits_bf16(long long nwg, long long rows, int tiles, int d) {
   int best = 1;
   double best_cost = 0.0;
-  for (int S = 1; S <= kMaxSplit && (S == 1 || (tiles + S - 1) / S >= 4); ++S) {
+  for (int S = 1; S <= kMaxSplit && (S == 1 || (tiles + S - 1) / S >= kFLeast); ++S) {
     const double rounds = (double)((nwg * S + kCUs - 1) / kCUs);
     double cost = rounds * ((tiles + S - 1) / S + 6);
     if (S > 1) cost += 4.0 + (double)rows * S * (8.0 * d + 16.0) / (4e12 * 1.6e-6);
@@ -621,8 +647,8 @@ hipError_t attn_impl(const dkv_bank &bank, const void *q, int nq, KvSeg win, KvS
   if (nsplit > 1) {
     constexpr int kRows = 256 / (D / 4);
     // the bf16 maxima are raw scores, the fp32 ones already in log2 units
-    k_attn_combine<D, DT><<<(unsigned)((rows + kRows - 1) / kRows), 256, 0, s>>>(part, nsplit, rows, out,
-                                                                                 DT == DKV_BF16 ? scale_log2 : 1.0f);
+    k_attn_combine<D, DT><<<(unsigned)((rows + kRows - 1) / kRows), 256, 0, s>>>(bank, part, nsplit, rows, nq, win.n, sink.n,
+                                                                                 out, DT == DKV_BF16 ? scale_log2 : 1.0f);
   }
   return hipGetLastError();
 }

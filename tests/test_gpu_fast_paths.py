@@ -5,6 +5,8 @@ banks are compared bit for bit, attention within the row-normalised error of
 the path (2e-2 bf16, 1e-5 fp32).
 """
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -74,6 +76,34 @@ def test_attention_key_splits(dt, d, nq, cap, m, nw, ns):
             continue
         ref = attention(q[b], np.concatenate([K[b], sk[b]]), np.concatenate([V[b], sv[b]]), wk[b], wv[b], 1 / np.sqrt(d))
         assert attention_error(out[b], ref) <= tol
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("m", [0, 1, 192, 193, 384, 385, 5000])  # bf16: 1 split up to 6 tiles of 64 keys, then 2
+def test_attention_splits_of_banks_below_their_capacity(dt, m):
+    """The host sizes the splits by the capacity; a bank takes those that its keys fill, and the partial results
+    of the others, left as the workspace held them (NaN here), are not read."""
+    _log(f"attention splits below capacity dt={dt} m={m}")
+    rng = np.random.default_rng(m)
+    B, cap, d, nq, nw = 3, 18720, 64, 5, 0 if m else 40
+    bank = api.Bank(B, cap, d, dtype=TORCH_DT[dt])
+    draw = lambda n: synth.to_storage(rng.standard_normal((B, n, d)).astype(np.float32), dt)
+    K, V, wk, wv, q = (draw(n) for n in (m, m, nw, nw, nq))
+    bank.k.fill_(float("nan"))
+    bank.v.fill_(float("nan"))
+    bank.k[:, :m], bank.v[:, :m] = dev(K, dt), dev(V, dt)
+    bank.occupancy.fill_(m)
+    out, cb, size = torch.empty(B, nq, d, device="cuda", dtype=TORCH_DT[dt]), bank.c(), ctypes.c_size_t(0)
+    lib = api.lib()
+    assert lib.densitykv_attention_workspace_size(ctypes.byref(cb), nq, nw, 0, ctypes.byref(size)) == 0 and size.value
+    ws = torch.full((size.value // 4,), float("nan"), device="cuda")
+    qd, w = dev(q, dt), [dev(x, dt) if nw else None for x in (wk, wv)]
+    assert lib.densitykv_bank_attention_ws(ctypes.byref(cb), qd.data_ptr(), nq, None, None, 0,
+                                           *(None if x is None else x.data_ptr() for x in w), nw, out.data_ptr(),
+                                           1 / d ** 0.5, ws.data_ptr(), size.value, api._stream()) == 0
+    for b in range(B):
+        ref = attention(q[b], K[b], V[b], wk[b], wv[b], 1 / np.sqrt(d))
+        assert attention_error(host(out)[b], ref) <= (2e-2 if dt == "bf16" else 1e-5)
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
