@@ -324,10 +324,16 @@ int densitykv_bank_attention_sink(const dkv_bank *bank, const void *q, int32_t n
  * blocks (256 queries of one bank; 128 in fp32) are too few to fill the GPU splits
  * its keys over workgroups, which leave partial results in the workspace, and a
  * second kernel combines them.  densitykv_attention_workspace_size gives the
- * bytes this takes (0 when the call does not split; host-only); with a NULL
- * or smaller workspace the call runs unsplit, as densitykv_bank_attention_sink.
- * The contents need not be kept between calls; calls that overlap in time need
- * workspaces of their own.
+ * bytes this takes (0 when the call does not split; host-only); with a NULL or
+ * smaller workspace, or one that is not 16-byte aligned, the call runs unsplit, as
+ * densitykv_bank_attention_sink.  The contents need not be kept between calls;
+ * calls that overlap in time need workspaces of their own.
+ * The number of splits follows from the sizes, the capacity and the occupancy, and
+ * with it the order of a row's sums (and in bf16 the reference of its rounded
+ * weights): the result of one and the same row may differ in its last bits between
+ * calls of other n_query, capacity or workspace (2e-3 in bf16, 1e-6 in fp32, in the
+ * 2-norm).  Its error against exact arithmetic is the same, and equal calls give
+ * equal bits.
  */
 int densitykv_attention_workspace_size(const dkv_bank *bank, int32_t n_query, int32_t n_window, int32_t n_sink,
                                        size_t *bytes);

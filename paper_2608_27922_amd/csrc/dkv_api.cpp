@@ -310,10 +310,10 @@ int densitykv_bank_attention_ws(const dkv_bank *bank, const void *q, int32_t n_q
   if (n_sink > 0 && (!sink_k || !sink_v)) return DKV_ERR_INVALID;
   if (!(softmax_scale > 0.0f) || softmax_scale > 1e6f) return DKV_ERR_RANGE;
   const Geom g = geom_of(bank, 0);
-  // without room for the partial results every query block walks all its keys
+  // without room for the partial results (read and written 16 bytes at a time) every query block walks all its keys
   size_t need = 0;
   int nsplit = attention_splits(*bank, n_query, n_window, n_sink, &need);
-  if (!workspace || workspace_bytes < need) nsplit = 1;
+  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0 || workspace_bytes < need) nsplit = 1;
   hipError_t e = launch_attention(*bank, q, n_query, KvSeg{win_k, win_v, n_window}, KvSeg{sink_k, sink_v, n_sink},
                                   out, softmax_scale, g, workspace, nsplit, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DKV_OK : DKV_ERR_HIP;

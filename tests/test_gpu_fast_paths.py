@@ -107,6 +107,37 @@ def test_attention_splits_of_banks_below_their_capacity(dt, m):
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_attention_without_a_fitting_workspace(dt):
+    """No workspace, one byte too little, or an address that is not a multiple of 16: the bits of the unsplit call,
+    and nothing written to the workspace."""
+    d, m, nq = 64, 2000, 9
+    g = torch.Generator(device="cuda").manual_seed(1)
+    bank = api.Bank(2, m, d, dtype=TORCH_DT[dt])
+    bank.k.normal_(generator=g)
+    bank.v.normal_(generator=g)
+    bank.occupancy.fill_(m)
+    q = torch.randn(2, nq, d, device="cuda", generator=g).to(TORCH_DT[dt])
+    lib, cb, size = api.lib(), bank.c(), ctypes.c_size_t(0)
+    assert lib.densitykv_attention_workspace_size(ctypes.byref(cb), nq, 0, 0, ctypes.byref(size)) == 0 and size.value
+    ws = torch.full((size.value + 64,), 7, device="cuda", dtype=torch.uint8)
+
+    def run(offset, nbytes):
+        out = torch.empty_like(q)
+        assert lib.densitykv_bank_attention_ws(ctypes.byref(cb), q.data_ptr(), nq, None, None, 0, None, None, 0,
+                                               out.data_ptr(), 1 / d ** 0.5,
+                                               None if offset is None else ws.data_ptr() + offset, nbytes,
+                                               api._stream()) == 0
+        return out
+
+    ref = run(None, 0)
+    for offset, nbytes in ((0, size.value - 1), (4, size.value), (8, size.value)):
+        assert torch.equal(run(offset, nbytes), ref)
+        assert bool((ws == 7).all())
+    assert attention_error(host(run(16, size.value)), host(ref)) <= (2e-2 if dt == "bf16" else 1e-5)
+    assert not bool((ws == 7).all())
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_attention_key_splits_of_infinite_scores(dt):
     """A split whose scores are all -inf weighs nothing beside finite ones; a row of such scores alone is
     NaN, as softmax gives; a NaN key makes its row NaN in whatever split it lies."""
