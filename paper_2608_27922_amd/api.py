@@ -122,7 +122,7 @@ def _check(status: int, where: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # an integer: the c_void_p argument types convert it
 
 
 def _stream(stream=None):
