@@ -4,7 +4,9 @@
 // of "row" items against a stream of "column" items and reduces them per row:
 //
 //   k_score_mfma       rows = candidates, columns = bank states:
-//                      S_x = sum_i RNE(w_ix bs_i)  (Eq. 6)
+//                      S_x = sum_i RNE(w_ix bs_i)  (Eq. 6), or an approximation
+//                      for the banks that k_score_probe picks (then k_order_mark,
+//                      k_rescore and k_order_fix make the order exact)
 //   k_first_part_mfma  per bank state, over the first 256 ordered candidates:
 //                      64-candidate chunk sums (the prefix checkpoints of
 //                      Eqs. 8-9) and the first prefix that reaches tau b
@@ -23,7 +25,7 @@
 // Layout: a workgroup of 4 waves owns 128 row items; wave w owns 32 of them,
 // held for the whole kernel as the B operand of v_mfma_f32_32x32x16_bf16
 // (lane l <-> row item l % 32).  Column items stream through LDS in stages of 64
-// (three stages resident, loaded global -> LDS directly, key rows swizzled)
+// (two or three stages resident, loaded global -> LDS directly, key rows swizzled)
 // and form the A operand, so each lane ends up with 16 weights of its own row
 // item and reduces them in registers.
 //
@@ -148,7 +150,9 @@ __device__ __forceinline__ void load_row_frag(RowFrag<D> &rf, const Desc &src, i
 
 // ---------------------------------------------------------------------------
 // Column stages in LDS: 64 column items per stage, three stages resident (two
-// loading while one is used).  Keys go global -> LDS with 16-byte direct-to-LDS
+// loading while one is used), or two where the registers allow a fourth workgroup
+// per CU (the score up to descriptor dimension 128) or hide nothing more (the
+// crossing search).  Keys go global -> LDS with 16-byte direct-to-LDS
 // loads (no VGPR staging); a key row is 2 d bytes with its 16-byte chunk c
 // stored at c ^ (row % chunks), so that the A-operand reads (32 rows, one chunk
 // each) are free of bank conflicts.  Each item's extra K step (column_aug,
@@ -2150,8 +2154,8 @@ __global__ __launch_bounds__(256) void k_gather_sorted(const void *seg_k, const 
 inline unsigned cdiv(int a, int b) { return (unsigned)((a + b - 1) / b); }
 inline unsigned grid_of(uint64_t items, unsigned most) { return (unsigned)(items < 1 ? 1 : (items < most ? items : most)); }
 // Workgroups of a Gram kernel that the 256 CUs hold at once (three per CU; one
-// of 8 waves at descriptor dimension 256): the grid of the kernels that walk
-// equal work items.
+// of 8 waves at descriptor dimension 256): the grid of the exact re-scores, whose
+// work items are equal.
 template <int D>
 constexpr unsigned kGramWgs = gram_waves<D>() == 4 ? 3 * 256 : 256;
 

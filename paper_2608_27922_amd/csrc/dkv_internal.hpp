@@ -53,7 +53,7 @@ struct Workspace {
   uint4 *caug;         // [B, N]   of each candidate, source order
   uint4 *saug;         // [B, N]   of each candidate, score order
   int32_t *exact;      // [B] approximate scores are not worth it for the bank (k_score_probe)
-  int32_t *crossed;    // [B] first word: nonzero if some bank admits or releases a state
+  int32_t *crossed;    // [1] nonzero if some bank admits or releases a state
   int32_t *more;       // [G] 64-candidate chunks after which the group's crossing search may end (kMoreOpen: not known)
   int32_t *whole;      // [B] the bank's group is replaced whole (k_begin); the storage of m_new, free until k_select
   uint32_t *feas;      // [B, nfw], row of a group's first bank: bit r: prefix length r feasible for the group
@@ -161,8 +161,9 @@ hipError_t launch_sequential(const dkv_bank &bank, const dkv_segment &seg, const
 // barriers).  64 banks at a time, one per lane, with a scan over the wave kept in
 // LDS (pre, 65 words: the body's registers stay free of it; every wave writes the
 // same values).  A grid that nothing is left for costs a launch (about 5 us)
-// instead of one empty workgroup per possible item (85 us for the prefix-chunk
-// Gram of 360 banks).
+// instead of one empty workgroup per possible item (85 us for 264,000).  The
+// walk's registers add to the body's: the kernels that it slows where there is
+// work (the chunk sums and the whole crossing search) do without it.
 template <class Count, class Body>
 __device__ __forceinline__ void walk_items(int B, int *pre, Count count, Body body) {
   const int l = threadIdx.x & 63;

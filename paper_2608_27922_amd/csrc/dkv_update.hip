@@ -2,8 +2,8 @@
 //
 // One update of every bank from one block (Supp. C, Algorithm 1) is the kernel
 // sequence below, all on the caller's stream, with r* kept on the device.  The
-// Gram stages of bf16 banks run on MFMA (dkv_gram_mfma.hip: k_score_mfma,
-// k_order_mark, k_rescore, k_order_fix, k_first_part_mfma, k_gather_sorted,
+// Gram stages of bf16 banks run on MFMA (dkv_gram_mfma.hip: k_score_probe,
+// k_score_mfma, k_order_mark, k_rescore, k_order_fix, k_first_part_mfma, k_gather_sorted,
 // k_chunk_part_mfma, k_cross_mfma, k_rowsum_mfma, k_maint_mfma); fp32 banks use
 // dkv_gram_f32.hip.
 //

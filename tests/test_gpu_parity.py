@@ -115,7 +115,7 @@ def test_rollout_checkpoint_tiles(trace):
 def test_rollout_candidate_count_boundaries(n, trace):
     """Candidate counts at the edges of the 64-candidate chunks, the 256-candidate
     first part of the crossing search, the 512-key sort chunks, the 128-row Gram
-    blocks and the 512-column admitted x admitted splits (budget 1,100: the first
+    blocks and the runs of the symmetric admitted x admitted Gram (budget 1,100: the first
     blocks admit everything, later ones evict); without the trace outputs the
     crossing search may end after its first part."""
     _log(f"rollout candidate count n={n} trace={trace}")
