@@ -705,7 +705,7 @@ __global__ __launch_bounds__(64 * gram_waves<D>(), gram_waves<D>() == 4 ? 4 : 2)
   const int g0 = (b / g.gs) * g.gs;
   for (int j = t & 63; j < g.gs; j += 64) near |= ws.n_ev[g0 + j] != 0;
   near = __any(near);
-  if (g.N < S || m == 0 || ws.whole[b] == 2 || !near) {  // too few to judge; nothing to score; not worth it
+  if (g.N < S || m == 0 || ws.whole[b] == 2 || !near) {  // too few to tell; nothing to score; not worth it
     if (t == 0) ws.exact[b] = g.N < S || !near;
     return;
   }
