@@ -321,7 +321,8 @@ int densitykv_bank_attention_sink(const dkv_bank *bank, const void *q, int32_t n
 
 /*
  * The same attention with an optional device workspace.  A call whose query
- * blocks (256 queries of one bank; 128 in fp32) are too few to fill the GPU splits
+ * blocks (256 queries of one bank; 128 in fp32) are too few to fill the GPU, and
+ * whose keys are more than a second launch is worth, splits
  * its keys over workgroups, which leave partial results in the workspace, and a
  * second kernel combines them.  densitykv_attention_workspace_size gives the
  * bytes this takes (0 when the call does not split; host-only); with a NULL or

@@ -598,6 +598,20 @@ int attn_splits_f32(long long nwg, int tiles) {
   return (int)(fill < 1 ? 1 : (fill > tiles ? (tiles < 1 ? 1 : tiles) : fill));
 }
 
+// A split call takes a second launch and a buffer for the partial results: 14 us
+// from launch to launch where an unsplit call takes 10 (eager calls from Python; a
+// smaller GPU time shows in a captured graph only).  So calls whose one workgroup
+// per query block ends within 14 us stay unsplit.  Its time: bf16 with 2 (8) of the
+// 8 waves at work 3.0 + 0.72 (5.1 + 1.02) us per tile at d = 64, 3.7 + 0.94 (7.9 +
+// 1.34) at d = 128; fp32 3.2 + 2.9 and 3.9 + 5.1.  2 banks x 64 queries, d = 64: 10
+// tiles 10.2 us unsplit, 15.2 split; 16 tiles 14.7 and 14.8; 24 tiles 20.3 and 13.9.
+constexpr double kSplitFrom = 14.0;
+double unsplit_us(int dtype, int d, int nq, int tiles) {
+  if (dtype != DKV_BF16) return d == 64 ? 3.2 + 2.9 * tiles : 3.9 + 5.1 * tiles;
+  const int w = nq >= kFQ ? kFWaves : (nq + 31) / 32;  // waves at work
+  return d == 64 ? 2.3 + 0.35 * w + (0.62 + 0.05 * w) * tiles : 2.3 + 0.7 * w + (0.81 + 0.066 * w) * tiles;
+}
+
 }  // namespace
 
 // Splits the launch takes (1: none) and the bytes of its partial results.
@@ -605,12 +619,13 @@ int attention_splits(const dkv_bank &bank, int nq, int nw, int ns, size_t *bytes
   *bytes = 0;
   if (nq <= 0) return 1;
   const long long rows = (long long)bank.num_banks * nq;
+  const int K = bank.dtype == DKV_BF16 ? kFK : kRK;
+  const int tiles = (bank.capacity + K - 1) / K + (nw + K - 1) / K + (ns + K - 1) / K;
+  if (unsplit_us(bank.dtype, bank.head_dim, nq, tiles) < kSplitFrom) return 1;
   int S;
   if (bank.dtype == DKV_BF16) {
-    const int tiles = (bank.capacity + kFK - 1) / kFK + (nw + kFK - 1) / kFK + (ns + kFK - 1) / kFK;
     S = attn_splits_bf16((long long)((nq + kFQ - 1) / kFQ) * bank.num_banks, rows, tiles, bank.head_dim);
   } else {
-    const int tiles = (bank.capacity + kRK - 1) / kRK + (nw + kRK - 1) / kRK + (ns + kRK - 1) / kRK;
     S = attn_splits_f32((long long)((nq + kRQ - 1) / kRQ) * bank.num_banks, tiles);
     if (S > kMaxSplit) S = kMaxSplit;
   }
