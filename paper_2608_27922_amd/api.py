@@ -350,50 +350,52 @@ def update_bank_noalloc(bank: Bank, seg_k: Optional[torch.Tensor], seg_v: Option
 def _kv_segment(bank: Bank, k: Optional[torch.Tensor], v: Optional[torch.Tensor], what: str) -> int:
     if k is None:
         return 0
-    if k.dim() != 3 or k.shape[0] != bank.B or k.shape[2] != bank.d or v is None or v.shape != k.shape:
+    s = k.shape
+    if len(s) != 3 or s[0] != bank.B or s[2] != bank.d or v is None or v.shape != s:
         raise ValueError(f"{what} must be [num_banks, n, head_dim] keys and values")
     if not (k.is_contiguous() and v.is_contiguous()) or k.dtype != bank.dtype or v.dtype != bank.dtype:
         raise ValueError(f"{what} tensors must be contiguous in the bank dtype")
-    return int(k.shape[1])
+    return int(s[1])
 
 
-def _check_q(bank: Bank, q: torch.Tensor):
-    if q.dim() != 3 or q.shape[0] != bank.B or q.shape[2] != bank.d or q.dtype != bank.dtype or not q.is_contiguous():
+def _check_q(bank: Bank, q: torch.Tensor) -> int:
+    s = q.shape
+    if len(s) != 3 or s[0] != bank.B or s[2] != bank.d or q.dtype != bank.dtype or not q.is_contiguous():
         raise ValueError("q must be a contiguous [num_banks, n_query, head_dim] tensor in the bank dtype")
+    return int(s[1])
 
 
-def _attention(bank: Bank, q, sink_k, sink_v, ns, win_k, win_v, nw, softmax_scale, out, where):
+def _attention(bank: Bank, q, nq, sink_k, sink_v, ns, win_k, win_v, nw, softmax_scale, out, where):
     """The attention call; the partial results of a split one (few queries) in a
     buffer of the caching allocator, held for the call on the current stream."""
     if out is None:
         out = torch.empty_like(q)
     scale = (1.0 / bank.d ** 0.5) if softmax_scale is None else float(softmax_scale)
-    cb, nq, size = bank.c(), int(q.shape[1]), ctypes.c_size_t(0)
-    ws = None
-    if lib().densitykv_attention_workspace_size(ctypes.byref(cb), nq, nw, ns, ctypes.byref(size)) == 0 and size.value:
+    L, cb, size = lib(), bank.c(), ctypes.c_size_t(0)
+    pb, ws = ctypes.byref(cb), None
+    if L.densitykv_attention_workspace_size(pb, nq, nw, ns, ctypes.byref(size)) == 0 and size.value:
         ws = torch.empty(size.value, dtype=torch.uint8, device=q.device)
-    _check(lib().densitykv_bank_attention_ws(ctypes.byref(cb), _ptr(q), nq, _ptr(sink_k), _ptr(sink_v), ns,
-                                             _ptr(win_k), _ptr(win_v), nw, _ptr(out), ctypes.c_float(scale), _ptr(ws),
-                                             size.value, _stream()), where)
+    _check(L.densitykv_bank_attention_ws(pb, _ptr(q), nq, _ptr(sink_k), _ptr(sink_v), ns, _ptr(win_k), _ptr(win_v), nw,
+                                         _ptr(out), scale, _ptr(ws), size.value, _stream()), where)
     return out
 
 
 def bank_attention(bank: Bank, q: torch.Tensor, win_k: Optional[torch.Tensor], win_v: Optional[torch.Tensor],
                    softmax_scale: Optional[float] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """densitykv_bank_attention: softmax(q [bank; window]^T * scale) [bank; window]."""
-    _check_q(bank, q)
+    nq = _check_q(bank, q)
     nw = _kv_segment(bank, win_k, win_v, "window")
-    return _attention(bank, q, None, None, 0, win_k, win_v, nw, softmax_scale, out, "bank_attention")
+    return _attention(bank, q, nq, None, None, 0, win_k, win_v, nw, softmax_scale, out, "bank_attention")
 
 
 def bank_attention_sink(bank: Bank, q: torch.Tensor, sink_k: Optional[torch.Tensor], sink_v: Optional[torch.Tensor],
                         win_k: Optional[torch.Tensor], win_v: Optional[torch.Tensor],
                         softmax_scale: Optional[float] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """densitykv_bank_attention_sink: softmax over [bank; window; sink]."""
-    _check_q(bank, q)
+    nq = _check_q(bank, q)
     ns = _kv_segment(bank, sink_k, sink_v, "sink")
     nw = _kv_segment(bank, win_k, win_v, "window")
-    return _attention(bank, q, sink_k, sink_v, ns, win_k, win_v, nw, softmax_scale, out, "bank_attention_sink")
+    return _attention(bank, q, nq, sink_k, sink_v, ns, win_k, win_v, nw, softmax_scale, out, "bank_attention_sink")
 
 
 def pair_weight_q23(d2: torch.Tensor, params: Params = Params()) -> torch.Tensor:
